@@ -7,7 +7,7 @@
 #include <random>
 
 #include "qh_internal.h"
-#include "qh_spmv.h"
+#include "qh_sell.h"
 
 int qh_fail(qh_ctx *c, int code, const std::string &msg) {
     if (c) c->err = msg;
@@ -57,22 +57,17 @@ int upload(qh_ctx *c, T **dst, const T *src, size_t n) {
     return QH_OK;
 }
 
-int upload_csr(qh_ctx *c, DevCsr &d, const HostCsr &h, bool two) {
-    d.n = (int32_t)h.nrow;
-    d.nnz = (int64_t)h.col.size();
-    int rc;
-    if ((rc = upload(c, &d.ptr, h.ptr.data(), h.ptr.size()))) return rc;
-    if ((rc = upload(c, &d.col, h.col.data(), h.col.size()))) return rc;
-    if ((rc = upload(c, two ? &d.val2 : &d.val, h.val.data(), h.val.size()))) return rc;
-    std::vector<int2> tiles;
-    if (!qh_make_tiles(h.ptr.data(), d.n, tiles)) return qh_fail(c, QH_EINVAL, "matrix row longer than a product tile");
-    d.ntiles = (int32_t)tiles.size() - 1;
-    if ((rc = upload(c, &d.tiles, tiles.data(), tiles.size()))) return rc;
-    std::vector<int4> tbase;
-    std::vector<uint16_t> col16;
-    d.nnz_c16 = qh_compact_cols(h.col.data(), tiles, tbase, col16);
-    if ((rc = upload(c, &d.tbase, tbase.data(), tbase.size()))) return rc;
-    if ((rc = upload(c, &d.col16, col16.data(), col16.size()))) return rc;
+// A host matrix on slices with its values (rows, cpos: as qh_build_sell).
+int upload_sell_values(qh_ctx *c, DevSell &d, const HostCsr &h, const int32_t *rows, const int32_t *cpos) {
+    SellHost sh;
+    qh_build_sell((int32_t)h.nrow, h.ptr.data(), h.col.data(), rows, cpos, sh);
+    int rc = qh_upload_sell(c, d, sh);
+    if (rc) return rc;
+    std::vector<double> v(sh.src.size(), 0.0);
+    for (size_t i = 0; i < v.size(); ++i)
+        if (sh.src[i] >= 0) v[i] = h.val[sh.src[i]];
+    if ((rc = upload(c, &d.val, v.data(), v.size()))) return rc;
+    QH_HIP(c, hipStreamSynchronize(c->stream));
     return QH_OK;
 }
 
@@ -83,6 +78,19 @@ void free_all(qh_ctx *c) {
 
 int sync(qh_ctx *c) {
     QH_HIP(c, hipStreamSynchronize(c->stream));
+    return QH_OK;
+}
+
+// Edge unknowns between the host's interior-edge numbering and the device's, through a device
+// buffer `stage` of their number (queued on the stream; the caller synchronises).
+int edge_from_host(qh_ctx *c, const double *host, double *stage, double *dev) {
+    QH_HIP(c, hipMemcpyAsync(stage, host, sizeof(double) * c->A.n, hipMemcpyHostToDevice, c->stream));
+    QH_HIP(c, launch_renumber(c, c->A.n, c->order, stage, dev));
+    return QH_OK;
+}
+int edge_to_host(qh_ctx *c, const double *dev, double *stage, double *host) {
+    QH_HIP(c, launch_renumber(c, c->A.n, c->pos_of, dev, stage));
+    QH_HIP(c, hipMemcpyAsync(host, stage, sizeof(double) * c->A.n, hipMemcpyDeviceToHost, c->stream));
     return QH_OK;
 }
 
@@ -98,13 +106,28 @@ int ensure_assembled(qh_ctx *c) {
     if (!c->assembled) {
         qh_assemble(c->hm, c->phys.eps0, c->phys.mu0, c->hA, c->hCMb, c->hGtM, c->hK);
         // A: val2 = [*eps], A_S = S, val = [*eps] + tau S (device)
-        if ((rc = upload_csr(c, c->A, c->hA, true))) return rc;
-        if ((rc = upload(c, &c->A_S, c->hA.val2.data(), c->hA.val2.size()))) return rc;
-        if ((rc = qh_alloc(c, &c->A.val, c->A.nnz))) return rc;
-        if ((rc = qh_alloc(c, &c->A_rhs, c->A.nnz))) return rc;
-        if ((rc = upload_csr(c, c->CMb, c->hCMb, false))) return rc;
-        if ((rc = upload_csr(c, c->GtM, c->hGtM, false))) return rc;
-        if ((rc = upload_csr(c, c->K, c->hK, false))) return rc;
+        const HostMesh &m = c->hm;
+        c->A.n = (int32_t)c->hA.nrow;
+        c->A.nnz = (int64_t)c->hA.col.size();
+        if ((rc = upload(c, &c->A.ptr, c->hA.ptr.data(), c->hA.ptr.size())) ||
+            (rc = upload(c, &c->A.col, c->hA.col.data(), c->hA.col.size())) ||
+            (rc = upload(c, &c->A.val2, c->hA.val.data(), c->hA.val.size())) ||
+            (rc = upload(c, &c->A_S, c->hA.val2.data(), c->hA.val2.size())) ||
+            (rc = qh_alloc(c, &c->A.val, c->A.nnz)))
+            return rc;
+        {
+            SellHost sh;
+            qh_build_sell(c->A.n, c->hA.ptr.data(), c->hA.col.data(), m.order.data(), m.pos_of.data(), sh);
+            c->nnz_edge_c16 = sh.nnz_c16;
+            if ((rc = qh_upload_sell(c, c->As, sh)) || (rc = qh_alloc(c, &c->As.val, (size_t)c->As.len)) ||
+                (rc = qh_alloc(c, &c->A_rhs, (size_t)c->As.len)))
+                return rc;
+            QH_HIP(c, hipStreamSynchronize(c->stream));
+        }
+        if ((rc = upload_sell_values(c, c->CMb, c->hCMb, m.order.data(), nullptr)) ||
+            (rc = upload_sell_values(c, c->GtM, c->hGtM, nullptr, m.pos_of.data())) ||
+            (rc = upload_sell_values(c, c->K, c->hK, nullptr, nullptr)))
+            return rc;
         if ((rc = qh_cg_alloc(c, c->cge, c->A.n))) return rc;
         if ((rc = qh_cg_alloc(c, c->cgn, c->K.n))) return rc;
         if ((rc = qh_alloc(c, &c->e_old, std::max<int64_t>(1, c->A.n)))) return rc;
@@ -119,13 +142,13 @@ int ensure_assembled(qh_ctx *c) {
         std::vector<double> e_h(c->hm.Ne, 0.0), x(c->A.n);
         QH_HIP(c, hipMemcpyAsync(e_h.data(), c->e, sizeof(double) * c->hm.Ne, hipMemcpyDeviceToHost, c->stream));
         QH_HIP(c, hipStreamSynchronize(c->stream));
-        for (int32_t i = 0; i < c->A.n; ++i) x[i] = e_h[c->hm.int_edges[i]];
+        for (int32_t i = 0; i < c->A.n; ++i) x[i] = e_h[c->hm.dev_edges[i]];
         QH_HIP(c, hipMemcpyAsync(c->cge.x, x.data(), sizeof(double) * x.size(), hipMemcpyHostToDevice, c->stream));
     }
     double tau = 0.25 * c->phys.dt * c->phys.dt;
     if (tau != c->tau_assembled) {
         QH_HIP(c, launch_assemble_A(c, tau));
-        QH_HIP(c, launch_diag_inv(c, c->A, c->cge.dinv));
+        QH_HIP(c, launch_diag_inv(c, c->As, c->cge.dinv));
         c->tau_assembled = tau;
     }
     return sync(c);
@@ -153,7 +176,7 @@ int set_fields(qh_ctx *c, const double *e, const int64_t *b) {
     QH_HIP(c, hipMemsetAsync(c->divb0, 0, sizeof(int64_t) * m.Nt, c->stream));
     if (c->assembled) {
         std::vector<double> x(m.int_edges.size());
-        for (size_t i = 0; i < x.size(); ++i) x[i] = eh[m.int_edges[i]];
+        for (size_t i = 0; i < x.size(); ++i) x[i] = eh[m.dev_edges[i]];
         QH_HIP(c, hipMemcpyAsync(c->cge.x, x.data(), sizeof(double) * x.size(), hipMemcpyHostToDevice, c->stream));
     }
     c->have_fields = true;
@@ -226,6 +249,19 @@ int recompute_charge(qh_ctx *c) {
 }
 
 }  // namespace
+
+int qh_upload_sell(qh_ctx *c, DevSell &d, const SellHost &h) {
+    d.n = h.n;
+    d.ns = h.ns;
+    d.len = (int64_t)h.src.size();
+    int rc;
+    if ((rc = upload(c, &d.off, h.off.data(), h.off.size())) || (rc = upload(c, &d.base, h.base.data(), h.base.size())) ||
+        (rc = upload(c, &d.src, h.src.data(), h.src.size())) || (rc = upload(c, &d.c16, h.c16.data(), h.c16.size())))
+        return rc;
+    if (h.wide && (rc = upload(c, &d.c32, h.c32.data(), h.c32.size()))) return rc;
+    QH_HIP(c, hipStreamSynchronize(c->stream));  // h may go
+    return QH_OK;
+}
 
 extern "C" {
 
@@ -379,6 +415,7 @@ int qh_set_plane_wave(qh_ctx *c, double E0, double f0, double bandwidth, double 
             nlist.insert(nlist.end(), lists[v].begin(), lists[v].end());
             nptr.push_back((int32_t)nlist.size());
         }
+    for (int32_t &i : edge) i = m.pos_of[i];  // where the right-hand side holds the edge
     QH_HIP(c, hipStreamSynchronize(c->stream));  // a second call replaces the first one's tables
     qh_release(c, c->pw_ptr), qh_release(c, c->pw_edge), qh_release(c, c->pw_coef), qh_release(c, c->pw_xi);
     qh_release(c, c->pw_xs), qh_release(c, c->pw_tab);
@@ -440,7 +477,9 @@ int qh_mesh_upload(qh_ctx *c, int64_t n_nodes, const double *xyz, int64_t n_tets
     if ((rc = upload(c, &c->tfaces, m.tf.data(), m.tf.size()))) return rc;
     if ((rc = upload(c, &c->tsign, m.tsign.data(), m.tsign.size()))) return rc;
     if ((rc = upload(c, &c->face_edges, m.face_edges.data(), m.face_edges.size()))) return rc;
-    if ((rc = upload(c, &c->int_edges, m.int_edges.data(), std::max<size_t>(1, m.int_edges.size())))) return rc;
+    if ((rc = upload(c, &c->int_edges, m.dev_edges.data(), std::max<size_t>(1, m.dev_edges.size())))) return rc;
+    if ((rc = upload(c, &c->order, m.order.data(), std::max<size_t>(1, m.order.size())))) return rc;
+    if ((rc = upload(c, &c->pos_of, m.pos_of.data(), std::max<size_t>(1, m.pos_of.size())))) return rc;
     if ((rc = upload(c, &c->int_nodes, m.int_nodes.data(), std::max<size_t>(1, m.int_nodes.size())))) return rc;
     if ((rc = upload(c, &c->int_node_of, m.int_node_of.data(), m.int_node_of.size()))) return rc;
     if ((rc = upload(c, &c->edge_nodes, m.edges.data(), m.edges.size()))) return rc;
@@ -487,7 +526,7 @@ int qh_mesh_info(const qh_ctx *c, qh_mesh_info_t *out) {
     out->n_int_edges = (int64_t)m.int_edges.size();
     out->nnz_edge = (int64_t)c->hA.col.size();
     out->nnz_node = (int64_t)c->hK.col.size();
-    out->nnz_edge_c16 = c->A.nnz_c16;
+    out->nnz_edge_c16 = c->nnz_edge_c16;
     out->nnz_factor = c->lp.built ? c->lp.nnz : 0;
     out->nnz_factor_c16 = c->lp.built ? c->lp.nnz_c16 : 0;
     qh_ctx *mc = const_cast<qh_ctx *>(c);
@@ -890,8 +929,9 @@ int qh_edge_system_download(const qh_ctx *cc, double *rhs, double *sol) {
     if (!c) return QH_EINVAL;
     if (c->host_only) return qh_fail(c, QH_ESTATE, "host-only context has no device");
     if (!c->assembled) return qh_fail(c, QH_ESTATE, "mesh and physics first");
-    if (rhs) QH_HIP(c, hipMemcpyAsync(rhs, c->cge.b, sizeof(double) * c->A.n, hipMemcpyDeviceToHost, c->stream));
-    if (sol) QH_HIP(c, hipMemcpyAsync(sol, c->e_star, sizeof(double) * c->A.n, hipMemcpyDeviceToHost, c->stream));
+    int rc;
+    if (rhs && (rc = edge_to_host(c, c->cge.b, c->cge.z, rhs))) return rc;
+    if (sol && (rc = edge_to_host(c, c->e_star, c->cge.q, sol))) return rc;
     return sync(c);
 }
 
@@ -1080,8 +1120,8 @@ int qh_pic_step(qh_ctx *c, const qh_step_params_t *P, int32_t n_steps, qh_step_s
                 qh_tend(c, t0, QK_BOUNDARY);
             }
             const bool mixed = P->solver == QH_SOLVER_MIXED;
-            int rc = mixed ? qh_cg_solve_mixed(c, c->A, c->cge, P->tol_edge, P->max_it_edge, P->check_every, se, learned)
-                           : qh_cg_solve(c, c->A, c->cge, P->tol_edge, P->max_it_edge, P->check_every, se, nullptr,
+            int rc = mixed ? qh_cg_solve_mixed(c, c->As, c->cge, P->tol_edge, P->max_it_edge, P->check_every, se, learned)
+                           : qh_cg_solve(c, c->As, c->cge, P->tol_edge, P->max_it_edge, P->check_every, se, nullptr,
                                          false, learned);
             if (rc) return rc;
             c->last_refinements = se.refinements;
@@ -1093,7 +1133,7 @@ int qh_pic_step(qh_ctx *c, const qh_step_params_t *P, int32_t n_steps, qh_step_s
                     QH_HIP(c, hipMemcpyAsync(c->cge.x, c->e_old, sizeof(double) * c->A.n, hipMemcpyDeviceToDevice,
                                              c->stream));
                 SolveResult sj;
-                rc = qh_cg_solve(c, c->A, c->cge, P->tol_edge, P->max_it_edge, P->check_every, sj, nullptr);
+                rc = qh_cg_solve(c, c->As, c->cge, P->tol_edge, P->max_it_edge, P->check_every, sj, nullptr);
                 if (rc) return rc;
                 sj.iters += se.iters;
                 se = sj;
@@ -1103,7 +1143,7 @@ int qh_pic_step(qh_ctx *c, const qh_step_params_t *P, int32_t n_steps, qh_step_s
             if (!se.converged) status = QH_ENOTCONV;
             QH_HIP(c, hipMemcpyAsync(c->e_star, c->cge.x, sizeof(double) * c->A.n, hipMemcpyDeviceToDevice, c->stream));
             // the (rhs, solution) pair of this step into the bank, while recording
-            if (c->lp.pair_rec && (rc = qh_learned_record_pair(c, c->cge.b, c->e_star))) return rc;
+            if (c->lp.pair_rec && (rc = qh_learned_record_pair(c, c->cge.b, c->e_star, c->pos_of))) return rc;
             if (P->gauss) {
                 t0 = qh_tbeg(c);
                 QH_HIP(c, launch_gauss_rhs(c, c->scratch_d, P->tol_node));
@@ -1248,7 +1288,7 @@ int qh_fields_decompose(qh_ctx *c, double tol, int32_t max_it, double *e_ns, dou
     (void)hipEventDestroy(e1);
     if (e_s) {
         std::fill(e_s, e_s + m.Ne, 0.0);
-        for (int32_t i = 0; i < ne; ++i) e_s[m.int_edges[i]] = es[i];
+        for (int32_t i = 0; i < ne; ++i) e_s[m.dev_edges[i]] = es[i];
     }
     if (e_ns) {
         std::fill(e_ns, e_ns + m.Nn, 0.0);
@@ -1282,7 +1322,7 @@ int qh_field_solve(qh_ctx *c, int32_t system, const double *rhs, double *x, doub
     if (solver != QH_SOLVER_FP64 && solver != QH_SOLVER_MIXED) return qh_fail(c, QH_EINVAL, "solver");
     if (c->host_only) return qh_fail(c, QH_ESTATE, "host-only context has no device");
     if (!c->assembled) return qh_fail(c, QH_ESTATE, "mesh and physics first");
-    DevCsr *M = system == QH_SYS_EDGE ? &c->A : system == QH_SYS_NODE ? &c->K : nullptr;
+    DevSell *M = system == QH_SYS_EDGE ? &c->As : system == QH_SYS_NODE ? &c->K : nullptr;
     if (!M) return qh_fail(c, QH_EINVAL, "system must be QH_SYS_EDGE or QH_SYS_NODE");
     if (precond != QH_PC_JACOBI && !(precond == QH_PC_LEARNED && system == QH_SYS_EDGE))
         return qh_fail(c, QH_EINVAL, "the learned preconditioner exists for the edge system only");
@@ -1298,8 +1338,13 @@ int qh_field_solve(qh_ctx *c, int32_t system, const double *rhs, double *x, doub
     if (mixed && (rc = qh_cg_alloc32(c, c->cgx, nmax))) return rc;
     CgWork w = c->cgx;
     w.n = M->n;
-    QH_HIP(c, hipMemcpyAsync(w.b, rhs, sizeof(double) * w.n, hipMemcpyHostToDevice, c->stream));
-    QH_HIP(c, hipMemcpyAsync(w.x, x, sizeof(double) * w.n, hipMemcpyHostToDevice, c->stream));
+    const bool edge = system == QH_SYS_EDGE;
+    auto from_host = [&](const double *h, double *stage, double *d) -> int {
+        if (edge) return edge_from_host(c, h, stage, d);
+        QH_HIP(c, hipMemcpyAsync(d, h, sizeof(double) * w.n, hipMemcpyHostToDevice, c->stream));
+        return QH_OK;
+    };
+    if ((rc = from_host(rhs, w.z, w.b)) || (rc = from_host(x, w.q, w.x))) return rc;
     QH_HIP(c, launch_diag_inv(c, *M, w.dinv));
     hipEvent_t e0, e1;
     QH_HIP(c, hipEventCreate(&e0));
@@ -1312,7 +1357,7 @@ int qh_field_solve(qh_ctx *c, int32_t system, const double *rhs, double *x, doub
     int fallback = 0;
     if ((learned || mixed) && !r.converged) {
         // FP64 Jacobi restart from the iterate, or from the initial guess after non-finite values
-        if (r.flag == 3) QH_HIP(c, hipMemcpyAsync(w.x, x, sizeof(double) * w.n, hipMemcpyHostToDevice, c->stream));
+        if (r.flag == 3 && (rc = from_host(x, w.q, w.x))) return rc;
         SolveResult rj;
         rc = qh_cg_solve(c, *M, w, tol, max_it, 8, rj, nullptr);
         if (rc) return rc;
@@ -1321,7 +1366,11 @@ int qh_field_solve(qh_ctx *c, int32_t system, const double *rhs, double *x, doub
         fallback = 1;
     }
     QH_HIP(c, hipEventRecord(e1, c->stream));
-    QH_HIP(c, hipMemcpyAsync(x, w.x, sizeof(double) * w.n, hipMemcpyDeviceToHost, c->stream));
+    if (edge) {
+        if ((rc = edge_to_host(c, w.x, w.q, x))) return rc;
+    } else {
+        QH_HIP(c, hipMemcpyAsync(x, w.x, sizeof(double) * w.n, hipMemcpyDeviceToHost, c->stream));
+    }
     QH_HIP(c, hipStreamSynchronize(c->stream));
     qh_tflush(c);
     if (stats) {
@@ -1421,7 +1470,15 @@ int state_write(qh_ctx *c, Writer &w) {
     if ((rc = dev(c->e, 8 * m.Ne)) || (rc = dev(c->b, 8 * m.Nf)) || (rc = dev(c->Q, 8 * m.Nn)) ||
         (rc = dev(c->Q_bg, 8 * m.Nn)))
         return rc;
-    if (c->wave_hist && ((rc = dev(c->e_prev, 8 * ni)) || (rc = dev(c->g_prev, 8 * m.Ne)))) return rc;
+    if (c->wave_hist) {
+        if (w.p) {  // in the interior edges' order
+            std::vector<double> ep(ni);
+            QH_HIP(c, hipMemcpy(ep.data(), c->e_prev, 8 * ni, hipMemcpyDeviceToHost));
+            for (int64_t i = 0; i < ni; ++i) std::memcpy(w.p + w.n + 8 * i, &ep[m.pos_of[i]], 8);
+        }
+        w.n += 8 * ni;
+        if ((rc = dev(c->g_prev, 8 * m.Ne))) return rc;
+    }
     if (has_d && (rc = dev(c->dbnd, 8 * m.Nn))) return rc;
     for (const Species &s : c->species) {
         w.val<double>(s.qm);
@@ -1535,7 +1592,9 @@ int qh_state_load(qh_ctx *c, const void *buf, size_t len) {
     QH_HIP(c, hipMemcpy(c->Q_old, Q, 8 * m.Nn, hipMemcpyHostToDevice));
     QH_HIP(c, hipMemcpy(c->Q_bg, Qbg, 8 * m.Nn, hipMemcpyHostToDevice));
     if (wave) {
-        QH_HIP(c, hipMemcpy(c->e_prev, ep, 8 * ni, hipMemcpyHostToDevice));
+        std::vector<double> epd(ni);
+        for (int64_t i = 0; i < ni; ++i) std::memcpy(&epd[m.pos_of[i]], reinterpret_cast<const unsigned char *>(ep) + 8 * i, 8);
+        QH_HIP(c, hipMemcpy(c->e_prev, epd.data(), 8 * ni, hipMemcpyHostToDevice));
         QH_HIP(c, hipMemcpy(c->g_prev, gp, 8 * m.Ne, hipMemcpyHostToDevice));
     }
     c->wave_hist = wave;
@@ -1605,14 +1664,13 @@ int qh_precond_apply(qh_ctx *c, const double *r, double *z) {
     int rc = qh_learned_setup(c);
     if (rc) return rc;
     if (!c->lp.factor_valid && (rc = qh_learned_factor(c))) return rc;
-    const int32_t n = c->A.n;
     int32_t nmax = std::max(c->A.n, c->K.n);
     if (c->cgx.n < nmax && (rc = qh_cg_alloc(c, c->cgx, nmax))) return rc;
     // r in the standalone solve's residual slot, z in its preconditioned slot; the r.z partials
     // go to its partial buffer (unused here)
-    QH_HIP(c, hipMemcpyAsync(c->cgx.r, r, sizeof(double) * n, hipMemcpyHostToDevice, c->stream));
+    if ((rc = edge_from_host(c, r, c->cgx.q, c->cgx.r))) return rc;
     QH_HIP(c, launch_prec_apply(c, c->cgx.r, c->cgx.z, c->cgx.partial, nullptr));
-    QH_HIP(c, hipMemcpyAsync(z, c->cgx.z, sizeof(double) * n, hipMemcpyDeviceToHost, c->stream));
+    if ((rc = edge_to_host(c, c->cgx.z, c->cgx.q, z))) return rc;
     return sync(c);
 }
 
@@ -1668,7 +1726,7 @@ int qh_pairs_add(qh_ctx *c, int32_t n_pairs, const double *rhs, const double *so
     for (int32_t k = 0; k < n_pairs; ++k) {
         QH_HIP(c, hipMemcpyAsync(c->cgx.r, rhs + k * n, 8 * n, hipMemcpyHostToDevice, c->stream));
         QH_HIP(c, hipMemcpyAsync(c->cgx.z, sol + k * n, 8 * n, hipMemcpyHostToDevice, c->stream));
-        if ((rc = qh_learned_record_pair(c, c->cgx.r, c->cgx.z))) {
+        if ((rc = qh_learned_record_pair(c, c->cgx.r, c->cgx.z, nullptr))) {
             L.pair_rec = rec;
             return rc;
         }
@@ -1725,11 +1783,12 @@ int qh_precond_train(qh_ctx *c, const qh_train_params_t *P, int32_t n_pairs, con
     auto validate = [&](bool learned, int *iters) -> int {
         int tot = 0;
         for (int k = 0; k < n_val; ++k) {
-            QH_HIP(c, hipMemcpyAsync(w.b, rhs + (int64_t)k * n, 8 * (int64_t)n, hipMemcpyHostToDevice, c->stream));
+            int rc2 = edge_from_host(c, rhs + (int64_t)k * n, w.q, w.b);
+            if (rc2) return rc2;
             QH_HIP(c, hipMemsetAsync(w.x, 0, 8 * (int64_t)n, c->stream));
-            if (!learned) QH_HIP(c, launch_diag_inv(c, c->A, w.dinv));
+            if (!learned) QH_HIP(c, launch_diag_inv(c, c->As, w.dinv));
             SolveResult r;
-            int rc2 = qh_cg_solve(c, c->A, w, P->val_tol, P->val_max_it, 16, r, nullptr, false, learned);
+            rc2 = qh_cg_solve(c, c->As, w, P->val_tol, P->val_max_it, 16, r, nullptr, false, learned);
             if (rc2) return rc2;
             tot += r.converged ? r.iters : 10 * P->val_max_it;
         }
@@ -1742,7 +1801,7 @@ int qh_precond_train(qh_ctx *c, const qh_train_params_t *P, int32_t n_pairs, con
     QH_HIP(c, hipEventRecord(e0, c->stream));
     qh_train_stats_t S;
     std::memset(&S, 0, sizeof(S));
-    QH_HIP(c, launch_diag_inv(c, c->A, w.dinv));
+    QH_HIP(c, launch_diag_inv(c, c->As, w.dinv));
     if (n_val > 0 && (rc = validate(false, &S.val_iters_jacobi))) return rc;
     int best = 1 << 30;
     if (n_val > 0) {
@@ -1811,9 +1870,9 @@ int qh_precond_train(qh_ctx *c, const qh_train_params_t *P, int32_t n_pairs, con
         std::vector<double> z(n), vv(n);
         double worst = 0.0;
         for (int k = 0; k < n_val; ++k) {
-            QH_HIP(c, hipMemcpyAsync(w.r, rhs + (int64_t)k * n, 8 * (int64_t)n, hipMemcpyHostToDevice, c->stream));
+            if ((rc = edge_from_host(c, rhs + (int64_t)k * n, w.q, w.r))) return rc;
             QH_HIP(c, launch_prec_apply(c, w.r, w.z, w.partial, nullptr));
-            QH_HIP(c, hipMemcpyAsync(z.data(), w.z, 8 * (int64_t)n, hipMemcpyDeviceToHost, c->stream));
+            if ((rc = edge_to_host(c, w.z, w.q, z.data()))) return rc;
             QH_HIP(c, hipStreamSynchronize(c->stream));
             const double *x = sol + (int64_t)k * n;
             for (int32_t i = 0; i < n; ++i) vv[i] = x[i] - z[i];

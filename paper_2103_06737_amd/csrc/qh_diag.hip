@@ -26,18 +26,19 @@ __device__ __forceinline__ double block_sum(double v, double *lds) {
     return s;
 }
 
-// part[blockIdx.x] = sum over this block's rows i of x_i * sum_j eps_ij x_j
+// part[blockIdx.x] = sum over this block's rows i of x_i * sum_j eps_ij x_j (unknown i at x[pos[i]])
 __global__ void __launch_bounds__(kThreads) k_energy_e(int32_t n, const int32_t *__restrict__ ptr,
                                                        const int32_t *__restrict__ col,
                                                        const double *__restrict__ eps,
+                                                       const int32_t *__restrict__ pos,
                                                        const double *__restrict__ x, double *__restrict__ part) {
     __shared__ double lds[kThreads / 64];
     const int32_t i = blockIdx.x * kThreads + threadIdx.x;
     double v = 0.0;
     if (i < n) {
         double s = 0.0;
-        for (int32_t k = ptr[i]; k < ptr[i + 1]; ++k) s += eps[k] * x[col[k]];
-        v = x[i] * s;
+        for (int32_t k = ptr[i]; k < ptr[i + 1]; ++k) s += eps[k] * x[pos[col[k]]];
+        v = x[pos[i]] * s;
     }
     v = block_sum(v, lds);
     if (threadIdx.x == 0) part[blockIdx.x] = v;
@@ -126,7 +127,7 @@ hipError_t launch_field_energy(qh_ctx *c, double *part, double *out) {
     const int32_t me = std::max<int32_t>((n + kThreads - 1) / kThreads, 1);
     const int32_t mb = std::max<int32_t>((nt + kThreads - 1) / kThreads, 1);
     hipLaunchKernelGGL(k_energy_e, dim3(me), dim3(kThreads), 0, c->stream, n, c->A.ptr, c->A.col, c->A.val2,
-                       c->cge.x, part);
+                       c->pos_of, c->cge.x, part);
     hipLaunchKernelGGL(k_energy_b, dim3(mb), dim3(kThreads), 0, c->stream, nt, c->tnodes, c->tfaces, c->xyz_d,
                        c->b, c->phys.u_b, part + me);
     hipLaunchKernelGGL(k_energy_finish, dim3(1), dim3(kThreads), 0, c->stream, part, me, part + me, mb,

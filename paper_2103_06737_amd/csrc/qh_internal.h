@@ -47,6 +47,9 @@ struct HostMesh {
     std::vector<uint8_t> wall_edge, wall_node, wall_face;
     std::vector<int32_t> int_edge_of, int_node_of;  // global -> interior index or -1
     std::vector<int32_t> int_edges, int_nodes;      // interior index -> global
+    // device numbering of the edge unknowns (qh_sell.h): position -> interior index and back, and
+    // position -> global edge
+    std::vector<int32_t> order, pos_of, dev_edges;
     std::vector<double> grad;                   // 12*Nt: grad lambda_0..3
     std::vector<double> vol;                    // Nt
     std::vector<double> cen;                    // 3*Nt
@@ -69,21 +72,40 @@ void qh_assemble(const HostMesh &m, double eps0, double mu0, HostCsr &A, HostCsr
 
 // ---------------------------------------------------------------------------------------
 // Device containers
-// Column indices of a tiled matrix as the tiled products read them. A tile whose columns lie in
-// at most four windows [w_k, w_k + 2^14) keeps each as 16 bits: the window number in the top two
-// bits, the offset from its start in the low fourteen (tbase[tile] = {w_0, w_1, w_2, w_3}); a
-// row couples a few index clusters (on a box mesh: the layers below, at and above it), each
-// narrow. Any other tile reads the 32-bit columns (tbase[tile].x = -1). tbase == nullptr: 32-bit
-// columns throughout.
-struct TileCols {
-    const int32_t *col;
-    const uint16_t *col16;
-    const int4 *tbase;
-    // optional, BF16 values only: value bits << 16 | 16-bit column per entry, one load each in
-    // the compact tiles (the value and column arrays still serve the others)
-    const uint32_t *pk = nullptr;
-    // every tile compact and non-empty: the packed words alone describe the matrix
-    bool all_pk = false;
+// A sparse matrix in slices of 64 rows (qh_sell.h): off[s] .. off[s + 1], in units of 64 entries,
+// are slice s's entries, entry k of its 64 rows side by side. A slice whose columns lie in at most
+// four windows [w_k, w_k + 2^14) keeps each as 16 bits: the window number in the top two bits, the
+// offset from its start in the low fourteen (base[s] = {w_0, w_1, w_2, w_3}); a row couples a few
+// index clusters (on a box mesh: the layers below, at and above it), each narrow. Any other slice
+// reads 32-bit columns (base[s].x = -1).
+struct SellCols {
+    const int32_t *off;
+    const int4 *base;
+    const uint16_t *c16;
+    const int32_t *c32;
+};
+
+struct SellHost {
+    int32_t n = 0, ns = 0;
+    std::vector<int32_t> off;
+    std::vector<int32_t> src;   // CSR entry of each stored one, -1: padding
+    std::vector<int32_t> c32;
+    std::vector<uint16_t> c16;
+    std::vector<int4> base;
+    int64_t nnz_c16 = 0;        // entries (without padding) read with 16-bit columns
+    bool wide = false;          // some slice reads 32-bit columns
+};
+
+struct DevSell {
+    int32_t n = 0, ns = 0;
+    int64_t len = 0;            // stored entries, padding included
+    int32_t *off = nullptr, *src = nullptr, *c32 = nullptr;
+    int4 *base = nullptr;
+    uint16_t *c16 = nullptr;
+    double *val = nullptr;
+    float *val32 = nullptr;     // FP32 copy of val for the mixed-precision solve (allocated on first use)
+    double val32_tau = -1.0;    // the context's tau when val32 was taken (A's values follow dt)
+    SellCols cols() const { return SellCols{off, base, c16, c32}; }
 };
 
 struct DevCsr {
@@ -92,14 +114,6 @@ struct DevCsr {
     int32_t *ptr = nullptr, *col = nullptr;
     double *val = nullptr;
     double *val2 = nullptr;
-    float *val32 = nullptr; // FP32 copy of val for the mixed-precision solve (allocated on first use)
-    double val32_tau = -1.0; // the context's tau when val32 was taken (A's values follow dt)
-    int2 *tiles = nullptr;  // row tiles of the tiled product (qh_spmv.h)
-    int32_t ntiles = 0;
-    uint16_t *col16 = nullptr;  // per-tile 16-bit columns (TileCols)
-    int4 *tbase = nullptr;
-    int64_t nnz_c16 = 0;        // entries in tiles with 16-bit columns
-    TileCols cols() const { return TileCols{col, col16, tbase}; }
 };
 
 struct Species {
@@ -145,17 +159,13 @@ struct LearnedPrec {
     std::vector<int32_t> h_row, h_col;
     int32_t *gptr = nullptr, *gcol = nullptr, *grow = nullptr;   // G, row-major
     int32_t *tptr = nullptr, *tcol = nullptr, *tsrc = nullptr;   // G^T rows; tsrc: entry of G
-    int2 *gtiles = nullptr, *ttiles = nullptr;                   // row tiles of G and G^T
-    int32_t ngtiles = 0, nttiles = 0;
-    uint16_t *gcol16 = nullptr, *tcol16 = nullptr;               // their compact columns (TileCols)
-    int4 *gtbase = nullptr, *ttbase = nullptr;
-    int64_t nnz_c16 = 0;                                         // entries of G and G^T in such tiles
-    bool g_all_pk = false, t_all_pk = false;                     // every tile compact and non-empty
+    DevSell gs, ts;                                              // G and G^T as the application reads them
+    int64_t nnz_c16 = 0;                                         // their entries with 16-bit columns
     unsigned short *feats = nullptr;         // nnz x 16 BF16 features
     float *gscale = nullptr;                 // 1/sqrt(A_jj) (1/sqrt(A_ii) on the diagonal)
     float *gval = nullptr, *tval = nullptr, *o = nullptr, *d_o = nullptr;
-    uint16_t *gval_h = nullptr, *tval_h = nullptr;  // BF16 copies of G and G^T for the application
-    uint32_t *gpk = nullptr, *tpk = nullptr;         // the same packed with their 16-bit columns
+    uint32_t *gpk = nullptr, *tpk = nullptr; // BF16 copies packed with their 16-bit columns, in the slices' order
+    bool pk_valid = false;                   // gpk and tpk hold the present factor
     double *y = nullptr;
     float *y32 = nullptr;  // the application's intermediate G r on FP32 vectors (allocated on first use)
     float *w = nullptr, *best_w = nullptr, *adam_m = nullptr, *adam_v = nullptr, *grad = nullptr;
@@ -195,7 +205,9 @@ struct qh_ctx {
     int8_t *tsign = nullptr;     // Nt
     float4 *frec = nullptr;      // 3*Nt: (alpha, beta_x) (beta_y, beta_z, B_x, B_y) (B_z, -, -, -)
     int32_t *face_edges = nullptr;  // 3*Nf
-    int32_t *int_edges = nullptr;   // interior -> global edge
+    int32_t *int_edges = nullptr;   // position of an edge unknown -> global edge
+    int32_t *order = nullptr;       // position of an edge unknown -> interior index
+    int32_t *pos_of = nullptr;      // interior index of an edge unknown (as in the C ABI) -> position
     int32_t *int_nodes = nullptr;   // interior -> global node
     int32_t *int_node_of = nullptr; // global node -> interior or -1
     int32_t *edge_nodes = nullptr;  // 2*Ne
@@ -206,9 +218,13 @@ struct qh_ctx {
     unsigned int *mail_cnt = nullptr;            // per mailbox (run of kMailTets tets): records posted
     int32_t *mail = nullptr;                     // mailboxes: ceil(Nt / kMailTets) x kMailCap x kMailWords int32
 
-    DevCsr A, CMb, GtM, K;  // A: val = [*eps] + tau S, val2 = [*eps]
+    // A in CSR, interior-edge numbering (training, energy): val = [*eps] + tau S, val2 = [*eps];
+    // the products of the field update on slices, edge unknowns in device numbering
+    DevCsr A;
+    DevSell As, CMb, GtM, K;
+    int64_t nnz_edge_c16 = 0;  // entries of A with 16-bit columns (without padding)
     double *A_S = nullptr;  // S values on the pattern of A
-    double *A_rhs = nullptr;  // [*eps] - tau S on the pattern of A (right-hand side)
+    double *A_rhs = nullptr;  // [*eps] - tau S on the slices of A (right-hand side)
     double tau_assembled = -1.0;
     int32_t last_refinements = 0;  // the last step's reliable updates (mixed-precision edge solve)
     bool assembled = false;
@@ -363,14 +379,17 @@ struct SolveResult {
 };
 int qh_cg_alloc(qh_ctx *c, CgWork &w, int32_t n);
 // Jacobi PCG on matrix M, rhs in w.b, initial guess in w.x; thr2 target on ||r||^2 set on device.
-int qh_cg_solve(qh_ctx *c, const DevCsr &M, CgWork &w, double tol, int max_it, int check_every,
+int qh_cg_solve(qh_ctx *c, const DevSell &M, CgWork &w, double tol, int max_it, int check_every,
                 SolveResult &out, const double *abs_thr2_dev, bool node_system = false, bool learned = false);
 // The edge system in mixed precision: FP32 PCG with FP64 reliable updates (Jacobi or the
 // learned preconditioner), stopping on the FP64 residual ||b - A x|| <= tol ||b||.
-int qh_cg_solve_mixed(qh_ctx *c, DevCsr &M, CgWork &w, double tol, int max_it, int check_every,
+int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, int check_every,
                       SolveResult &out, bool learned);
 // FP32 buffers of a CgWork for n unknowns (kept when large enough)
 int qh_cg_alloc32(qh_ctx *c, CgWork &w, int32_t n);
+
+// uploads the slices (columns, entry map; values are allocated by the caller)
+int qh_upload_sell(qh_ctx *c, DevSell &d, const SellHost &h);
 
 // qh_learned.hip
 int qh_learned_setup(qh_ctx *c);
@@ -381,12 +400,16 @@ hipError_t launch_prec_apply(qh_ctx *c, const double *r, double *z, double *part
 hipError_t launch_prec_apply32(qh_ctx *c, const float *r, float *z, double *part, const int32_t *done);
 int qh_learned_loss_grad(qh_ctx *c, const float *V_dev, bool want_grad, double pair_weight = 0.0,
                          const int32_t *pair_idx = nullptr);
-// records the edge system's (rhs, solution) into the next slot of the pair bank
-int qh_learned_record_pair(qh_ctx *c, const double *rhs, const double *sol);
+// records the edge system's (rhs, solution) into the next slot of the pair bank (interior-edge
+// numbering); pos: where each unknown stands in rhs and sol (null: in that numbering)
+int qh_learned_record_pair(qh_ctx *c, const double *rhs, const double *sol, const int32_t *pos);
 constexpr int QH_PAIR_BATCH = 16;  // pairs per training step
 int qh_learned_adam(qh_ctx *c, float lr, int32_t t);
 int qh_learned_probes(qh_ctx *c, float *V_dev, uint64_t seed);
-hipError_t launch_diag_inv(qh_ctx *c, const DevCsr &M, double *dinv);
+// out[i] = in[idx[i]]: edge unknowns from the C ABI's numbering to the device's (idx = order) or
+// back (idx = pos_of)
+hipError_t launch_renumber(qh_ctx *c, int64_t n, const int32_t *idx, const double *in, double *out);
+hipError_t launch_diag_inv(qh_ctx *c, const DevSell &M, double *dinv);
 hipError_t launch_assemble_A(qh_ctx *c, double tau);
 hipError_t launch_edge_rhs(qh_ctx *c);
 hipError_t launch_wave_rhs(qh_ctx *c);
@@ -396,6 +419,4 @@ hipError_t launch_gauss_apply(qh_ctx *c);
 hipError_t launch_div_e(qh_ctx *c, double *out3, double tol_n);
 hipError_t launch_grad_add(qh_ctx *c, const double *delta, double *e_int);
 hipError_t launch_faraday(qh_ctx *c);
-hipError_t launch_true_residual(qh_ctx *c, const DevCsr &M, const double *x, const double *b,
-                                double *out2 /* [0] ||b-Ax||^2 [1] ||b||^2 */);
 hipError_t launch_gauss_check(qh_ctx *c, double *out3);

@@ -20,7 +20,7 @@
 #include <random>
 
 #include "qh_internal.h"
-#include "qh_spmv.h"
+#include "qh_sell.h"
 
 namespace {
 
@@ -209,58 +209,61 @@ __global__ void __launch_bounds__(64 * kWaves) k_mlp_factor(const float *__restr
     }
 }
 
-// G^T values out[k] = in[src[k]], and BF16 copies of G and G^T for the application
+// G^T values out[k] = in[src[k]]
 __global__ void k_gather_f32(int64_t n, const int32_t *__restrict__ src, const float *__restrict__ in,
-                             float *__restrict__ out, uint16_t *__restrict__ in_h, uint16_t *__restrict__ out_h,
-                             const uint16_t *__restrict__ in_c16, const uint16_t *__restrict__ out_c16,
-                             uint32_t *__restrict__ in_pk, uint32_t *__restrict__ out_pk) {
+                             float *__restrict__ out) {
     int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < n) {
-        const float v = in[src[k]];
-        out[k] = v;
-        const uint32_t vo = (uint16_t)f2bf(v), vi = (uint16_t)f2bf(in[k]);
-        out_h[k] = (uint16_t)vo;
-        in_h[k] = (uint16_t)vi;
-        // packed with the compact columns (BF16 bits high, column low)
-        out_pk[k] = vo << 16 | out_c16[k];
-        in_pk[k] = vi << 16 | in_c16[k];
-    }
+    if (k < n) out[k] = in[src[k]];
+}
+
+// BF16 copy of G or G^T for the application, packed with the 16-bit columns (value bits high,
+// column low) in the order of the slices (src: entry of in, -1: padding)
+__global__ void k_pack_slices(int64_t len, const int32_t *__restrict__ src, const float *__restrict__ in,
+                              const uint16_t *__restrict__ c16, uint32_t *__restrict__ pk) {
+    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= len) return;
+    const int32_t e = src[k];
+    const uint32_t h = e >= 0 ? (uint16_t)f2bf(in[e]) : 0u;
+    pk[k] = h << 16 | c16[k];
 }
 
 // ---------------------------------------------------------------------------------------
 // Preconditioner application: y = G r (rows of G), then z = G^T y (rows of G^T) with the
 // partials of r.z, from BF16 copies of G and G^T (the network's own precision; the products
-// and sums are FP64, so M = G^T G stays one fixed SPD operator), both as tiled products (each block a contiguous, XCD-grouped range of row
-// tiles). Grids are multiples of 8 blocks, at most 2048.
+// and sums are FP64, so M = G^T G stays one fixed SPD operator), both as products over slices of
+// 64 rows (qh_sell.h), the unknowns in device numbering.
 // T: the vectors' type (FP64, or FP32 in the inner iterations of the mixed-precision solve; the
 // products and sums are FP64 either way, and the dot product takes the stored values).
+constexpr int kUPrec = 8;  // entries in flight per lane
 template <bool DOT, typename T>
-__global__ void __launch_bounds__(kTileThreads) k_prec_g(const int2 *__restrict__ tiles, int32_t ntiles,
-                                                         const int32_t *__restrict__ ptr,
-                                                         const TileCols cols, const uint16_t *__restrict__ val,
+__global__ void __launch_bounds__(kSellThreads) k_prec_g(int32_t n, int32_t ns, const SellCols S,
+                                                         const uint32_t *__restrict__ pk,
                                                          const T *__restrict__ in, T *__restrict__ out,
                                                          const T *__restrict__ r, double *__restrict__ part,
                                                          const int32_t *__restrict__ done) {
     if (done && done[0]) return;  // the solve has converged: nothing left to precondition
-    __shared__ double prod[kTileCap];
+    const SellRange sr = sell_range(ns);
     double acc = 0.0;
-    auto pre = [&](int32_t row) { return DOT ? r[row] : (T)0; };
-    auto epi = [&](int32_t row, double s, T rr) {
-        const T st = (T)s;
-        out[row] = st;
-        if (DOT) acc += (double)st * (double)rr;
-    };
-    if (cols.all_pk)  // packed words only: the next tile's loaded during this one
-        tile_spmv_pk(tiles, ntiles, ptr, cols, in, prod, pre, epi);
-    else
-        tile_spmv(tiles, ntiles, ptr, cols, val, in, prod, pre, epi);
+    for (int32_t s = sr.begin; s < sr.end; s += sr.step) {
+        const int32_t row = s * kSlice + (int32_t)(threadIdx.x & 63);
+        const double rr = DOT && row < n ? (double)r[row] : 0.0;
+        const T st = (T)sell_dot_pk<kUPrec>(S, pk, in, s);
+        if (row < n) {
+            out[row] = st;
+            if (DOT) acc += (double)st * rr;
+        }
+    }
     if (DOT) {
-        __shared__ double sh[kTileThreads / 64];
+        __shared__ double sh[kSellWaves];
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
         if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
         __syncthreads();
-        if (threadIdx.x == 0) part[blockIdx.x] = sh[0] + sh[1] + sh[2] + sh[3];
+        if (threadIdx.x == 0) {
+            double t = 0.0;
+            for (int w = 0; w < kSellWaves; ++w) t += sh[w];
+            part[blockIdx.x] = t;
+        }
     }
 }
 
@@ -420,14 +423,17 @@ __global__ void __launch_bounds__(256) k_kaporin_grad(int64_t nnz, int32_t n, co
 //   dL_E/dG_ij = -(2/P) sum_k (Y_ik AV_jk + GAV_ik B_jk) / x_k.b_k,
 // added with a weight to the Kaporin gradient in d o (through G's dependence on o).
 
-// one pair into bank slot k: FP32 copies of b and x, and x.b (FP64) as per-block partials
-__global__ void __launch_bounds__(256) k_pair_store(int32_t n, const double *__restrict__ b, const double *__restrict__ x,
+// one pair into its bank slot: FP32 copies of b and x (unknown i at pos[i], null: at i), and x.b
+// (FP64) as per-block partials
+__global__ void __launch_bounds__(256) k_pair_store(int32_t n, const int32_t *__restrict__ pos,
+                                                    const double *__restrict__ b, const double *__restrict__ x,
                                                     float *__restrict__ pb, float *__restrict__ px,
                                                     double *__restrict__ part) {
     __shared__ double sh[256];
     double d = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const double bi = b[i], xi = x[i];
+        const int64_t k = pos ? pos[i] : i;
+        const double bi = b[k], xi = x[k];
         pb[i] = (float)bi;
         px[i] = (float)xi;
         d += bi * xi;
@@ -765,8 +771,7 @@ int qh_learned_setup(qh_ctx *c) {
             (rc = qh_alloc(c, &L.tptr, n + 1)) || (rc = qh_alloc(c, &L.tcol, nnz)) || (rc = qh_alloc(c, &L.tsrc, nnz)) ||
             (rc = qh_alloc(c, &L.feats, nnz * kF)) || (rc = qh_alloc(c, &L.gscale, nnz)) ||
             (rc = qh_alloc(c, &L.gval, nnz)) || (rc = qh_alloc(c, &L.tval, nnz)) ||
-            (rc = qh_alloc(c, &L.gval_h, nnz)) || (rc = qh_alloc(c, &L.tval_h, nnz)) || (rc = qh_alloc(c, &L.o, nnz)) ||
-            (rc = qh_alloc(c, &L.d_o, nnz)) || (rc = qh_alloc(c, &L.y, n)) || (rc = qh_alloc(c, &L.w, 5313)) ||
+            (rc = qh_alloc(c, &L.o, nnz)) || (rc = qh_alloc(c, &L.d_o, nnz)) || (rc = qh_alloc(c, &L.y, n)) || (rc = qh_alloc(c, &L.w, 5313)) ||
             (rc = qh_alloc(c, &L.adam_m, 5313)) || (rc = qh_alloc(c, &L.adam_v, 5313)) ||
             (rc = qh_alloc(c, &L.grad, 5313)) || (rc = qh_alloc(c, &L.loss, 4)))
             return rc;
@@ -776,32 +781,16 @@ int qh_learned_setup(qh_ctx *c) {
         QH_HIP(c, hipMemcpyAsync(L.tptr, tptr.data(), 4 * (n + 1), hipMemcpyHostToDevice, c->stream));
         QH_HIP(c, hipMemcpyAsync(L.tcol, tcol.data(), 4 * nnz, hipMemcpyHostToDevice, c->stream));
         QH_HIP(c, hipMemcpyAsync(L.tsrc, tsrc.data(), 4 * nnz, hipMemcpyHostToDevice, c->stream));
-        std::vector<int2> gt, tt;
-        if (!qh_make_tiles(gptr.data(), n, gt) || !qh_make_tiles(tptr.data(), n, tt))
-            return qh_fail(c, QH_EINVAL, "factor row longer than a product tile");
-        L.ngtiles = (int32_t)gt.size() - 1;
-        L.nttiles = (int32_t)tt.size() - 1;
-        if ((rc = qh_alloc(c, &L.gtiles, gt.size())) || (rc = qh_alloc(c, &L.ttiles, tt.size()))) return rc;
-        QH_HIP(c, hipMemcpyAsync(L.gtiles, gt.data(), sizeof(int2) * gt.size(), hipMemcpyHostToDevice, c->stream));
-        QH_HIP(c, hipMemcpyAsync(L.ttiles, tt.data(), sizeof(int2) * tt.size(), hipMemcpyHostToDevice, c->stream));
-        std::vector<int4> gb, tb;
-        std::vector<uint16_t> g16, t16;
-        L.nnz_c16 = qh_compact_cols(gcol.data(), gt, gb, g16) + qh_compact_cols(tcol.data(), tt, tb, t16);
-        auto all_compact = [](const std::vector<int4> &b) {
-            for (const int4 &q : b)
-                if (q.x < 0) return false;
-            return !b.empty();
-        };
-        L.g_all_pk = all_compact(gb);
-        L.t_all_pk = all_compact(tb);
-        if ((rc = qh_alloc(c, &L.gtbase, gb.size())) || (rc = qh_alloc(c, &L.ttbase, tb.size())) ||
-            (rc = qh_alloc(c, &L.gcol16, g16.size())) || (rc = qh_alloc(c, &L.tcol16, t16.size())) ||
-            (rc = qh_alloc(c, &L.gpk, g16.size())) || (rc = qh_alloc(c, &L.tpk, t16.size())))
+        // G and G^T on slices, unknowns in device numbering; G^T's entries refer to G's
+        SellHost gh, th;
+        qh_build_sell(n, gptr.data(), gcol.data(), m.order.data(), m.pos_of.data(), gh);
+        qh_build_sell(n, tptr.data(), tcol.data(), m.order.data(), m.pos_of.data(), th);
+        for (int32_t &q : th.src)
+            if (q >= 0) q = tsrc[q];
+        L.nnz_c16 = gh.nnz_c16 + th.nnz_c16;
+        if ((rc = qh_upload_sell(c, L.gs, gh)) || (rc = qh_upload_sell(c, L.ts, th)) ||
+            (rc = qh_alloc(c, &L.gpk, (size_t)L.gs.len)) || (rc = qh_alloc(c, &L.tpk, (size_t)L.ts.len)))
             return rc;
-        QH_HIP(c, hipMemcpyAsync(L.gtbase, gb.data(), sizeof(int4) * gb.size(), hipMemcpyHostToDevice, c->stream));
-        QH_HIP(c, hipMemcpyAsync(L.ttbase, tb.data(), sizeof(int4) * tb.size(), hipMemcpyHostToDevice, c->stream));
-        QH_HIP(c, hipMemcpyAsync(L.gcol16, g16.data(), 2 * g16.size(), hipMemcpyHostToDevice, c->stream));
-        QH_HIP(c, hipMemcpyAsync(L.tcol16, t16.data(), 2 * t16.size(), hipMemcpyHostToDevice, c->stream));
         QH_HIP(c, hipStreamSynchronize(c->stream));
         if (!L.have_weights) {
             // He-normal hidden layers, zero output layer: the initial network is Jacobi
@@ -894,23 +883,42 @@ int qh_learned_factor(qh_ctx *c) {
     hipLaunchKernelGGL(k_mlp_factor, dim3(mlp_grid(L.nnz)), dim3(64 * kWaves), 0, c->stream, L.w, L.feats, L.grow,
                        L.gcol, L.gscale, L.nnz, L.o, L.gval);
     hipLaunchKernelGGL(k_gather_f32, dim3((unsigned)((L.nnz + 255) / 256)), dim3(256), 0, c->stream, L.nnz, L.tsrc,
-                       L.gval, L.tval, L.gval_h, L.tval_h, (const uint16_t *)L.gcol16, (const uint16_t *)L.tcol16,
-                       L.gpk, L.tpk);
+                       L.gval, L.tval);
     QH_HIP(c, hipGetLastError());
     L.factor_valid = true;
+    L.pk_valid = false;
     return QH_OK;
 }
 
-unsigned qh_prec_grid(qh_ctx *c) { return tile_grid(c->lp.nttiles); }
+unsigned qh_prec_grid(qh_ctx *c) { return sell_grid(c->lp.ts.ns); }
+
+// The packed copies of the present factor: made when an application first needs them (training
+// steps, which change the factor every time, do not).
+static void pack_factor(qh_ctx *c) {
+    LearnedPrec &L = c->lp;
+    if (L.pk_valid) return;
+    hipLaunchKernelGGL(k_pack_slices, dim3((unsigned)((L.gs.len + 255) / 256)), dim3(256), 0, c->stream, L.gs.len,
+                       L.gs.src, L.gval, L.gs.c16, L.gpk);
+    hipLaunchKernelGGL(k_pack_slices, dim3((unsigned)((L.ts.len + 255) / 256)), dim3(256), 0, c->stream, L.ts.len,
+                       L.ts.src, L.gval, L.ts.c16, L.tpk);
+    L.pk_valid = true;
+}
+
+template <typename T>
+static void prec_apply(qh_ctx *c, const T *r, T *y, T *z, double *part, const int32_t *done) {
+    LearnedPrec &L = c->lp;
+    if (L.n == 0) return;
+    pack_factor(c);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_prec_g<false, T>), dim3(sell_grid(L.gs.ns)), dim3(kSellThreads), 0, c->stream,
+                       L.n, L.gs.ns, L.gs.cols(), L.gpk, r, y, (const T *)nullptr, (double *)nullptr, done);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_prec_g<true, T>), dim3(sell_grid(L.ts.ns)), dim3(kSellThreads), 0, c->stream,
+                       L.n, L.ts.ns, L.ts.cols(), L.tpk, (const T *)y, z, r, part, done);
+}
 
 // z = G^T (G r); part[block] = partial r.z (qh_prec_grid blocks). With done != null both
 // passes return at once when done[0] is set (a converged solve).
 hipError_t launch_prec_apply(qh_ctx *c, const double *r, double *z, double *part, const int32_t *done) {
-    LearnedPrec &L = c->lp;
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_prec_g<false, double>), dim3(tile_grid(L.ngtiles)), dim3(kTileThreads), 0, c->stream, L.gtiles,
-                       L.ngtiles, L.gptr, TileCols{L.gcol, L.gcol16, L.gtbase, L.gpk, L.g_all_pk}, L.gval_h, r, L.y, (const double *)nullptr, (double *)nullptr, done);
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_prec_g<true, double>), dim3(tile_grid(L.nttiles)), dim3(kTileThreads), 0, c->stream, L.ttiles,
-                       L.nttiles, L.tptr, TileCols{L.tcol, L.tcol16, L.ttbase, L.tpk, L.t_all_pk}, L.tval_h, L.y, z, r, part, done);
+    prec_apply<double>(c, r, c->lp.y, z, part, done);
     return hipGetLastError();
 }
 
@@ -923,21 +931,18 @@ hipError_t launch_prec_apply32(qh_ctx *c, const float *r, float *z, double *part
         c->allocations.push_back((void *)y);
         L.y32 = y;
     }
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_prec_g<false, float>), dim3(tile_grid(L.ngtiles)), dim3(kTileThreads), 0, c->stream, L.gtiles,
-                       L.ngtiles, L.gptr, TileCols{L.gcol, L.gcol16, L.gtbase, L.gpk, L.g_all_pk}, L.gval_h, r, L.y32, (const float *)nullptr, (double *)nullptr, done);
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_prec_g<true, float>), dim3(tile_grid(L.nttiles)), dim3(kTileThreads), 0, c->stream, L.ttiles,
-                       L.nttiles, L.tptr, TileCols{L.tcol, L.tcol16, L.ttbase, L.tpk, L.t_all_pk}, L.tval_h, L.y32, z, r, part, done);
+    prec_apply<float>(c, r, L.y32, z, part, done);
     return hipGetLastError();
 }
 
 // Loss and gradient for the current weights with probes V (device, [n][16] floats).
-int qh_learned_record_pair(qh_ctx *c, const double *rhs, const double *sol) {
+int qh_learned_record_pair(qh_ctx *c, const double *rhs, const double *sol, const int32_t *pos) {
     LearnedPrec &L = c->lp;
     if (!L.pair_rec || L.pair_n >= L.pair_cap) return QH_OK;
     const int32_t n = c->A.n;
     const unsigned g = (unsigned)std::min<int64_t>((n + 255) / 256, 1024);
     const int64_t off = (int64_t)L.pair_n * n;
-    hipLaunchKernelGGL(k_pair_store, dim3(g), dim3(256), 0, c->stream, n, rhs, sol, L.pair_b + off, L.pair_x + off,
+    hipLaunchKernelGGL(k_pair_store, dim3(g), dim3(256), 0, c->stream, n, pos, rhs, sol, L.pair_b + off, L.pair_x + off,
                        L.ppart);
     hipLaunchKernelGGL(k_pair_store_finish, dim3(1), dim3(256), 0, c->stream, L.ppart, (int32_t)g,
                        L.pair_xb + L.pair_n);

@@ -5,6 +5,7 @@
 #include <numeric>
 
 #include "qh_internal.h"
+#include "qh_sell.h"
 
 namespace {
 
@@ -203,6 +204,29 @@ std::string qh_build_mesh(HostMesh &m, int64_t Nn, const double *xyz, int64_t Nt
         for (int64_t e = 0; e < m.Ne; ++e) {
             m.n2e[cur[m.edges[2 * e]]++] = -(int32_t)(e + 1);
             m.n2e[cur[m.edges[2 * e + 1]]++] = (int32_t)(e + 1);
+        }
+    }
+    // Device numbering of the edge unknowns: in groups of 256 nodes, by their rank among the edges
+    // whose lower node is theirs, then by that node. On meshes numbered line by line those of one
+    // rank are edges of one direction at consecutive nodes.
+    {
+        constexpr int32_t kGroup = 256;
+        const size_t n = m.int_edges.size();
+        std::vector<int32_t> rank(m.Ne, 0);
+        for (int64_t e = 1; e < m.Ne; ++e) rank[e] = m.edges[2 * e] == m.edges[2 * e - 2] ? rank[e - 1] + 1 : 0;
+        auto group = [&](size_t i) { return m.edges[2 * (int64_t)m.int_edges[i]] / kGroup; };
+        m.order.resize(n);
+        std::iota(m.order.begin(), m.order.end(), 0);
+        for (size_t i0 = 0, i1; i0 < n; i0 = i1) {
+            for (i1 = i0 + 1; i1 < n && group(i1) == group(i0);) ++i1;
+            std::stable_sort(m.order.begin() + i0, m.order.begin() + i1,
+                             [&](int32_t a, int32_t b) { return rank[m.int_edges[a]] < rank[m.int_edges[b]]; });
+        }
+        m.pos_of.resize(n);
+        m.dev_edges.resize(n);
+        for (size_t p = 0; p < n; ++p) {
+            m.pos_of[m.order[p]] = (int32_t)p;
+            m.dev_edges[p] = m.int_edges[m.order[p]];
         }
     }
     return "";
@@ -412,4 +436,78 @@ void qh_assemble(const HostMesh &m, double eps0, double mu0, HostCsr &A, HostCsr
                   });
     K.ncol = K.nrow;
     (void)local_edge;
+}
+
+// The windows of a slice are laid greedily from its smallest column up (each starts at the smallest
+// column not yet covered); a slice that needs more than four keeps 32-bit columns.
+void qh_build_sell(int32_t n, const int32_t *ptr, const int32_t *col, const int32_t *rows, const int32_t *cpos,
+                   SellHost &o) {
+    constexpr int32_t kSpan = 1 << 14;
+    o = SellHost();
+    o.n = n;
+    o.ns = (n + kSlice - 1) / kSlice;
+    o.off.assign((size_t)o.ns + 1, 0);
+    for (int32_t s = 0; s < o.ns; ++s) {
+        int32_t w = 0;
+        for (int32_t p = s * kSlice; p < std::min(n, (s + 1) * kSlice); ++p) {
+            const int32_t r = rows ? rows[p] : p;
+            w = std::max(w, ptr[r + 1] - ptr[r]);
+        }
+        o.off[s + 1] = o.off[s] + w;
+    }
+    const size_t len = (size_t)o.off[o.ns] * kSlice;
+    o.src.assign(len, -1);
+    o.c32.assign(len, 0);
+    o.c16.assign(len, 0);
+    o.base.assign((size_t)std::max(o.ns, 1), make_int4(-1, 0, 0, 0));
+    std::vector<int32_t> cs;
+    for (int32_t s = 0; s < o.ns; ++s) {
+        const size_t e0 = (size_t)o.off[s] * kSlice;
+        const int32_t w = o.off[s + 1] - o.off[s];
+        if (w == 0) continue;
+        cs.clear();
+        int64_t real = 0;
+        for (int l = 0; l < kSlice; ++l) {
+            const int32_t p = s * kSlice + l;
+            const int32_t r = p < n ? (rows ? rows[p] : p) : -1;
+            const int32_t j0 = r < 0 ? 0 : ptr[r], cnt = r < 0 ? 0 : ptr[r + 1] - ptr[r];
+            for (int32_t k = 0; k < cnt; ++k) {
+                const int32_t c = cpos ? cpos[col[j0 + k]] : col[j0 + k];
+                o.src[e0 + (size_t)k * kSlice + l] = j0 + k;
+                o.c32[e0 + (size_t)k * kSlice + l] = c;
+                cs.push_back(c);
+            }
+            real += cnt;
+        }
+        std::sort(cs.begin(), cs.end());
+        // padding reads the row's own first column (positions past the last row: the slice's)
+        for (int l = 0; l < kSlice; ++l) {
+            const int32_t c0 = o.src[e0 + l] >= 0 ? o.c32[e0 + l] : cs[0];
+            for (int32_t k = 0; k < w; ++k)
+                if (o.src[e0 + (size_t)k * kSlice + l] < 0) o.c32[e0 + (size_t)k * kSlice + l] = c0;
+        }
+        int32_t win[4];
+        int nw = 0;
+        bool fits = true;
+        for (int32_t v : cs) {
+            if (nw > 0 && v < win[nw - 1] + kSpan) continue;
+            if (nw == 4) {
+                fits = false;
+                break;
+            }
+            win[nw++] = v;
+        }
+        if (!fits) {
+            o.wide = true;
+            continue;
+        }
+        for (int i = nw; i < 4; ++i) win[i] = win[nw - 1];
+        o.base[s] = make_int4(win[0], win[1], win[2], win[3]);
+        for (size_t e = e0; e < e0 + (size_t)w * kSlice; ++e) {
+            int i = nw - 1;
+            while (o.c32[e] < win[i]) --i;  // the last window starting at or below the column
+            o.c16[e] = (uint16_t)((uint32_t)i << 14 | (uint32_t)(o.c32[e] - win[i]));
+        }
+        o.nnz_c16 += real;
+    }
 }

@@ -10,13 +10,16 @@
 #include <cmath>
 
 #include "qh_internal.h"
-#include "qh_spmv.h"
+#include "qh_sell.h"
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kLpr = 8;          // lanes per CSR row
-constexpr int kMaxBlocks = 2048; // fixed grid of the reducing kernels (fixed summation order)
+constexpr int kThreads = kSellThreads;
+constexpr int kMaxBlocks = kSellMaxBlocks;  // grids of the reducing kernels (fixed summation order)
+static_assert(kMaxBlocks == 2 * kThreads, "a sum of partials takes two per thread");
+// Entries in flight per lane (a whole row at once, 20, measured no faster at any size).
+constexpr int kU64 = 8;   // FP64 products
+constexpr int kU32 = 10;  // FP32 products
 
 // device scalar slots of a CgWork: S_RZ + parity r.z (double-buffered), S_RR r.r, S_THR2 the
 // target on r.r, S_BB b.b, S_RES the true-residual sums, S_SCALE the mixed-precision solve's
@@ -30,37 +33,37 @@ enum { CG_RUNNING = 0, CG_CONVERGED = 1, CG_STALLED = 2, CG_NONFINITE = 3 };
 constexpr int kStallWindow = 10;
 constexpr double kStallRatio2 = 0.81;  // (1 - 0.1)^2 on r.r
 
-__device__ __forceinline__ double wave_sum_lpr(double v) {
-#pragma unroll
-    for (int off = kLpr / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kLpr);
-    return v;
-}
-
-inline unsigned grid_rows(int64_t nrows) {
-    int64_t b = (nrows * kLpr + kThreads - 1) / kThreads;
-    b = b < kMaxBlocks ? (b < 1 ? 1 : b) : kMaxBlocks;
-    return (unsigned)((b + 7) / 8 * 8);
-}
+// Consecutive vector entries per thread in the element-wise kernels: 16 bytes.
+template <typename T>
+constexpr int kVec = 16 / (int)sizeof(T);
+template <typename T>
 inline unsigned grid_elems(int64_t n) {
-    int64_t b = (n + kThreads - 1) / kThreads;
+    int64_t b = ((n + kVec<T> - 1) / kVec<T> + kThreads - 1) / kThreads;
     return (unsigned)(b < kMaxBlocks ? (b < 1 ? 1 : b) : kMaxBlocks);
 }
 
-// Rows of a CSR kernel: each block takes one contiguous range, and the block index is
-// remapped so that each of the 8 XCDs (which receive blocks round-robin) covers one
-// contiguous span of rows: neighbouring rows share the vector entries they gather, and
-// those then stay in one XCD's L2. Grids are multiples of 8 blocks.
-struct Rows {
-    int64_t begin, end;
-};
-__device__ __forceinline__ Rows block_rows(int64_t n) {
-    const unsigned nb = gridDim.x, per_x = nb / 8;
-    const unsigned lb = (blockIdx.x & 7) * per_x + (blockIdx.x >> 3);
-    const int64_t per = (n + nb - 1) / nb;
-    Rows r;
-    r.begin = (int64_t)lb * per;
-    r.end = r.begin + per < n ? r.begin + per : n;
-    return r;
+// kVec consecutive entries of a vector: one 16-byte access inside the vector, single ones at its
+// end.
+template <typename T>
+using Vec = T __attribute__((ext_vector_type(kVec<T>)));
+template <typename T>
+__device__ __forceinline__ Vec<T> load_vec(const T *__restrict__ p, int64_t i, int64_t n) {
+    if (i + kVec<T> <= n) return *reinterpret_cast<const Vec<T> *>(p + i);
+    Vec<T> v = (T)0;
+#pragma unroll
+    for (int q = 0; q < kVec<T>; ++q)
+        if (i + q < n) v[q] = p[i + q];
+    return v;
+}
+template <typename T>
+__device__ __forceinline__ void store_vec(T *__restrict__ p, int64_t i, int64_t n, Vec<T> v) {
+    if (i + kVec<T> <= n) {
+        *reinterpret_cast<Vec<T> *>(p + i) = v;
+        return;
+    }
+#pragma unroll
+    for (int q = 0; q < kVec<T>; ++q)
+        if (i + q < n) p[i + q] = v[q];
 }
 
 // ---------------------------------------------------------------------------------------
@@ -71,20 +74,41 @@ __device__ __forceinline__ Rows block_rows(int64_t n) {
 // Scalars: scal[S_RZ + parity] holds r.z of the current iterate (double-buffered by the
 // iteration parity so no block reads a slot another block of the same kernel writes).
 
-// Every block: sum of part[0..m) in a fixed order, returned to all threads.
-__device__ __forceinline__ double sum_partials(const double *__restrict__ part, int m, double *sh) {
-    double s = 0.0;
-    for (int j = threadIdx.x; j < m; j += kThreads) s += part[j];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+// This thread's share of part[0..m), m <= kMaxBlocks: two loads, issued where a kernel starts, so
+// that they are in flight beside its first matrix and vector loads.
+__device__ __forceinline__ double load_partials(const double *__restrict__ part, int m) {
+    const int t = (int)threadIdx.x;
+    const double a = t < m ? part[t] : 0.0;
+    const double b = t + kThreads < m ? part[t + kThreads] : 0.0;
+    return a + b;
+}
+
+// Block-wide sums of NV values per thread in a fixed order, returned to every thread.
+template <int NV>
+__device__ __forceinline__ void block_sums(double (&v)[NV], double (*sh)[kThreads / 64]) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    __syncthreads();
-    if (lane == 0) sh[wid] = s;
-    __syncthreads();
-    double t = 0.0;
 #pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) t += sh[w];
-    return t;
+    for (int k = 0; k < NV; ++k) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
+        if (lane == 0) sh[k][wid] = v[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < kThreads / 64; ++w) t += sh[k][w];
+        v[k] = t;
+    }
+}
+
+// Every block: sum of part[0..m) in a fixed order, returned to all threads.
+__device__ __forceinline__ double sum_partials(const double *__restrict__ part, int m, double (*sh)[kThreads / 64]) {
+    double v[1] = {load_partials(part, m)};
+    __syncthreads();  // a caller's earlier sum has been read
+    block_sums<1>(v, sh);
+    return v[0];
 }
 
 // Block-wide sum of NV values, written as this block's partials part[k * kMaxBlocks + block].
@@ -102,28 +126,37 @@ __device__ __forceinline__ void write_partials(double (&v)[NV], double *__restri
     __syncthreads();
     if (threadIdx.x < NV) {
         double t = 0.0;
+#pragma unroll
         for (int w = 0; w < kThreads / 64; ++w) t += sh[threadIdx.x][w];
         part[threadIdx.x * kMaxBlocks + blockIdx.x] = t;
     }
 }
 
+// epi(row, product) for every row of this wave's slices.
+template <int U, typename VT, typename XT, typename Epi>
+__device__ __forceinline__ void sell_rows(int32_t n, int32_t ns, const SellCols &S, const VT *__restrict__ val,
+                                          const XT *__restrict__ x, Epi &&epi) {
+    const SellRange r = sell_range(ns);
+    for (int32_t s = r.begin; s < r.end; s += r.step) {
+        const double a = sell_dot<U>(S, val, x, s);
+        const int32_t row = s * kSlice + (int32_t)(threadIdx.x & 63);
+        if (row < n) epi(row, a);
+    }
+}
+
 // init: r = b - A x, z = D^-1 r, p_old = 0; partials of r.z, r.r, b.b
-__global__ void __launch_bounds__(kThreads) k_cg_init(const int2 *__restrict__ tiles, int32_t ntiles,
-                                                      const int32_t *__restrict__ ptr,
-                                                      const TileCols cols,
+__global__ void __launch_bounds__(kThreads) k_cg_init(int32_t n, int32_t ns, const SellCols S,
                                                       const double *__restrict__ val,
                                                       const double *__restrict__ x,
                                                       const double *__restrict__ b,
                                                       const double *__restrict__ dinv,
                                                       double *__restrict__ r, double *__restrict__ z,
                                                       double *__restrict__ p_old, double *__restrict__ part) {
-    __shared__ double prod[kTileCap];
     double acc[3] = {0.0, 0.0, 0.0};
-    tile_spmv(tiles, ntiles, ptr, cols, val, x, prod, [&](int32_t row) { return make_double2(b[row], dinv[row]); },
-              [&](int32_t row, double s, double2 bd) {
-        const double bb = bd.x;
+    sell_rows<kU64>(n, ns, S, val, x, [&](int32_t row, double s) {
+        const double bb = b[row];
         const double rr = bb - s;
-        const double zz = rr * bd.y;
+        const double zz = rr * dinv[row];
         r[row] = rr;
         z[row] = zz;
         p_old[row] = 0.0;
@@ -152,7 +185,7 @@ __device__ __forceinline__ int cg_state(double rr, double rz, double thr2, int s
 __global__ void __launch_bounds__(kThreads) k_cg_start(const double *__restrict__ part, int m,
                                                        const double *__restrict__ rz_part, int m_rz, double *scal,
                                                        int32_t *flags, double tol2, const double *abs_thr2, int stall) {
-    __shared__ double sh[kThreads / 64];
+    __shared__ double sh[1][kThreads / 64];
     double rz = sum_partials(rz_part, m_rz, sh);
     double rr = sum_partials(part + kMaxBlocks, m, sh);
     double bb = sum_partials(part + 2 * kMaxBlocks, m, sh);
@@ -174,10 +207,11 @@ __global__ void __launch_bounds__(kThreads) k_cg_start(const double *__restrict_
 // partials of p.q. Gathering one vector instead of z and p halves the scattered loads.
 // VT, XT: the matrix values' and the vectors' types (FP64, or FP32 in the inner iterations of
 // the mixed-precision solve; products, sums and dot products are FP64 either way).
+// The sums that the previous kernel left, the stop flag and the row's own entries are loaded beside
+// the first slice's product, which needs none of them: on small systems a launch is this chain of
+// loads and little else.
 template <typename VT, typename XT>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) k_cg_spmv(int32_t n, const int2 *__restrict__ tiles, int32_t ntiles,
-                                                      const int32_t *__restrict__ ptr,
-                                                      const TileCols cols,
+__global__ void __launch_bounds__(kThreads) k_cg_spmv(int32_t n, int32_t ns, const SellCols S,
                                                       const VT *__restrict__ val,
                                                       const XT *__restrict__ z,
                                                       XT *__restrict__ p, XT *__restrict__ q,
@@ -185,42 +219,77 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8
                                                       const double *__restrict__ rr_part, int m_rr,
                                                       double *__restrict__ part, double *scal, int32_t *flags,
                                                       int32_t k, int32_t par, int stall) {
-    if (flags[0]) return;
-    __shared__ double sh[kThreads / 64];
-    __shared__ double prod[kTileCap];
+    constexpr int U = std::is_same<VT, float>::value ? kU32 : kU64;
+    __shared__ double sh[2][kThreads / 64];
+    __shared__ int stopped;
+    const SellRange r = sell_range(ns);
+    const int32_t lane = (int32_t)(threadIdx.x & 63);
+    // one thread's reading decides for the block: block 0 may set the flag meanwhile
+    if (threadIdx.x == 0) stopped = flags[0];
+    double v[2] = {0.0, 0.0};  // r.z, r.r of the present iterate
+    if (k > 0) {
+        v[0] = load_partials(rz_part, m_rz);
+        v[1] = load_partials(rr_part, m_rr);
+    }
+    const double thr2 = scal[S_THR2], rz_old = scal[S_RZ + (k > 0 ? par : 0)];
+    int32_t row = r.begin * kSlice + lane;
+    bool have = r.begin < r.end && row < n;
+    double zi = 0.0, pi = 0.0, qi = 0.0, s = 0.0;
+    if (have) {
+        zi = (double)z[row];
+        if (k > 0) {
+            pi = (double)p[row];
+            qi = (double)q[row];
+        }
+    }
+    if (r.begin < r.end) s = sell_dot<U>(S, val, z, r.begin);
+    block_sums<2>(v, sh);
+    if (stopped) return;
     double beta = 0.0;
     if (k > 0) {
-        double rz_new = sum_partials(rz_part, m_rz, sh);
-        double rr = sum_partials(rr_part, m_rr, sh);
         // the ring slot read (k - 10) differs from the one written (k): no block reads what
         // block 0 writes in this launch
-        const int state = cg_state(rr, rz_new, scal[S_THR2], stall, k, scal + S_HIST);
+        const int state = cg_state(v[1], v[0], thr2, stall, k, scal + S_HIST);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
-            scal[S_RZ + (par ^ 1)] = rz_new;
-            scal[S_RR] = rr;
-            scal[S_HIST + (k & (kHist - 1))] = rr;
+            scal[S_RZ + (par ^ 1)] = v[0];
+            scal[S_RR] = v[1];
+            scal[S_HIST + (k & (kHist - 1))] = v[1];
             flags[1] = k;
             if (state) flags[0] = state;
         }
         if (state) return;  // the same decision in every block (same sums, same order)
-        beta = rz_new / scal[S_RZ + par];
+        beta = v[0] / rz_old;
     } else if (blockIdx.x == 0 && threadIdx.x == 0) {
-        scal[S_RZ + 1] = scal[S_RZ];
+        scal[S_RZ + 1] = rz_old;
     }
     double acc[1] = {0.0};
-    tile_spmv(tiles, ntiles, ptr, cols, val, z, prod, [&](int32_t) { return 0; },
-              [&](int32_t row, double s, int) {
-        const XT pn = (XT)(k > 0 ? (double)z[row] + beta * (double)p[row] : (double)z[row]);
-        const XT qn = (XT)(k > 0 ? s + beta * (double)q[row] : s);
-        p[row] = pn;
-        q[row] = qn;
-        acc[0] += (double)pn * (double)qn;
-    });
+    for (int32_t sl = r.begin; sl < r.end; sl += r.step) {
+        if (sl > r.begin) {
+            row = sl * kSlice + lane;
+            have = row < n;
+            if (have) {
+                zi = (double)z[row];
+                if (k > 0) {
+                    pi = (double)p[row];
+                    qi = (double)q[row];
+                }
+            }
+            s = sell_dot<U>(S, val, z, sl);
+        }
+        if (have) {
+            const XT pn = (XT)(k > 0 ? zi + beta * pi : zi);
+            const XT qn = (XT)(k > 0 ? s + beta * qi : s);
+            p[row] = pn;
+            q[row] = qn;
+            acc[0] += (double)pn * (double)qn;
+        }
+    }
     write_partials<1>(acc, part);
 }
 
 // alpha = r.z / p.q; x += alpha p; r -= alpha q; with Jacobi also z = D^-1 r; partials of
-// r.z (Jacobi) and r.r of the stored values. XT: the vectors' type, as in k_cg_spmv.
+// r.z (Jacobi) and r.r of the stored values. XT: the vectors' type, as in k_cg_spmv. The first
+// entries are loaded beside the sums.
 template <bool JAC, typename XT>
 __global__ void __launch_bounds__(kThreads) k_cg_update(int32_t n, XT *__restrict__ x,
                                                         XT *__restrict__ r, XT *__restrict__ z,
@@ -229,36 +298,62 @@ __global__ void __launch_bounds__(kThreads) k_cg_update(int32_t n, XT *__restric
                                                         const XT *__restrict__ dinv,
                                                         const double *__restrict__ qpart, double *__restrict__ part,
                                                         int m, const double *scal, const int32_t *flags, int32_t par) {
-    if (flags[0]) return;
-    __shared__ double sh[kThreads / 64];
-    const double alpha = scal[S_RZ + (par ^ 1)] / sum_partials(qpart, m, sh);
+    __shared__ double sh[1][kThreads / 64];
+    __shared__ int stopped;
+    if (threadIdx.x == 0) stopped = flags[0];
+    double pq[1] = {load_partials(qpart, m)};
+    const double rz = scal[S_RZ + (par ^ 1)];
+    int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * kVec<XT>;
+    Vec<XT> xv, rv, pv, qv, dv;
+    auto load = [&]() {
+        if (i >= n) return;
+        xv = load_vec(x, i, n);
+        rv = load_vec(r, i, n);
+        pv = load_vec(p, i, n);
+        qv = load_vec(q, i, n);
+        if (JAC) dv = load_vec(dinv, i, n);
+    };
+    load();
+    block_sums<1>(pq, sh);
+    if (stopped) return;
+    const double alpha = rz / pq[0];
     double acc[2] = {0.0, 0.0};
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
-        x[i] = (XT)((double)x[i] + alpha * (double)p[i]);
-        const XT ri = (XT)((double)r[i] - alpha * (double)q[i]);
-        r[i] = ri;
-        if (JAC) {
-            const XT zi = (XT)((double)ri * (double)dinv[i]);
-            z[i] = zi;
-            acc[0] += (double)ri * (double)zi;
+    while (i < n) {
+        Vec<XT> zv;
+#pragma unroll
+        for (int c = 0; c < kVec<XT>; ++c) {
+            xv[c] = (XT)((double)xv[c] + alpha * (double)pv[c]);
+            const XT ri = (XT)((double)rv[c] - alpha * (double)qv[c]);
+            rv[c] = ri;
+            if (i + c >= n) continue;
+            if (JAC) {
+                const XT zi = (XT)((double)ri * (double)dv[c]);
+                zv[c] = zi;
+                acc[0] += (double)ri * (double)zi;
+            }
+            acc[1] += (double)ri * (double)ri;
         }
-        acc[1] += (double)ri * (double)ri;
+        store_vec(x, i, n, xv);
+        store_vec(r, i, n, rv);
+        if (JAC) store_vec(z, i, n, zv);
+        i += (int64_t)gridDim.x * kThreads * kVec<XT>;
+        load();
     }
     write_partials<2>(acc, part);
 }
 
-// Mixed-precision solve. Outer step: r = b - A x in FP64, stored, with partials of r.r and b.b.
-__global__ void __launch_bounds__(kThreads) k_res_store(const int2 *__restrict__ tiles, int32_t ntiles,
-                                                        const int32_t *__restrict__ ptr, const TileCols cols,
-                                                        const double *__restrict__ val, const double *__restrict__ x,
-                                                        const double *__restrict__ b, double *__restrict__ r,
-                                                        double *__restrict__ part) {
-    __shared__ double prod[kTileCap];
+// ||b - A x||^2 and ||b||^2 (partials). STORE: also r = b - A x (the mixed-precision solve's
+// reliable updates).
+template <bool STORE>
+__global__ void __launch_bounds__(kThreads) k_residual(int32_t n, int32_t ns, const SellCols S,
+                                                       const double *__restrict__ val, const double *__restrict__ x,
+                                                       const double *__restrict__ b, double *__restrict__ r,
+                                                       double *__restrict__ part) {
     double acc[2] = {0.0, 0.0};
-    tile_spmv(tiles, ntiles, ptr, cols, val, x, prod, [&](int32_t row) { return b[row]; },
-              [&](int32_t row, double s, double bb) {
+    sell_rows<kU64>(n, ns, S, val, x, [&](int32_t row, double s) {
+        const double bb = b[row];
         const double ri = bb - s;
-        r[row] = ri;
+        if (STORE) r[row] = ri;
         acc[0] += ri * ri;
         acc[1] += bb * bb;
     });
@@ -339,7 +434,7 @@ __global__ void k_convert(int64_t n, const S *__restrict__ in, D *__restrict__ o
 __global__ void __launch_bounds__(kThreads) k_cg_check(const double *__restrict__ upart, int m, double *scal,
                                                        int32_t *flags, int32_t k) {
     if (flags[0]) return;
-    __shared__ double sh[kThreads / 64];
+    __shared__ double sh[1][kThreads / 64];
     double rr = sum_partials(upart + kMaxBlocks, m, sh);
     if (threadIdx.x == 0) {
         scal[S_RR] = rr;
@@ -351,59 +446,78 @@ __global__ void __launch_bounds__(kThreads) k_cg_check(const double *__restrict_
     }
 }
 
-__global__ void k_diag_inv(int32_t n, const int32_t *__restrict__ ptr, const int32_t *__restrict__ col,
-                           const double *__restrict__ val, double *__restrict__ dinv) {
-    int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void k_diag_inv(int32_t n, const SellCols S, const double *__restrict__ val, double *__restrict__ dinv) {
+    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x, s = i / kSlice, l = i % kSlice;
     if (i >= n) return;
+    const int4 b = S.base[s];
     double d = 0.0;
-    for (int32_t j = ptr[i]; j < ptr[i + 1]; ++j)
-        if (col[j] == i) d = val[j];
+    for (int32_t k = S.off[s]; k < S.off[s + 1]; ++k) {
+        const int64_t e = (int64_t)k * kSlice + l;
+        int32_t c;
+        if (b.x >= 0) {
+            const uint32_t h = S.c16[e], q = h >> 14;
+            c = (q == 0 ? b.x : q == 1 ? b.y : q == 2 ? b.z : b.w) + (int32_t)(h & 0x3fffu);
+        } else {
+            c = S.c32[e];
+        }
+        if (c == i && val[e] != 0.0) d = val[e];  // padding holds zeros
+    }
     dinv[i] = d != 0.0 ? 1.0 / d : 0.0;
 }
 
-// A = [*eps] + tau S and the right-hand-side matrix [*eps] - tau S on one pattern
+// A = [*eps] + tau S on the CSR pattern
 __global__ void k_axpy_vals(int64_t n, const double *__restrict__ a, const double *__restrict__ s, double tau,
-                            double *__restrict__ out, double *__restrict__ out_m) {
+                            double *__restrict__ out) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) {
-        out[i] = a[i] + tau * s[i];
-        out_m[i] = a[i] - tau * s[i];
+    if (i < n) out[i] = a[i] + tau * s[i];
+}
+
+// A = [*eps] + tau S and the right-hand-side matrix [*eps] - tau S on the slices (src: CSR entry,
+// -1: padding)
+__global__ void k_axpy_slices(int64_t len, const int32_t *__restrict__ src, const double *__restrict__ a,
+                              const double *__restrict__ s, double tau, double *__restrict__ out,
+                              double *__restrict__ out_m) {
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= len) return;
+    const int32_t e = src[i];
+    const double ae = e >= 0 ? a[e] : 0.0, se = e >= 0 ? s[e] : 0.0;
+    out[i] = ae + tau * se;
+    out_m[i] = ae - tau * se;
+}
+
+__global__ void k_renumber(int64_t n, const int32_t *__restrict__ idx, const double *__restrict__ in,
+                           double *__restrict__ out) {
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) out[i] = in[idx[i]];
+}
+
+// Edge right-hand side in one pass over the edge unknowns (two products per row):
+//   rhs_i = sum_j ([*eps] - tau S)_ij e_j - u_q g[int_edge_i] + dt u_b sum_f (C^T [*mu^-1])_if b_f
+__global__ void __launch_bounds__(kThreads) k_edge_rhs(int32_t n, int32_t ns, const SellCols S,
+                                                       const double *__restrict__ mval,
+                                                       const double *__restrict__ e, const SellCols SC,
+                                                       const double *__restrict__ cval,
+                                                       const int64_t *__restrict__ b, double dtub,
+                                                       const int64_t *__restrict__ g,
+                                                       const int32_t *__restrict__ int_edges, double u_q,
+                                                       double *__restrict__ rhs) {
+    const SellRange r = sell_range(ns);
+    for (int32_t s = r.begin; s < r.end; s += r.step) {
+        const int32_t row = s * kSlice + (int32_t)(threadIdx.x & 63);
+        const double t = sell_dot<kU64>(SC, cval, b, s);
+        const double a = sell_dot<kU64>(S, mval, e, s);
+        if (row < n) rhs[row] = (a - u_q * (double)g[int_edges[row]]) + dtub * t;
     }
-}
-
-// Edge right-hand side in two tiled passes over the interior edges:
-//   rhs_i = sum_j ([*eps] - tau S)_ij e_j - u_q g[int_edge_i]          (k_edge_rhs_e)
-//   rhs_i += dt u_b sum_f (C^T [*mu^-1])_if b_f                          (k_edge_rhs_b)
-__global__ void __launch_bounds__(kThreads) k_edge_rhs_e(const int2 *__restrict__ tiles, int32_t ntiles,
-                                                         const int32_t *__restrict__ ptr,
-                                                         const TileCols cols,
-                                                         const double *__restrict__ mval,
-                                                         const double *__restrict__ e,
-                                                         const int64_t *__restrict__ g,
-                                                         const int32_t *__restrict__ int_edges, double u_q,
-                                                         double *__restrict__ rhs) {
-    __shared__ double prod[kTileCap];
-    tile_spmv(tiles, ntiles, ptr, cols, mval, e, prod, [&](int32_t row) { return g[int_edges[row]]; },
-              [&](int32_t row, double s, int64_t gi) { rhs[row] = s - u_q * (double)gi; });
-}
-
-__global__ void __launch_bounds__(kThreads) k_edge_rhs_b(const int2 *__restrict__ tiles, int32_t ntiles,
-                                                         const int32_t *__restrict__ ptr,
-                                                         const TileCols cols,
-                                                         const double *__restrict__ cval,
-                                                         const int64_t *__restrict__ b, double dtub,
-                                                         double *__restrict__ rhs) {
-    __shared__ double prod[kTileCap];
-    tile_spmv(tiles, ntiles, ptr, cols, cval, b, prod, [&](int32_t row) { return rhs[row]; },
-              [&](int32_t row, double t, double r0) { rhs[row] = r0 + dtub * t; });
 }
 
 // Gauss residual rg = rho - G^T [*eps] e on interior nodes, rho = u_q (Q_bg - Q);
 // threshold thr2 = (tol_n (||rho|| + || |G^T [*eps]| |e| ||))^2: the residual is measured
 // against the size of the terms that cancel in G^T [*eps] e (normwise backward error), so
 // the tolerance stays above the FP64 rounding floor when the charge is small against E.
-__global__ void __launch_bounds__(kThreads) k_gauss_rhs(int32_t n, const int32_t *__restrict__ ptr,
-                                                        const int32_t *__restrict__ col,
+// Rows are few and long (about 50 entries: every edge of the tets around the node), so the eight
+// waves of a block share each slice, a part of its entries each: one wave per slice left most of
+// the chip idle behind seven dependent rounds of loads (25^3: 16.1 us a launch).
+__global__ void __launch_bounds__(kThreads) k_gauss_rhs(int32_t n, int32_t ns, const SellCols S,
                                                         const double *__restrict__ val,
                                                         const double *__restrict__ e,
                                                         const int64_t *__restrict__ Qbg,
@@ -412,29 +526,42 @@ __global__ void __launch_bounds__(kThreads) k_gauss_rhs(int32_t n, const int32_t
                                                         const double *__restrict__ dbnd,
                                                         double *__restrict__ rg, double *__restrict__ rho_out,
                                                         double *__restrict__ part) {
-    const int sub = threadIdx.x % kLpr;
-    const Rows rr_ = block_rows(n);
+    __shared__ double part_s[kSellWaves][kSlice], part_a[kSellWaves][kSlice];
+    const int32_t lane = (int32_t)(threadIdx.x & 63);
+    const int32_t wid = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
+    // one contiguous span of slices per XCD, as sell_range
+    const int32_t per_x = (int32_t)gridDim.x / 8, span = (ns + 7) / 8, xcd = (int32_t)blockIdx.x & 7;
+    const int32_t end = (xcd + 1) * span < ns ? (xcd + 1) * span : ns;
     double acc[3] = {0.0, 0.0, 0.0};
-    for (int64_t row = rr_.begin + threadIdx.x / kLpr; row < rr_.end; row += kThreads / kLpr) {
+    for (int32_t sl = xcd * span + ((int32_t)blockIdx.x >> 3); sl < end; sl += per_x) {
         double s = 0.0, sa = 0.0;
-        for (int32_t j = ptr[row] + sub; j < ptr[row + 1]; j += kLpr) {
-            double t = val[j] * e[col[j]];
+        sell_each<kU64>(S, val, e, sl, [&](double v, double x) {
+            const double t = v * x;
             s += t;
             sa += fabs(t);
-        }
-        s = wave_sum_lpr(s);
-        sa = wave_sum_lpr(sa);
-        if (sub == 0) {
+        }, wid, kSellWaves);
+        part_s[wid][lane] = s;
+        part_a[wid][lane] = sa;
+        __syncthreads();
+        const int32_t row = sl * kSlice + lane;
+        if (wid == 0 && row < n) {
+            s = sa = 0.0;
+#pragma unroll
+            for (int w = 0; w < kSellWaves; ++w) {
+                s += part_s[w][lane];
+                sa += part_a[w][lane];
+            }
             int32_t gn = int_nodes[row];
             // charge, plus the normal flux a plane wave brought in through a natural boundary
             double rho = u_q * (double)(Qbg[gn] - Q[gn]) + (dbnd ? dbnd[gn] : 0.0);
-            double r = rho - s;
-            rg[row] = r;
+            double res = rho - s;
+            rg[row] = res;
             if (rho_out) rho_out[row] = rho;
             acc[0] += rho * rho;
             acc[1] += sa * sa;
-            acc[2] += r * r;
+            acc[2] += res * res;
         }
+        __syncthreads();
     }
     write_partials<3>(acc, part);
 }
@@ -442,7 +569,7 @@ __global__ void __launch_bounds__(kThreads) k_gauss_rhs(int32_t n, const int32_t
 // one block: out[0] = (tol_n scale)^2, out[1] = scale, out[2] = ||r||^2, out[3] = ||rho||
 __global__ void __launch_bounds__(kThreads) k_gauss_finish(const double *__restrict__ part, int m, double *out,
                                                            double tol_n) {
-    __shared__ double sh[kThreads / 64];
+    __shared__ double sh[1][kThreads / 64];
     double a = sum_partials(part, m, sh);
     double b = sum_partials(part + kMaxBlocks, m, sh);
     double c = sum_partials(part + 2 * kMaxBlocks, m, sh);
@@ -486,26 +613,8 @@ __global__ void k_faraday_b(int64_t nf, const int32_t *__restrict__ fe, const in
     b[f] -= u[fe[3 * f + 2]] - u[fe[3 * f + 1]] + u[fe[3 * f]];
 }
 
-// ||b - A x||^2 and ||b||^2 (partials)
-__global__ void __launch_bounds__(kThreads) k_true_res(const int2 *__restrict__ tiles, int32_t ntiles,
-                                                       const int32_t *__restrict__ ptr,
-                                                       const TileCols cols,
-                                                       const double *__restrict__ val,
-                                                       const double *__restrict__ x,
-                                                       const double *__restrict__ b, double *__restrict__ part) {
-    __shared__ double prod[kTileCap];
-    double acc[2] = {0.0, 0.0};
-    tile_spmv(tiles, ntiles, ptr, cols, val, x, prod, [&](int32_t row) { return b[row]; },
-              [&](int32_t row, double s, double bb) {
-        const double r = bb - s;
-        acc[0] += r * r;
-        acc[1] += bb * bb;
-    });
-    write_partials<2>(acc, part);
-}
-
 __global__ void __launch_bounds__(kThreads) k_sum2(const double *__restrict__ part, int m, double *out) {
-    __shared__ double sh[kThreads / 64];
+    __shared__ double sh[1][kThreads / 64];
     double a = sum_partials(part, m, sh);
     double b = sum_partials(part + kMaxBlocks, m, sh);
     if (threadIdx.x == 0) {
@@ -516,11 +625,8 @@ __global__ void __launch_bounds__(kThreads) k_sum2(const double *__restrict__ pa
 
 // Right-hand side of the wave-equation update (eq. wave_cont, Newmark beta = 1/4, gamma = 1/2)
 // on the interior edges:
-//   rhs = 2 ([*eps] - tau S) e^n - ([*eps] + tau S) e^{n-1} - u_q (g^{n+1/2} - g^{n-1/2}),
-// the two products over the pattern of A in one kernel (the same thread owns the same row in
-// both passes, so the second adds to what the first wrote).
-__global__ void __launch_bounds__(kThreads) k_wave_rhs(const int2 *__restrict__ tiles, int32_t ntiles,
-                                                       const int32_t *__restrict__ ptr, const TileCols cols,
+//   rhs = 2 ([*eps] - tau S) e^n - ([*eps] + tau S) e^{n-1} - u_q (g^{n+1/2} - g^{n-1/2}).
+__global__ void __launch_bounds__(kThreads) k_wave_rhs(int32_t n, int32_t ns, const SellCols S,
                                                        const double *__restrict__ arhs,
                                                        const double *__restrict__ aval,
                                                        const double *__restrict__ e,
@@ -529,15 +635,16 @@ __global__ void __launch_bounds__(kThreads) k_wave_rhs(const int2 *__restrict__ 
                                                        const int64_t *__restrict__ g_prev,
                                                        const int32_t *__restrict__ int_edges, double u_q,
                                                        double *__restrict__ rhs) {
-    __shared__ double prod[kTileCap];
-    tile_spmv(tiles, ntiles, ptr, cols, arhs, e, prod,
-              [&](int32_t row) {
-                  const int32_t ge = int_edges[row];
-                  return (double)(g[ge] - g_prev[ge]);
-              },
-              [&](int32_t row, double s, double dg) { rhs[row] = 2.0 * s - u_q * dg; });
-    tile_spmv(tiles, ntiles, ptr, cols, aval, e_prev, prod, [&](int32_t) { return 0; },
-              [&](int32_t row, double s, int) { rhs[row] -= s; });
+    const SellRange r = sell_range(ns);
+    for (int32_t s = r.begin; s < r.end; s += r.step) {
+        const int32_t row = s * kSlice + (int32_t)(threadIdx.x & 63);
+        const double a = sell_dot<kU64>(S, arhs, e, s);
+        const double ap = sell_dot<kU64>(S, aval, e_prev, s);
+        if (row < n) {
+            const int32_t ge = int_edges[row];
+            rhs[row] = (2.0 * a - u_q * (double)(g[ge] - g_prev[ge])) - ap;
+        }
+    }
 }
 
 // Plane wave through the natural boundary. s'(tau) of the modulated Gaussian s(u) =
@@ -614,12 +721,19 @@ int qh_cg_alloc(qh_ctx *c, CgWork &w, int32_t n) {
     return QH_OK;
 }
 
-hipError_t launch_diag_inv(qh_ctx *c, const DevCsr &M, double *dinv) {
-    hipLaunchKernelGGL(k_diag_inv, dim3((M.n + 255) / 256), dim3(256), 0, c->stream, M.n, M.ptr, M.col, M.val, dinv);
+hipError_t launch_diag_inv(qh_ctx *c, const DevSell &M, double *dinv) {
+    if (M.n == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_diag_inv, dim3((M.n + 255) / 256), dim3(256), 0, c->stream, M.n, M.cols(), M.val, dinv);
     return hipGetLastError();
 }
 
-int qh_cg_solve(qh_ctx *c, const DevCsr &M, CgWork &w, double tol, int max_it, int check_every,
+hipError_t launch_renumber(qh_ctx *c, int64_t n, const int32_t *idx, const double *in, double *out) {
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_renumber, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, n, idx, in, out);
+    return hipGetLastError();
+}
+
+int qh_cg_solve(qh_ctx *c, const DevSell &M, CgWork &w, double tol, int max_it, int check_every,
                 SolveResult &out, const double *abs_thr2_dev, bool node_system, bool learned) {
     const int k_spmv = node_system ? QK_NODE_SPMV : QK_CG_SPMV;
     const int k_upd = node_system ? QK_NODE_UPDATE : QK_CG_UPDATE;
@@ -632,7 +746,7 @@ int qh_cg_solve(qh_ctx *c, const DevCsr &M, CgWork &w, double tol, int max_it, i
     // partials: [0, 4K) init / update (slot 0 r.z with Jacobi, 1 r.r, 2 b.b), [4K, 5K) products,
     // [5K, 6K) r.z of the learned preconditioner
     double *upart = w.partial, *qpart = w.partial + 4 * kMaxBlocks, *ppart = w.partial + 5 * kMaxBlocks;
-    const unsigned ge = grid_elems(w.n), gt = tile_grid(M.ntiles);
+    const unsigned ge = grid_elems<double>(w.n), gt = sell_grid(M.ns);
     const unsigned gp = learned ? qh_prec_grid(c) : 0;
     const int stall = learned ? 1 : 0;
     if (check_every <= 0) check_every = 8;
@@ -646,7 +760,7 @@ int qh_cg_solve(qh_ctx *c, const DevCsr &M, CgWork &w, double tol, int max_it, i
     constexpr int kRestarts = 2;
     for (int restart = 0;; ++restart) {
         int t0 = qh_tbeg(c);
-        hipLaunchKernelGGL(k_cg_init, dim3(gt), dim3(kThreads), 0, c->stream, M.tiles, M.ntiles, M.ptr, M.cols(), M.val,
+        hipLaunchKernelGGL(k_cg_init, dim3(gt), dim3(kThreads), 0, c->stream, w.n, M.ns, M.cols(), M.val,
                            w.x, w.b, w.dinv, w.r, w.z, w.p0, upart);
         if (learned) QH_HIP(c, launch_prec_apply(c, w.r, w.z, ppart, nullptr));
         hipLaunchKernelGGL(k_cg_start, dim3(1), dim3(kThreads), 0, c->stream, upart, (int)gt,
@@ -669,7 +783,7 @@ int qh_cg_solve(qh_ctx *c, const DevCsr &M, CgWork &w, double tol, int max_it, i
             for (int k = it - it0; k < it - it0 + batch; ++k) {
                 int par = k & 1;
                 int ta = qh_tbeg(c);
-                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_cg_spmv<double, double>), dim3(gt), dim3(kThreads), 0, c->stream, w.n, M.tiles, M.ntiles, M.ptr,
+                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_cg_spmv<double, double>), dim3(gt), dim3(kThreads), 0, c->stream, w.n, M.ns,
                                    M.cols(), M.val, w.z, w.p0, w.q, learned ? (const double *)ppart : (const double *)upart,
                                    learned ? (int)gp : m_up, upart + kMaxBlocks, m_up, qpart, w.scal, w.flags, k, par,
                                    stall);
@@ -701,8 +815,8 @@ int qh_cg_solve(qh_ctx *c, const DevCsr &M, CgWork &w, double tol, int max_it, i
         out.flag = hflags[0];
         // true residual, recomputed with a fresh FP64 product, against the same target
         int tr = qh_tbeg(c);
-        hipLaunchKernelGGL(k_true_res, dim3(gt), dim3(kThreads), 0, c->stream, M.tiles, M.ntiles, M.ptr, M.cols(), M.val,
-                           w.x, w.b, upart);
+        hipLaunchKernelGGL(k_residual<false>, dim3(gt), dim3(kThreads), 0, c->stream, w.n, M.ns, M.cols(), M.val, w.x,
+                           w.b, (double *)nullptr, upart);
         hipLaunchKernelGGL(k_sum2, dim3(1), dim3(kThreads), 0, c->stream, upart, (int)gt, w.scal + S_RES);
         qh_tend(c, tr, QK_TRUE_RES);
         double sc[S_RES + 2];
@@ -742,7 +856,7 @@ int qh_cg_alloc32(qh_ctx *c, CgWork &w, int32_t n) {
     return QH_OK;
 }
 
-int qh_cg_solve_mixed(qh_ctx *c, DevCsr &M, CgWork &w, double tol, int max_it, int check_every,
+int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, int check_every,
                       SolveResult &out, bool learned) {
     out = SolveResult();
     const int32_t n = w.n;
@@ -756,17 +870,17 @@ int qh_cg_solve_mixed(qh_ctx *c, DevCsr &M, CgWork &w, double tol, int max_it, i
     // FP32 copies: the matrix values once per time step size, the inverse diagonal every solve
     // (a work area may serve several systems)
     if (!M.val32 || M.val32_tau != c->tau_assembled) {
-        if (!M.val32 && (rc = qh_alloc(c, &M.val32, (size_t)M.nnz))) return rc;
-        const unsigned gc = (unsigned)std::min<int64_t>((M.nnz + 255) / 256, 8192);
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_convert<double, float>), dim3(gc), dim3(256), 0, c->stream, M.nnz, M.val,
+        if (!M.val32 && (rc = qh_alloc(c, &M.val32, (size_t)M.len))) return rc;
+        const unsigned gc = (unsigned)std::min<int64_t>((M.len + 255) / 256, 8192);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_convert<double, float>), dim3(gc), dim3(256), 0, c->stream, M.len, M.val,
                            M.val32);
         M.val32_tau = c->tau_assembled;
     }
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_convert<double, float>), dim3(grid_elems(n)), dim3(256), 0, c->stream,
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_convert<double, float>), dim3(grid_elems<float>(n)), dim3(256), 0, c->stream,
                        (int64_t)n, (const double *)w.dinv, w.dinv32);
     QH_HIP(c, hipGetLastError());
     double *upart = w.partial, *qpart = w.partial + 4 * kMaxBlocks, *ppart = w.partial + 5 * kMaxBlocks;
-    const unsigned ge = grid_elems(n), gt = tile_grid(M.ntiles);
+    const unsigned ge = grid_elems<float>(n), gt = sell_grid(M.ns);
     const unsigned gp = learned ? qh_prec_grid(c) : 0;
     const int stall = learned ? 1 : 0;
     if (check_every <= 0) check_every = 8;
@@ -774,8 +888,8 @@ int qh_cg_solve_mixed(qh_ctx *c, DevCsr &M, CgWork &w, double tol, int max_it, i
     double sc[2] = {0.0, 0.0};
     auto fp64_residual = [&]() -> int {
         int tr = qh_tbeg(c);
-        hipLaunchKernelGGL(k_res_store, dim3(gt), dim3(kThreads), 0, c->stream, M.tiles, M.ntiles, M.ptr, M.cols(), M.val,
-                           w.x, w.b, w.r, upart);
+        hipLaunchKernelGGL(k_residual<true>, dim3(gt), dim3(kThreads), 0, c->stream, n, M.ns, M.cols(), M.val, w.x, w.b,
+                           w.r, upart);
         hipLaunchKernelGGL(k_sum2, dim3(1), dim3(kThreads), 0, c->stream, upart, (int)gt, w.scal + S_RES);
         qh_tend(c, tr, QK_TRUE_RES);
         QH_HIP(c, hipGetLastError());
@@ -830,7 +944,7 @@ int qh_cg_solve_mixed(qh_ctx *c, DevCsr &M, CgWork &w, double tol, int max_it, i
                 const int par = kk & 1;
                 int ta = qh_tbeg(c);
                 hipLaunchKernelGGL(HIP_KERNEL_NAME(k_cg_spmv<float, float>), dim3(gt), dim3(kThreads), 0, c->stream, n,
-                                   M.tiles, M.ntiles, M.ptr, M.cols(), (const float *)M.val32, (const float *)w.z32,
+                                   M.ns, M.cols(), (const float *)M.val32, (const float *)w.z32,
                                    w.p32, w.q32, learned ? (const double *)ppart : (const double *)upart,
                                    learned ? (int)gp : (int)ge, upart + kMaxBlocks, (int)ge, qpart, w.scal, w.flags,
                                    kk, par, stall);
@@ -910,77 +1024,28 @@ int qh_cg_solve_mixed(qh_ctx *c, DevCsr &M, CgWork &w, double tol, int max_it, i
     return QH_OK;
 }
 
-bool qh_make_tiles(const int32_t *ptr, int32_t n, std::vector<int2> &tiles) {
-    tiles.clear();
-    int32_t r = 0;
-    tiles.push_back(make_int2(0, ptr[0]));
-    while (r < n) {
-        int32_t e = r;
-        while (e < n && e - r < kTileRows && ptr[e + 1] - ptr[r] <= kTileCap) ++e;
-        if (e == r) return false;
-        tiles.push_back(make_int2(e, ptr[e]));
-        r = e;
-    }
-    return true;
-}
-
-int64_t qh_compact_cols(const int32_t *col, const std::vector<int2> &tiles, std::vector<int4> &tbase,
-                        std::vector<uint16_t> &col16) {
-    constexpr int32_t kSpan = 1 << 14;
-    const size_t nt = tiles.size() - 1;
-    tbase.assign(nt, make_int4(-1, 0, 0, 0));
-    col16.assign((size_t)tiles[nt].y, 0);
-    int64_t n16 = 0;
-    std::vector<int32_t> cs;
-    for (size_t k = 0; k < nt; ++k) {
-        const int32_t e0 = tiles[k].y, e1 = tiles[k + 1].y;
-        if (e1 <= e0) continue;
-        cs.assign(col + e0, col + e1);
-        std::sort(cs.begin(), cs.end());
-        int32_t w[4];
-        int nw = 0;
-        bool fits = true;
-        for (int32_t v : cs) {
-            if (nw > 0 && v < w[nw - 1] + kSpan) continue;
-            if (nw == 4) {
-                fits = false;
-                break;
-            }
-            w[nw++] = v;
-        }
-        if (!fits) continue;
-        for (int i = nw; i < 4; ++i) w[i] = w[nw - 1];
-        tbase[k] = make_int4(w[0], w[1], w[2], w[3]);
-        for (int32_t e = e0; e < e1; ++e) {
-            int i = nw - 1;
-            while (col[e] < w[i]) --i;  // the last window starting at or below the column
-            col16[e] = (uint16_t)((uint32_t)i << 14 | (uint32_t)(col[e] - w[i]));
-        }
-        n16 += e1 - e0;
-    }
-    return n16;
-}
-
 hipError_t launch_assemble_A(qh_ctx *c, double tau) {
-    int64_t nnz = c->A.nnz;
+    int64_t nnz = c->A.nnz, len = c->As.len;
+    if (nnz == 0) return hipSuccess;
     hipLaunchKernelGGL(k_axpy_vals, dim3((unsigned)((nnz + 255) / 256)), dim3(256), 0, c->stream, nnz, c->A.val2,
-                       c->A_S, tau, c->A.val, c->A_rhs);
+                       c->A_S, tau, c->A.val);
+    hipLaunchKernelGGL(k_axpy_slices, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, c->stream, len, c->As.src,
+                       c->A.val2, c->A_S, tau, c->As.val, c->A_rhs);
     return hipGetLastError();
 }
 
 hipError_t launch_edge_rhs(qh_ctx *c) {
-    hipLaunchKernelGGL(k_edge_rhs_e, dim3(tile_grid(c->A.ntiles)), dim3(kThreads), 0, c->stream, c->A.tiles,
-                       c->A.ntiles, c->A.ptr, c->A.cols(), c->A_rhs, c->cge.x, c->g, c->int_edges, c->phys.u_q,
+    const DevSell &A = c->As, &C = c->CMb;
+    hipLaunchKernelGGL(k_edge_rhs, dim3(sell_grid(A.ns)), dim3(kThreads), 0, c->stream, A.n, A.ns, A.cols(), c->A_rhs,
+                       c->cge.x, C.cols(), C.val, c->b, c->phys.dt * c->phys.u_b, c->g, c->int_edges, c->phys.u_q,
                        c->cge.b);
-    hipLaunchKernelGGL(k_edge_rhs_b, dim3(tile_grid(c->CMb.ntiles)), dim3(kThreads), 0, c->stream, c->CMb.tiles,
-                       c->CMb.ntiles, c->CMb.ptr, c->CMb.cols(), c->CMb.val, c->b, c->phys.dt * c->phys.u_b, c->cge.b);
     return hipGetLastError();
 }
 
 hipError_t launch_wave_rhs(qh_ctx *c) {
-    hipLaunchKernelGGL(k_wave_rhs, dim3(tile_grid(c->A.ntiles)), dim3(kThreads), 0, c->stream, c->A.tiles,
-                       c->A.ntiles, c->A.ptr, c->A.cols(), c->A_rhs, c->A.val, c->cge.x, c->e_prev, c->g, c->g_prev,
-                       c->int_edges, c->phys.u_q, c->cge.b);
+    const DevSell &A = c->As;
+    hipLaunchKernelGGL(k_wave_rhs, dim3(sell_grid(A.ns)), dim3(kThreads), 0, c->stream, A.n, A.ns, A.cols(), c->A_rhs,
+                       A.val, c->cge.x, c->e_prev, c->g, c->g_prev, c->int_edges, c->phys.u_q, c->cge.b);
     return hipGetLastError();
 }
 
@@ -996,12 +1061,17 @@ hipError_t launch_plane_wave(qh_ctx *c, bool wave) {
     return hipGetLastError();
 }
 
+static unsigned gauss_grid(int32_t ns) {
+    const int32_t b = (ns + 7) / 8 * 8;
+    return (unsigned)(b < 8 ? 8 : b < kMaxBlocks ? b : kMaxBlocks);
+}
+
 hipError_t launch_gauss_rhs(qh_ctx *c, double *out3, double tol_n) {
-    int32_t n = c->GtM.n;
-    unsigned gr = grid_rows(n);
-    hipLaunchKernelGGL(k_gauss_rhs, dim3(gr), dim3(kThreads), 0, c->stream, n, c->GtM.ptr, c->GtM.col,
-                       c->GtM.val, c->cge.x, c->Q_bg, c->Q, c->int_nodes, c->phys.u_q,
-                       (const double *)c->dbnd, c->cgn.b, c->rho, c->cgn.partial);
+    const DevSell &M = c->GtM;
+    const unsigned gr = gauss_grid(M.ns);
+    hipLaunchKernelGGL(k_gauss_rhs, dim3(gr), dim3(kThreads), 0, c->stream, M.n, M.ns, M.cols(), M.val, c->cge.x,
+                       c->Q_bg, c->Q, c->int_nodes, c->phys.u_q, (const double *)c->dbnd, c->cgn.b, c->rho,
+                       c->cgn.partial);
     hipLaunchKernelGGL(k_gauss_finish, dim3(1), dim3(kThreads), 0, c->stream, c->cgn.partial, (int)gr, out3, tol_n);
     return hipGetLastError();
 }
@@ -1009,10 +1079,10 @@ hipError_t launch_gauss_rhs(qh_ctx *c, double *out3, double tol_n) {
 // Quasi-Helmholtz split: cgn.b = -G^T [*eps] e (the Gauss-law right-hand side with no charge
 // and no boundary flux), with the node solve's threshold in out3 as for the correction.
 hipError_t launch_div_e(qh_ctx *c, double *out3, double tol_n) {
-    int32_t n = c->GtM.n;
-    unsigned gr = grid_rows(n);
-    hipLaunchKernelGGL(k_gauss_rhs, dim3(gr), dim3(kThreads), 0, c->stream, n, c->GtM.ptr, c->GtM.col, c->GtM.val,
-                       c->cge.x, (const int64_t *)c->Q, (const int64_t *)c->Q, c->int_nodes, 0.0, (const double *)nullptr,
+    const DevSell &M = c->GtM;
+    const unsigned gr = gauss_grid(M.ns);
+    hipLaunchKernelGGL(k_gauss_rhs, dim3(gr), dim3(kThreads), 0, c->stream, M.n, M.ns, M.cols(), M.val, c->cge.x,
+                       (const int64_t *)c->Q, (const int64_t *)c->Q, c->int_nodes, 0.0, (const double *)nullptr,
                        c->cgn.b, (double *)nullptr, c->cgn.partial);
     hipLaunchKernelGGL(k_gauss_finish, dim3(1), dim3(kThreads), 0, c->stream, c->cgn.partial, (int)gr, out3, tol_n);
     return hipGetLastError();
@@ -1040,13 +1110,5 @@ hipError_t launch_faraday(qh_ctx *c) {
     int64_t nf = c->hm.Nf;
     hipLaunchKernelGGL(k_faraday_b, dim3((unsigned)((nf + 255) / 256)), dim3(256), 0, c->stream, nf, c->face_edges,
                        c->u_int, c->b);
-    return hipGetLastError();
-}
-
-hipError_t launch_true_residual(qh_ctx *c, const DevCsr &M, const double *x, const double *b, double *out2) {
-    const unsigned gt = tile_grid(M.ntiles);
-    hipLaunchKernelGGL(k_true_res, dim3(gt), dim3(kThreads), 0, c->stream, M.tiles, M.ntiles, M.ptr, M.cols(), M.val, x, b,
-                       c->cge.partial);
-    hipLaunchKernelGGL(k_sum2, dim3(1), dim3(kThreads), 0, c->stream, c->cge.partial, (int)gt, out2);
     return hipGetLastError();
 }
