@@ -63,8 +63,8 @@ int upload_sell_values(qh_ctx *c, DevSell &d, const HostCsr &h, const int32_t *r
     qh_build_sell((int32_t)h.nrow, h.ptr.data(), h.col.data(), rows, cpos, sh);
     int rc = qh_upload_sell(c, d, sh);
     if (rc) return rc;
-    std::vector<double> v(sh.src.size(), 0.0);
-    for (size_t i = 0; i < v.size(); ++i)
+    std::vector<double> v(sh.src.size() + kSellPad, 0.0);
+    for (size_t i = 0; i < sh.src.size(); ++i)
         if (sh.src[i] >= 0) v[i] = h.val[sh.src[i]];
     if ((rc = upload(c, &d.val, v.data(), v.size()))) return rc;
     QH_HIP(c, hipStreamSynchronize(c->stream));
@@ -119,12 +119,12 @@ int ensure_assembled(qh_ctx *c) {
             SellHost sh;
             qh_build_sell(c->A.n, c->hA.ptr.data(), c->hA.col.data(), m.order.data(), m.pos_of.data(), sh);
             c->nnz_edge_c16 = sh.nnz_c16;
-            if ((rc = qh_upload_sell(c, c->As, sh)) || (rc = qh_alloc(c, &c->As.val, (size_t)c->As.len)) ||
-                (rc = qh_alloc(c, &c->A_rhs, (size_t)c->As.len)))
+            if ((rc = qh_upload_sell(c, c->As, sh)) || (rc = qh_alloc(c, &c->As.val, (size_t)c->As.len + kSellPad)) ||
+                (rc = qh_alloc(c, &c->A_rhs, (size_t)c->As.len + kSellPad)))
                 return rc;
             QH_HIP(c, hipStreamSynchronize(c->stream));
         }
-        if ((rc = upload_sell_values(c, c->CMb, c->hCMb, m.order.data(), nullptr)) ||
+        if ((rc = upload_sell_values(c, c->CMb, c->hCMb, nullptr, nullptr)) ||
             (rc = upload_sell_values(c, c->GtM, c->hGtM, nullptr, m.pos_of.data())) ||
             (rc = upload_sell_values(c, c->K, c->hK, nullptr, nullptr)))
             return rc;
@@ -253,12 +253,18 @@ int recompute_charge(qh_ctx *c) {
 int qh_upload_sell(qh_ctx *c, DevSell &d, const SellHost &h) {
     d.n = h.n;
     d.ns = h.ns;
+    d.width = h.width;
     d.len = (int64_t)h.src.size();
+    const size_t len = h.src.size(), room = len + kSellPad;  // rounds of loads run past the last slice
     int rc;
     if ((rc = upload(c, &d.off, h.off.data(), h.off.size())) || (rc = upload(c, &d.base, h.base.data(), h.base.size())) ||
-        (rc = upload(c, &d.src, h.src.data(), h.src.size())) || (rc = upload(c, &d.c16, h.c16.data(), h.c16.size())))
+        (rc = upload(c, &d.src, h.src.data(), len)) || (rc = qh_alloc(c, &d.c16, room)))
         return rc;
-    if (h.wide && (rc = upload(c, &d.c32, h.c32.data(), h.c32.size()))) return rc;
+    QH_HIP(c, hipMemcpyAsync(d.c16, h.c16.data(), sizeof(uint16_t) * len, hipMemcpyHostToDevice, c->stream));
+    if (h.wide) {
+        if ((rc = qh_alloc(c, &d.c32, room))) return rc;
+        QH_HIP(c, hipMemcpyAsync(d.c32, h.c32.data(), sizeof(int32_t) * len, hipMemcpyHostToDevice, c->stream));
+    }
     QH_HIP(c, hipStreamSynchronize(c->stream));  // h may go
     return QH_OK;
 }

@@ -83,10 +83,11 @@ struct SellCols {
     const int4 *base;
     const uint16_t *c16;
     const int32_t *c32;
+    int32_t width;              // every slice's width, or 0: they differ (off)
 };
 
 struct SellHost {
-    int32_t n = 0, ns = 0;
+    int32_t n = 0, ns = 0, width = 0;
     std::vector<int32_t> off;
     std::vector<int32_t> src;   // CSR entry of each stored one, -1: padding
     std::vector<int32_t> c32;
@@ -97,7 +98,7 @@ struct SellHost {
 };
 
 struct DevSell {
-    int32_t n = 0, ns = 0;
+    int32_t n = 0, ns = 0, width = 0;
     int64_t len = 0;            // stored entries, padding included
     int32_t *off = nullptr, *src = nullptr, *c32 = nullptr;
     int4 *base = nullptr;
@@ -105,7 +106,7 @@ struct DevSell {
     double *val = nullptr;
     float *val32 = nullptr;     // FP32 copy of val for the mixed-precision solve (allocated on first use)
     double val32_tau = -1.0;    // the context's tau when val32 was taken (A's values follow dt)
-    SellCols cols() const { return SellCols{off, base, c16, c32}; }
+    SellCols cols() const { return SellCols{off, base, c16, c32, width}; }
 };
 
 struct DevCsr {

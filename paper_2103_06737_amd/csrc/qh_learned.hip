@@ -789,7 +789,7 @@ int qh_learned_setup(qh_ctx *c) {
             if (q >= 0) q = tsrc[q];
         L.nnz_c16 = gh.nnz_c16 + th.nnz_c16;
         if ((rc = qh_upload_sell(c, L.gs, gh)) || (rc = qh_upload_sell(c, L.ts, th)) ||
-            (rc = qh_alloc(c, &L.gpk, (size_t)L.gs.len)) || (rc = qh_alloc(c, &L.tpk, (size_t)L.ts.len)))
+            (rc = qh_alloc(c, &L.gpk, (size_t)L.gs.len + kSellPad)) || (rc = qh_alloc(c, &L.tpk, (size_t)L.ts.len + kSellPad)))
             return rc;
         QH_HIP(c, hipStreamSynchronize(c->stream));
         if (!L.have_weights) {

@@ -455,6 +455,15 @@ void qh_build_sell(int32_t n, const int32_t *ptr, const int32_t *col, const int3
         }
         o.off[s + 1] = o.off[s] + w;
     }
+    if (o.ns <= kSellOneWidth && n > 0) {
+        int32_t w = 1;
+        for (int32_t s = 0; s < o.ns; ++s) w = std::max(w, o.off[s + 1] - o.off[s]);
+        // unless that would pad by more than half
+        if ((int64_t)w * o.ns <= 3 * (int64_t)o.off[o.ns] / 2) {
+            o.width = w;
+            for (int32_t s = 0; s < o.ns; ++s) o.off[s + 1] = o.off[s] + w;
+        }
+    }
     const size_t len = (size_t)o.off[o.ns] * kSlice;
     o.src.assign(len, -1);
     o.c32.assign(len, 0);

@@ -21,6 +21,8 @@
 constexpr int kSlice = 64;                     // rows per slice: one per lane
 constexpr int kSellThreads = 512;
 constexpr int kSellWaves = kSellThreads / 64;  // slices a block works on side by side
+constexpr int kSellPad = 20 * kSlice;          // entries past the last that rounds of loads may touch
+constexpr int kSellOneWidth = 2048;            // matrices of at most this many slices get one width for all
 constexpr int kSellMaxBlocks = 1024;           // 8192 waves: what the 256 CUs hold at eight waves per SIMD
 
 // Slices of a CSR matrix. rows: matrix row of each position (null: the same), cpos: gather index
@@ -61,24 +63,15 @@ inline unsigned sell_grid(int32_t ns) {
     return (unsigned)(b < 8 ? 8 : (b + 7) / 8 * 8);
 }
 
-// Columns of slice s: entries k0 .. k0 + U (past the width: the last entry again).
-template <int U>
-__device__ __forceinline__ void sell_cols(const SellCols &S, int32_t o0, int32_t w, int4 base, int32_t k0, int32_t lane,
-                                          int32_t (&c)[U]) {
-    if (base.x >= 0) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t k = k0 + u < w ? k0 + u : w - 1;
-            const uint32_t h = (S.c16 + (int64_t)(o0 + k) * kSlice)[lane];
-            const uint32_t q = h >> 14;
-            c[u] = (q == 0 ? base.x : q == 1 ? base.y : q == 2 ? base.z : base.w) + (int32_t)(h & 0x3fffu);
-        }
+// Where slice s's entries start (units of 64) and how many each row has. Small matrices have one
+// width for all slices, so that the address of the first entries needs no load.
+__device__ __forceinline__ void sell_extent(const SellCols &S, int32_t s, int32_t &o0, int32_t &w) {
+    if (S.width > 0) {
+        o0 = s * S.width;
+        w = S.width;
     } else {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t k = k0 + u < w ? k0 + u : w - 1;
-            c[u] = (S.c32 + (int64_t)(o0 + k) * kSlice)[lane];
-        }
+        o0 = __builtin_amdgcn_readfirstlane(S.off[s]);
+        w = __builtin_amdgcn_readfirstlane(S.off[s + 1]) - o0;
     }
 }
 
@@ -88,36 +81,62 @@ __device__ __forceinline__ int4 sell_base(const SellCols &S, int32_t s) {
                      __builtin_amdgcn_readfirstlane(v.z), __builtin_amdgcn_readfirstlane(v.w));
 }
 
+// Gather index of a 16-bit column.
+__device__ __forceinline__ int32_t sell_col(uint32_t h, int4 base) {
+    const uint32_t q = h >> 14;
+    return (q == 0 ? base.x : q == 1 ? base.y : q == 2 ? base.z : base.w) + (int32_t)(h & 0x3fffu);
+}
+
+// Rounds of U entries per lane: U entries' loads, then U gathers are in flight together. Loads run
+// past a slice's end without a test (the arrays have kSellPad entries to spare), at constant
+// distances from one address per array; gathers past it take column `safe`, and their terms are
+// left out.
+template <int U>
+__device__ __forceinline__ void sell_cols(const SellCols &S, int32_t o0, int32_t left, int4 base, int32_t lane,
+                                          int32_t safe, int32_t (&c)[U]) {
+    static_assert(U * kSlice <= kSellPad, "a round stays inside the padding");
+    if (base.x >= 0) {
+        const uint16_t *cp = S.c16 + (int64_t)o0 * kSlice + lane;
+#pragma unroll
+        for (int u = 0; u < U; ++u) c[u] = cp[u * kSlice];
+#pragma unroll
+        for (int u = 0; u < U; ++u) c[u] = u < left ? sell_col((uint32_t)c[u], base) : safe;
+    } else {
+        const int32_t *cp = S.c32 + (int64_t)o0 * kSlice + lane;
+#pragma unroll
+        for (int u = 0; u < U; ++u) c[u] = cp[u * kSlice];
+#pragma unroll
+        for (int u = 0; u < U; ++u) c[u] = u < left ? c[u] : safe;
+    }
+}
+
 // op(value, x) for every entry of this lane's row of slice s, in the row's order (padding: zero
-// values). U entries' loads, then U gathers are in flight together.
-// part of parts: the entries k of [w part / parts, w (part + 1) / parts) only.
+// values). part of parts: the entries k of [w part / parts, w (part + 1) / parts) only.
 template <int U, typename VT, typename XT, typename Op>
 __device__ __forceinline__ void sell_each(const SellCols &S, const VT *__restrict__ val, const XT *__restrict__ x,
                                           int32_t s, Op &&op, int32_t part = 0, int32_t parts = 1) {
     const int32_t lane = (int32_t)(threadIdx.x & 63);
-    int32_t o0 = __builtin_amdgcn_readfirstlane(S.off[s]);
-    int32_t w = __builtin_amdgcn_readfirstlane(S.off[s + 1]) - o0;
+    int32_t o0, w;
+    sell_extent(S, s, o0, w);
     if (parts > 1) {
         const int32_t lo = w * part / parts, hi = w * (part + 1) / parts;
         o0 += lo;
         w = hi - lo;
     }
     const int4 base = sell_base(S, s);
-    for (int32_t k0 = 0; k0 < w; k0 += U) {
+    for (; w > 0; w -= U, o0 += U) {
+        const VT *vp = val + (int64_t)o0 * kSlice + lane;
         VT v[U];
         int32_t c[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t k = k0 + u < w ? k0 + u : w - 1;
-            v[u] = (val + (int64_t)(o0 + k) * kSlice)[lane];
-        }
-        sell_cols<U>(S, o0, w, base, k0, lane, c);
+        for (int u = 0; u < U; ++u) v[u] = vp[u * kSlice];
+        sell_cols<U>(S, o0, w, base, lane, 0, c);
         XT xv[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) xv[u] = x[c[u]];
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (k0 + u < w) op(sell_val(v[u]), (double)xv[u]);
+            if (u < w) op(sell_val(v[u]), (double)xv[u]);
     }
 }
 
@@ -136,33 +155,28 @@ template <int U, typename XT>
 __device__ __forceinline__ double sell_dot_pk(const SellCols &S, const uint32_t *__restrict__ pk,
                                               const XT *__restrict__ x, int32_t s) {
     const int32_t lane = (int32_t)(threadIdx.x & 63);
-    const int32_t o0 = __builtin_amdgcn_readfirstlane(S.off[s]);
-    const int32_t w = __builtin_amdgcn_readfirstlane(S.off[s + 1]) - o0;
+    int32_t o0, w;
+    sell_extent(S, s, o0, w);
     const int4 base = sell_base(S, s);
     double acc = 0.0;
-    for (int32_t k0 = 0; k0 < w; k0 += U) {
+    for (; w > 0; w -= U, o0 += U) {
+        const uint32_t *ep = pk + (int64_t)o0 * kSlice + lane;
         uint32_t e[U];
         int32_t c[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t k = k0 + u < w ? k0 + u : w - 1;
-            e[u] = (pk + (int64_t)(o0 + k) * kSlice)[lane];
-        }
+        for (int u = 0; u < U; ++u) e[u] = ep[u * kSlice];
         if (base.x >= 0) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t h = e[u] & 0xffffu, q = h >> 14;
-                c[u] = (q == 0 ? base.x : q == 1 ? base.y : q == 2 ? base.z : base.w) + (int32_t)(h & 0x3fffu);
-            }
+            for (int u = 0; u < U; ++u) c[u] = u < w ? sell_col(e[u] & 0xffffu, base) : 0;
         } else {
-            sell_cols<U>(S, o0, w, base, k0, lane, c);
+            sell_cols<U>(S, o0, w, base, lane, 0, c);
         }
         XT xv[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) xv[u] = x[c[u]];
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (k0 + u < w) acc = fma((double)__uint_as_float(e[u] & 0xffff0000u), (double)xv[u], acc);
+            if (u < w) acc = fma((double)__uint_as_float(e[u] & 0xffff0000u), (double)xv[u], acc);
     }
     return acc;
 }

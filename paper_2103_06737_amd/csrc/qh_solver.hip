@@ -17,9 +17,12 @@ namespace {
 constexpr int kThreads = kSellThreads;
 constexpr int kMaxBlocks = kSellMaxBlocks;  // grids of the reducing kernels (fixed summation order)
 static_assert(kMaxBlocks == 2 * kThreads, "a sum of partials takes two per thread");
-// Entries in flight per lane (a whole row at once, 20, measured no faster at any size).
+// Entries in flight per lane. Small matrices (one width for all slices, one slice per wave): a
+// launch is one chain of loads, so a row's entries (at most 19 on the box meshes) are issued
+// together; larger ones: fewer registers, more waves.
 constexpr int kU64 = 8;   // FP64 products
 constexpr int kU32 = 10;  // FP32 products
+constexpr int kUAll = 20; // small matrices
 
 // device scalar slots of a CgWork: S_RZ + parity r.z (double-buffered), S_RR r.r, S_THR2 the
 // target on r.r, S_BB b.b, S_RES the true-residual sums, S_SCALE the mixed-precision solve's
@@ -153,7 +156,7 @@ __global__ void __launch_bounds__(kThreads) k_cg_init(int32_t n, int32_t ns, con
                                                       double *__restrict__ r, double *__restrict__ z,
                                                       double *__restrict__ p_old, double *__restrict__ part) {
     double acc[3] = {0.0, 0.0, 0.0};
-    sell_rows<kU64>(n, ns, S, val, x, [&](int32_t row, double s) {
+    sell_rows<kUAll>(n, ns, S, val, x, [&](int32_t row, double s) {
         const double bb = b[row];
         const double rr = bb - s;
         const double zz = rr * dinv[row];
@@ -210,7 +213,7 @@ __global__ void __launch_bounds__(kThreads) k_cg_start(const double *__restrict_
 // The sums that the previous kernel left, the stop flag and the row's own entries are loaded beside
 // the first slice's product, which needs none of them: on small systems a launch is this chain of
 // loads and little else.
-template <typename VT, typename XT>
+template <typename VT, typename XT, int U>
 __global__ void __launch_bounds__(kThreads) k_cg_spmv(int32_t n, int32_t ns, const SellCols S,
                                                       const VT *__restrict__ val,
                                                       const XT *__restrict__ z,
@@ -219,7 +222,6 @@ __global__ void __launch_bounds__(kThreads) k_cg_spmv(int32_t n, int32_t ns, con
                                                       const double *__restrict__ rr_part, int m_rr,
                                                       double *__restrict__ part, double *scal, int32_t *flags,
                                                       int32_t k, int32_t par, int stall) {
-    constexpr int U = std::is_same<VT, float>::value ? kU32 : kU64;
     __shared__ double sh[2][kThreads / 64];
     __shared__ int stopped;
     const SellRange r = sell_range(ns);
@@ -350,7 +352,7 @@ __global__ void __launch_bounds__(kThreads) k_residual(int32_t n, int32_t ns, co
                                                        const double *__restrict__ b, double *__restrict__ r,
                                                        double *__restrict__ part) {
     double acc[2] = {0.0, 0.0};
-    sell_rows<kU64>(n, ns, S, val, x, [&](int32_t row, double s) {
+    sell_rows<kUAll>(n, ns, S, val, x, [&](int32_t row, double s) {
         const double bb = b[row];
         const double ri = bb - s;
         if (STORE) r[row] = ri;
@@ -491,22 +493,38 @@ __global__ void k_renumber(int64_t n, const int32_t *__restrict__ idx, const dou
     if (i < n) out[i] = in[idx[i]];
 }
 
-// Edge right-hand side in one pass over the edge unknowns (two products per row):
-//   rhs_i = sum_j ([*eps] - tau S)_ij e_j - u_q g[int_edge_i] + dt u_b sum_f (C^T [*mu^-1])_if b_f
-__global__ void __launch_bounds__(kThreads) k_edge_rhs(int32_t n, int32_t ns, const SellCols S,
-                                                       const double *__restrict__ mval,
-                                                       const double *__restrict__ e, const SellCols SC,
-                                                       const double *__restrict__ cval,
-                                                       const int64_t *__restrict__ b, double dtub,
-                                                       const int64_t *__restrict__ g,
-                                                       const int32_t *__restrict__ int_edges, double u_q,
-                                                       double *__restrict__ rhs) {
+// Edge right-hand side in two passes over the edge unknowns:
+//   rhs_i = sum_j ([*eps] - tau S)_ij e_j - u_q g[int_edge_i]          (k_edge_rhs_e)
+//   rhs_i += dt u_b sum_f (C^T [*mu^-1])_if b_f                          (k_edge_rhs_b)
+// The second takes its rows in interior-edge order (pos: their place in rhs): face fluxes are kept
+// by face number, a dozen per node, and the edges of one node share most of them. Rows in device
+// numbering would gather 96 bytes apart (48^3: 93 us for both passes in one kernel, 86 us so).
+__global__ void __launch_bounds__(kThreads) k_edge_rhs_e(int32_t n, int32_t ns, const SellCols S,
+                                                         const double *__restrict__ mval,
+                                                         const double *__restrict__ e,
+                                                         const int64_t *__restrict__ g,
+                                                         const int32_t *__restrict__ int_edges, double u_q,
+                                                         double *__restrict__ rhs) {
     const SellRange r = sell_range(ns);
     for (int32_t s = r.begin; s < r.end; s += r.step) {
         const int32_t row = s * kSlice + (int32_t)(threadIdx.x & 63);
-        const double t = sell_dot<kU64>(SC, cval, b, s);
-        const double a = sell_dot<kU64>(S, mval, e, s);
-        if (row < n) rhs[row] = (a - u_q * (double)g[int_edges[row]]) + dtub * t;
+        const double a = sell_dot<kUAll>(S, mval, e, s);
+        if (row < n) rhs[row] = a - u_q * (double)g[int_edges[row]];
+    }
+}
+
+__global__ void __launch_bounds__(kThreads) k_edge_rhs_b(int32_t n, int32_t ns, const SellCols S,
+                                                         const double *__restrict__ cval,
+                                                         const int64_t *__restrict__ b, double dtub,
+                                                         const int32_t *__restrict__ pos, double *__restrict__ rhs) {
+    const SellRange r = sell_range(ns);
+    for (int32_t s = r.begin; s < r.end; s += r.step) {
+        const int32_t row = s * kSlice + (int32_t)(threadIdx.x & 63);
+        const double t = sell_dot<kUAll>(S, cval, b, s);
+        if (row < n) {
+            double *d = rhs + pos[row];
+            *d += dtub * t;
+        }
     }
 }
 
@@ -638,8 +656,8 @@ __global__ void __launch_bounds__(kThreads) k_wave_rhs(int32_t n, int32_t ns, co
     const SellRange r = sell_range(ns);
     for (int32_t s = r.begin; s < r.end; s += r.step) {
         const int32_t row = s * kSlice + (int32_t)(threadIdx.x & 63);
-        const double a = sell_dot<kU64>(S, arhs, e, s);
-        const double ap = sell_dot<kU64>(S, aval, e_prev, s);
+        const double a = sell_dot<kUAll>(S, arhs, e, s);
+        const double ap = sell_dot<kUAll>(S, aval, e_prev, s);
         if (row < n) {
             const int32_t ge = int_edges[row];
             rhs[row] = (2.0 * a - u_q * (double)(g[ge] - g_prev[ge])) - ap;
@@ -783,7 +801,7 @@ int qh_cg_solve(qh_ctx *c, const DevSell &M, CgWork &w, double tol, int max_it, 
             for (int k = it - it0; k < it - it0 + batch; ++k) {
                 int par = k & 1;
                 int ta = qh_tbeg(c);
-                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_cg_spmv<double, double>), dim3(gt), dim3(kThreads), 0, c->stream, w.n, M.ns,
+                hipLaunchKernelGGL((M.width > 0 ? k_cg_spmv<double, double, kUAll> : k_cg_spmv<double, double, kU64>), dim3(gt), dim3(kThreads), 0, c->stream, w.n, M.ns,
                                    M.cols(), M.val, w.z, w.p0, w.q, learned ? (const double *)ppart : (const double *)upart,
                                    learned ? (int)gp : m_up, upart + kMaxBlocks, m_up, qpart, w.scal, w.flags, k, par,
                                    stall);
@@ -870,7 +888,7 @@ int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, 
     // FP32 copies: the matrix values once per time step size, the inverse diagonal every solve
     // (a work area may serve several systems)
     if (!M.val32 || M.val32_tau != c->tau_assembled) {
-        if (!M.val32 && (rc = qh_alloc(c, &M.val32, (size_t)M.len))) return rc;
+        if (!M.val32 && (rc = qh_alloc(c, &M.val32, (size_t)M.len + kSellPad))) return rc;
         const unsigned gc = (unsigned)std::min<int64_t>((M.len + 255) / 256, 8192);
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_convert<double, float>), dim3(gc), dim3(256), 0, c->stream, M.len, M.val,
                            M.val32);
@@ -943,7 +961,7 @@ int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, 
             for (int kk = k; kk < k + batch; ++kk) {
                 const int par = kk & 1;
                 int ta = qh_tbeg(c);
-                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_cg_spmv<float, float>), dim3(gt), dim3(kThreads), 0, c->stream, n,
+                hipLaunchKernelGGL((M.width > 0 ? k_cg_spmv<float, float, kUAll> : k_cg_spmv<float, float, kU32>), dim3(gt), dim3(kThreads), 0, c->stream, n,
                                    M.ns, M.cols(), (const float *)M.val32, (const float *)w.z32,
                                    w.p32, w.q32, learned ? (const double *)ppart : (const double *)upart,
                                    learned ? (int)gp : (int)ge, upart + kMaxBlocks, (int)ge, qpart, w.scal, w.flags,
@@ -1036,9 +1054,10 @@ hipError_t launch_assemble_A(qh_ctx *c, double tau) {
 
 hipError_t launch_edge_rhs(qh_ctx *c) {
     const DevSell &A = c->As, &C = c->CMb;
-    hipLaunchKernelGGL(k_edge_rhs, dim3(sell_grid(A.ns)), dim3(kThreads), 0, c->stream, A.n, A.ns, A.cols(), c->A_rhs,
-                       c->cge.x, C.cols(), C.val, c->b, c->phys.dt * c->phys.u_b, c->g, c->int_edges, c->phys.u_q,
-                       c->cge.b);
+    hipLaunchKernelGGL(k_edge_rhs_e, dim3(sell_grid(A.ns)), dim3(kThreads), 0,
+                       c->stream, A.n, A.ns, A.cols(), c->A_rhs, c->cge.x, c->g, c->int_edges, c->phys.u_q, c->cge.b);
+    hipLaunchKernelGGL(k_edge_rhs_b, dim3(sell_grid(C.ns)), dim3(kThreads), 0,
+                       c->stream, C.n, C.ns, C.cols(), C.val, c->b, c->phys.dt * c->phys.u_b, c->pos_of, c->cge.b);
     return hipGetLastError();
 }
 
