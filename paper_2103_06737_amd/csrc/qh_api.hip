@@ -293,7 +293,14 @@ int qh_create(qh_ctx **out, int device, void *stream) {
         return QH_ENOMEM;
     }
     c->counters = cnt;
+    if (hipHostMalloc((void **)&c->host, sizeof(HostResults), hipHostMallocDefault) != hipSuccess) {
+        free_all(c);
+        delete c;
+        return QH_ENOMEM;
+    }
+    std::memset(c->host, 0, sizeof(HostResults));
     if (qh_alloc(c, &c->scratch_d, 16) != QH_OK) {
+        (void)hipHostFree(c->host);
         free_all(c);
         delete c;
         return QH_ENOMEM;
@@ -314,6 +321,9 @@ void qh_destroy(qh_ctx *c) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
     for (auto e : c->ev_pool) (void)hipEventDestroy(e);
+    for (auto e : c->step_ev)
+        if (e) (void)hipEventDestroy(e);
+    (void)hipHostFree(c->host);
     free_all(c);
     delete c;
 }
@@ -499,6 +509,7 @@ int qh_mesh_upload(qh_ctx *c, int64_t n_nodes, const double *xyz, int64_t n_tets
     {
         const int64_t nmail = (m.Nt + kMailTets - 1) / kMailTets;
         if ((rc = qh_alloc(c, &c->mail_cnt, nmail)) || (rc = qh_alloc(c, &c->mail, nmail * kMailCap * kMailWords))) return rc;
+        QH_HIP(c, hipMemsetAsync(c->mail_cnt, 0, sizeof(unsigned int) * nmail, c->stream));
     }
     if ((rc = qh_alloc(c, &c->frec, 3 * m.Nt))) return rc;
     if ((rc = qh_alloc(c, &c->e, m.Ne)) || (rc = qh_alloc(c, &c->b, m.Nf)) || (rc = qh_alloc(c, &c->g, m.Ne)) ||
@@ -1071,16 +1082,12 @@ int qh_pic_step(qh_ctx *c, const qh_step_params_t *P, int32_t n_steps, qh_step_s
     }
     const HostMesh &m = c->hm;
     int status = QH_OK;
-    hipEvent_t ev[4];
-    bool use_ev = stats != nullptr;
+    const bool use_ev = stats != nullptr;
+    hipEvent_t *ev = c->step_ev;
     if (use_ev)
-        for (auto &x : ev) QH_HIP(c, hipEventCreateWithFlags(&x, hipEventDisableSystemFence));
-    // totals of the whole call (fixed-point headroom overflows of the gathers, lost particles,
-    // verification failures), kept whether or not stats are asked for; the per-step slots before
-    // them are cleared every step
-    unsigned long long *totals = c->counters + 4 * QH_COUNTER_SLOTS + QH_CNT_HEADROOM_CALL;
-    constexpr int kTotals = QH_CNT_DIVB_CALL - QH_CNT_HEADROOM_CALL + 1;
-    QH_HIP(c, hipMemsetAsync(totals, 0, sizeof(unsigned long long) * kTotals, c->stream));
+        for (int k = 0; k < 3; ++k)
+            if (!ev[k]) QH_HIP(c, hipEventCreateWithFlags(&ev[k], hipEventDisableSystemFence));
+    volatile const HostResults *H = c->host;
     for (int32_t st = 0; st < n_steps; ++st) {
         bool capture = c->capture_next;
         c->capture_next = false;
@@ -1092,10 +1099,9 @@ int qh_pic_step(qh_ctx *c, const qh_step_params_t *P, int32_t n_steps, qh_step_s
             c->fields_dirty = false;
         }
         std::swap(c->Q, c->Q_old);
-        QH_HIP(c, hipMemsetAsync(c->Q, 0, sizeof(int64_t) * m.Nn, c->stream));
-        QH_HIP(c, hipMemsetAsync(c->g, 0, sizeof(int64_t) * m.Ne, c->stream));
-        QH_HIP(c, hipMemsetAsync(c->counters, 0, sizeof(unsigned long long) * (4 * QH_COUNTER_SLOTS + QH_CNT_STEP_END),
-                                 c->stream));
+        // the counters' totals (fixed-point headroom overflows of the gathers, lost particles,
+        // verification failures) are those of the whole call, whether or not stats are asked for
+        QH_HIP(c, launch_step_begin(c, st == 0, solve));
         for (size_t k = 0; k < c->species.size(); ++k) {
             int t0 = qh_tbeg(c);
             QH_HIP(c, launch_particle_step(c, c->species[k], (int)k, capture));
@@ -1111,9 +1117,7 @@ int qh_pic_step(qh_ctx *c, const qh_step_params_t *P, int32_t n_steps, qh_step_s
             }
         if (use_ev) QH_HIP(c, hipEventRecord(ev[1], c->stream));
         SolveResult se, sn;
-        double gauss_out[4] = {0, 0, 0, 0};
         if (solve) {
-            QH_HIP(c, hipMemcpyAsync(c->e_old, c->cge.x, sizeof(double) * c->A.n, hipMemcpyDeviceToDevice, c->stream));
             // the wave-equation right-hand side needs e^{n-1} and the previous current: without
             // them (first step in this mode) the step takes the trapezoidal update
             const bool wave = P->field_mode == QH_FIELDS_WAVE && c->wave_hist;
@@ -1147,21 +1151,32 @@ int qh_pic_step(qh_ctx *c, const qh_step_params_t *P, int32_t n_steps, qh_step_s
             }
             c->last_fallbacks = fallbacks;
             if (!se.converged) status = QH_ENOTCONV;
-            QH_HIP(c, hipMemcpyAsync(c->e_star, c->cge.x, sizeof(double) * c->A.n, hipMemcpyDeviceToDevice, c->stream));
             // the (rhs, solution) pair of this step into the bank, while recording
-            if (c->lp.pair_rec && (rc = qh_learned_record_pair(c, c->cge.b, c->e_star, c->pos_of))) return rc;
+            if (c->lp.pair_rec && (rc = qh_learned_record_pair(c, c->cge.b, c->cge.x, c->pos_of))) return rc;
+            bool correct = false;
             if (P->gauss) {
                 t0 = qh_tbeg(c);
                 QH_HIP(c, launch_gauss_rhs(c, c->scratch_d, P->tol_node));
-                QH_HIP(c, hipMemsetAsync(c->cgn.x, 0, sizeof(double) * c->K.n, c->stream));
                 qh_tend(c, t0, QK_GAUSS);
-                rc = qh_cg_solve(c, c->K, c->cgn, P->tol_node, P->max_it_node, P->check_every, sn, c->scratch_d, true);
-                if (rc) return rc;
-                if (!sn.converged) status = QH_ENOTCONV;
-                t0 = qh_tbeg(c);
-                QH_HIP(c, launch_gauss_apply(c));
-                qh_tend(c, t0, QK_GAUSS);
+                // where the last node solve needed no iteration, the residual is looked at first:
+                // at its target the solve would return its start, zero
+                correct = true;
+                if (c->cgn.last_iters[0] == 0) {
+                    QH_HIP(c, hipStreamSynchronize(c->stream));
+                    const double thr2 = H->gauss[0], rr = H->gauss[2];
+                    correct = !(rr <= thr2);
+                    sn.converged = sn.true_ok = !correct;
+                    sn.res = rr > 0 ? 1.0 : 0.0;
+                }
+                if (correct) {
+                    rc = qh_cg_solve(c, c->K, c->cgn, P->tol_node, P->max_it_node, P->check_every, sn, c->scratch_d, true);
+                    if (rc) return rc;
+                    if (!sn.converged) status = QH_ENOTCONV;
+                }
             }
+            t0 = qh_tbeg(c);
+            QH_HIP(c, launch_gauss_apply(c, correct));
+            qh_tend(c, t0, QK_GAUSS);
             int t1 = qh_tbeg(c);
             QH_HIP(c, launch_faraday(c));
             qh_tend(c, t1, QK_FARADAY);
@@ -1174,24 +1189,17 @@ int qh_pic_step(qh_ctx *c, const qh_step_params_t *P, int32_t n_steps, qh_step_s
             if (stats) {
                 // Gauss residual after the update (reuses the node right-hand-side buffer)
                 QH_HIP(c, launch_gauss_rhs(c, c->scratch_d + 4, P->tol_node));
-                QH_HIP(c, hipMemcpyAsync(gauss_out, c->scratch_d + 4, sizeof(gauss_out), hipMemcpyDeviceToHost, c->stream));
             }
         }
         if (!solve) c->wave_hist = false;  // the fields did not follow this step's current
         if (P->verify) QH_HIP(c, launch_verify(c, true));
+        if (stats || st == n_steps - 1) QH_HIP(c, launch_step_counts(c));
         if (use_ev) QH_HIP(c, hipEventRecord(ev[2], c->stream));
         if (stats) {
-            std::vector<unsigned long long> raw(4 * QH_COUNTER_SLOTS + 8);
-            QH_HIP(c, hipMemcpyAsync(raw.data(), c->counters, sizeof(unsigned long long) * raw.size(),
-                                     hipMemcpyDeviceToHost, c->stream));
             QH_HIP(c, hipStreamSynchronize(c->stream));
-            unsigned long long cnt[6] = {0, 0, 0, 0, 0, 0};
-            for (int k = 0; k < QH_COUNTER_SLOTS; ++k) {
-                for (int j = 0; j < 3; ++j) cnt[j] += raw[4 * k + j];
-                cnt[5] += raw[4 * k + 3];
-            }
-            cnt[3] = raw[4 * QH_COUNTER_SLOTS + QH_CNT_CONT];
-            cnt[4] = raw[4 * QH_COUNTER_SLOTS + QH_CNT_DIVB];
+            double gauss_out[4] = {0, 0, 0, 0};
+            if (solve)
+                for (int k = 0; k < 4; ++k) gauss_out[k] = H->gauss[k];
             qh_step_stats_t &S = stats[st];
             std::memset(&S, 0, sizeof(S));
             S.edge_iters = se.iters;
@@ -1200,12 +1208,12 @@ int qh_pic_step(qh_ctx *c, const qh_step_params_t *P, int32_t n_steps, qh_step_s
             S.node_res = sn.res;
             S.gauss_res = gauss_out[1] > 0 ? std::sqrt(gauss_out[2]) / gauss_out[1] : 0.0;
             S.gauss_res_rho = gauss_out[3] > 0 ? std::sqrt(gauss_out[2]) / gauss_out[3] : 0.0;
-            S.crossings = (int64_t)cnt[0];
-            S.wall_hits = (int64_t)cnt[1];
-            S.lost = (int64_t)cnt[2];
-            S.continuity_bad = P->verify ? (int64_t)cnt[3] : -1;
-            S.divb_bad = P->verify ? (int64_t)cnt[4] : -1;
-            S.foreign = (int64_t)cnt[5];
+            S.crossings = (int64_t)H->step[0];
+            S.wall_hits = (int64_t)H->step[1];
+            S.lost = (int64_t)H->step[2];
+            S.continuity_bad = P->verify ? (int64_t)H->step[4] : -1;
+            S.divb_bad = P->verify ? (int64_t)H->step[5] : -1;
+            S.foreign = (int64_t)H->step[3];
             S.fallbacks = solve ? c->last_fallbacks : 0;
             S.edge_refinements = solve ? c->last_refinements : 0;
             (void)hipEventElapsedTime(&S.ms_particles, ev[0], ev[1]);
@@ -1214,11 +1222,11 @@ int qh_pic_step(qh_ctx *c, const qh_step_params_t *P, int32_t n_steps, qh_step_s
         qh_tflush(c);
         c->step_index++;
     }
-    if (use_ev)
-        for (auto &x : ev) (void)hipEventDestroy(x);
-    unsigned long long tot[kTotals] = {};
-    QH_HIP(c, hipMemcpyAsync(tot, totals, sizeof(tot), hipMemcpyDeviceToHost, c->stream));
-    QH_HIP(c, hipStreamSynchronize(c->stream));
+    unsigned long long tot[4] = {0, 0, 0, 0};
+    if (n_steps > 0) {
+        if (!stats) QH_HIP(c, hipStreamSynchronize(c->stream));
+        for (int k = 0; k < 4; ++k) tot[k] = H->call[k];
+    }
     const unsigned long long nhead = tot[0], nlost = tot[QH_CNT_LOST_CALL - QH_CNT_HEADROOM_CALL],
                              ncont = tot[QH_CNT_CONT_CALL - QH_CNT_HEADROOM_CALL],
                              ndivb = tot[QH_CNT_DIVB_CALL - QH_CNT_HEADROOM_CALL];
@@ -1275,7 +1283,6 @@ int qh_fields_decompose(qh_ctx *c, double tol, int32_t max_it, double *e_ns, dou
     if (nn > 0) {
         // K delta = -G^T [*eps] e, so delta = -E_ns and E_s = e + G delta
         QH_HIP(c, launch_div_e(c, c->scratch_d, tol));
-        QH_HIP(c, hipMemsetAsync(c->cgn.x, 0, sizeof(double) * nn, c->stream));
         if ((rc = qh_cg_solve(c, c->K, c->cgn, tol, max_it, 8, sn, c->scratch_d, true))) return rc;
     }
     QH_HIP(c, hipMemcpyAsync(c->dec_e, c->cge.x, sizeof(double) * ne, hipMemcpyDeviceToDevice, c->stream));

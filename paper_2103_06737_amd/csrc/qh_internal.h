@@ -183,6 +183,20 @@ struct LearnedPrec {
     double *ppart = nullptr, *pw = nullptr;
 };
 
+// What the host waits for, in pinned host memory: kernels write it there directly, so a read is
+// a stream synchronisation without a copy (one short kernel and its synchronisation take 13 us, with
+// a copy to pageable memory 23 us).
+struct HostResults {
+    int32_t flags[2];           // why the iteration stopped (0: it has not), iterations
+    double rr;                  // r.r of the iterate last checked
+    double thr2, rr0, bb;       // target on r.r, r.r and b.b at the start
+    double res[2];              // ||b - A x||^2 and ||b||^2, recomputed
+    double gauss[4];            // k_gauss_finish
+    unsigned long long step[6]; // crossings, wall hits, lost, posted pieces, continuity, D b violations
+    int32_t live;               // particles left after a sort that drops absorbed ones
+    unsigned long long call[4]; // totals of the step call: headroom, lost, continuity, D b
+};
+
 struct qh_ctx {
     int device = 0;
     int32_t bc = QH_BC_PEC;  // field boundary condition (qh_set_boundary, before the mesh)
@@ -267,6 +281,8 @@ struct qh_ctx {
     int32_t *loc_seed = nullptr;
     float loc_lo[3] = {0, 0, 0}, loc_inv[3] = {0, 0, 0};
     int32_t loc_n[3] = {0, 0, 0};
+    HostResults *host = nullptr;  // pinned
+    hipEvent_t step_ev[3] = {nullptr, nullptr, nullptr};  // phase times of a step with statistics
     unsigned long long *counters = nullptr;  // 4*QH_COUNTER_SLOTS + QH_CNT_ALL (see QH_CNT_*)
     int32_t *hist = nullptr, *cursor = nullptr, *scan_tmp = nullptr;
     int32_t *perm = nullptr;   // the sort's source index per destination slot (perm_cap entries)
@@ -352,6 +368,11 @@ hipError_t launch_deposit_lists(qh_ctx *c, int64_t n_seg, const int32_t *seg_tet
                                 int64_t n_pt, const int32_t *pt_tet, const int32_t *pl,
                                 const int32_t *pz, int64_t *g, int64_t *Q);
 hipError_t launch_verify(qh_ctx *c, bool check_divb);
+// Start of a step: deposits and step counters (and, at the start of a call, the call's totals)
+// cleared, e_old = the edge unknowns if they will change
+hipError_t launch_step_begin(qh_ctx *c, bool call_begins, bool solve);
+// Counters into c->host->step and c->host->call
+hipError_t launch_step_counts(qh_ctx *c);
 hipError_t launch_divb(qh_ctx *c, int64_t *out);
 // Field energy (qh_diag.hip): qh_energy_parts(c) partial sums in part, out[0] electric, out[1] magnetic
 int32_t qh_energy_parts(const qh_ctx *c);
@@ -415,9 +436,10 @@ hipError_t launch_assemble_A(qh_ctx *c, double tau);
 hipError_t launch_edge_rhs(qh_ctx *c);
 hipError_t launch_wave_rhs(qh_ctx *c);
 hipError_t launch_plane_wave(qh_ctx *c, bool wave);
-hipError_t launch_gauss_rhs(qh_ctx *c, double *thr2_dev, double tol_n);
-hipError_t launch_gauss_apply(qh_ctx *c);
+// r = rho - G^T [*eps] e (node right-hand side), its threshold and norms into out4 and c->host->gauss
+hipError_t launch_gauss_rhs(qh_ctx *c, double *out4, double tol_n);
+// e_star = e; e += G delta unless delta is 0
+hipError_t launch_gauss_apply(qh_ctx *c, bool delta);
 hipError_t launch_div_e(qh_ctx *c, double *out3, double tol_n);
 hipError_t launch_grad_add(qh_ctx *c, const double *delta, double *e_int);
 hipError_t launch_faraday(qh_ctx *c);
-hipError_t launch_gauss_check(qh_ctx *c, double *out3);

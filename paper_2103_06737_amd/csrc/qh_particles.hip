@@ -14,6 +14,7 @@
 // faces by vertex id) the piece adds z (L_a^0 L_b^1 - L_a^1 L_b^0) to edge a->b and the end
 // point adds z 2^20 L_n to node n. G^T g then telescopes to Q^{n+1} - Q^n in int64: discrete
 // continuity holds bit for bit and the sums are independent of order.
+#include <algorithm>
 #include <type_traits>
 
 #include "qh_internal.h"
@@ -620,8 +621,9 @@ __global__ void __launch_bounds__(256) k_gather(int64_t nitems, const int32_t *_
 
 // Mailbox m (tets [kMailTets m, kMailTets (m+1))) into acc_tet: each record's 10 values (as
 // in the particle kernel) summed in LDS by tet, then added to the (already written) per-tet
-// sums. One block per mailbox, so every tet has a single writer.
-__global__ void __launch_bounds__(256) k_mail_apply(const unsigned int *__restrict__ mail_cnt,
+// sums. One block per mailbox, so every tet has a single writer. The mailbox is left empty for the
+// next launch.
+__global__ void __launch_bounds__(256) k_mail_apply(unsigned int *__restrict__ mail_cnt,
                                                     const int32_t *__restrict__ mail, int32_t zq, int64_t nt,
                                                     int64_t *__restrict__ acc_tet) {
     const int o = blockIdx.x;
@@ -632,6 +634,7 @@ __global__ void __launch_bounds__(256) k_mail_apply(const unsigned int *__restri
     const int W = (int)min((int64_t)kMailTets, nt - T0);
     for (int j = threadIdx.x; j < 10 * kMailTets; j += 256) acc[j] = 0;
     __syncthreads();
+    if (threadIdx.x == 0) mail_cnt[o] = 0;  // every thread has read it
     const int LE0[6] = {0, 0, 0, 1, 1, 2};
     const int LE1[6] = {1, 2, 3, 2, 3, 3};
     const int32_t *box = mail + (int64_t)o * kMailCap * kMailWords;
@@ -697,8 +700,7 @@ hipError_t launch_particle_step(qh_ctx *c, Species &s, int sidx, bool capture) {
     a.species = sidx; a.cap = c->cap_segments; a.seg_count = c->seg_count; a.seg_buf = c->seg_buf;
     dim3 grid((unsigned)((s.n + kChunk - 1) / kChunk));
     const unsigned nmail = (unsigned)((c->hm.Nt + kMailTets - 1) / kMailTets);
-    hipError_t e = hipMemsetAsync(c->mail_cnt, 0, sizeof(unsigned int) * nmail, c->stream);
-    if (e != hipSuccess) return e;
+    hipError_t e;
     // few particles on a large mesh (the blocks' windows cannot cover it): one fill clears the
     // per-tet sums instead of each block zeroing a long owned range
     a.zeroed = (int64_t)grid.x * kWin < c->hm.Nt ? 1 : 0;
@@ -716,6 +718,55 @@ hipError_t launch_particle_step(qh_ctx *c, Species &s, int sidx, bool capture) {
                        m.Nt, c->g, ge, headroom);
     hipLaunchKernelGGL((k_gather<6, kLpiN>), dim3(gn), dim3(256), 0, c->stream, m.Nn, c->n2t_ptr, c->n2t, c->acc_tet,
                        m.Nt, c->Q, gn, headroom);
+    return hipGetLastError();
+}
+
+// Deposits and step counters cleared, e_old = x, in one launch.
+__global__ void __launch_bounds__(256) k_step_begin(int64_t ne, int64_t *__restrict__ g, int64_t nn,
+                                                    int64_t *__restrict__ Q, int nc, unsigned long long *counters,
+                                                    int64_t nx, const double *__restrict__ x,
+                                                    double *__restrict__ e_old) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < ne) g[i] = 0;
+    if (i < nn) Q[i] = 0;
+    if (i < nc) counters[i] = 0;
+    if (i < nx) e_old[i] = x[i];
+}
+
+hipError_t launch_step_begin(qh_ctx *c, bool call_begins, bool solve) {
+    const HostMesh &m = c->hm;
+    // the call's totals follow the step's counters
+    const int nc = 4 * QH_COUNTER_SLOTS + (call_begins ? QH_CNT_DIVB_CALL + 1 : (int)QH_CNT_STEP_END);
+    const int64_t most = std::max<int64_t>(std::max(m.Ne, m.Nn), nc);
+    hipLaunchKernelGGL(k_step_begin, dim3((unsigned)((most + 255) / 256)), dim3(256), 0, c->stream, m.Ne, c->g, m.Nn,
+                       c->Q, nc, c->counters, solve ? (int64_t)c->A.n : (int64_t)0, c->cge.x, c->e_old);
+    return hipGetLastError();
+}
+
+// One block: the step's counters and the call's totals to the host.
+__global__ void __launch_bounds__(256) k_step_counts(const unsigned long long *__restrict__ counters,
+                                                     HostResults *host) {
+    static_assert(QH_COUNTER_SLOTS == 256, "one slot per thread");
+    __shared__ unsigned long long sh[4][4];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        unsigned long long v = counters[4 * threadIdx.x + j];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v += (unsigned long long)__shfl_xor((long long)v, off, 64);
+        if (lane == 0) sh[j][wid] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        const int j = threadIdx.x;
+        host->step[j] = sh[j][0] + sh[j][1] + sh[j][2] + sh[j][3];
+        host->call[j] = counters[4 * QH_COUNTER_SLOTS + QH_CNT_HEADROOM_CALL + j];
+        if (j < 2) host->step[4 + j] = counters[4 * QH_COUNTER_SLOTS + QH_CNT_CONT + j];
+    }
+}
+
+hipError_t launch_step_counts(qh_ctx *c) {
+    hipLaunchKernelGGL(k_step_counts, dim3(1), dim3(256), 0, c->stream, c->counters, c->host);
     return hipGetLastError();
 }
 
@@ -1123,8 +1174,9 @@ int qh_sort_species(qh_ctx *c, Species &s) {
     hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, c->stream, c->scan_tmp, chunks);
     hipLaunchKernelGGL(k_scan_final, dim3(chunks), dim3(1024), 0, c->stream, c->hist, nk, c->scan_tmp, c->cursor);
     const bool absorb = c->walls == QH_WALLS_ABSORB;
-    int32_t live = (int32_t)s.n;  // the start of the last bucket
-    if (absorb) QH_HIP(c, hipMemcpyAsync(&live, c->cursor + nt, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
+    // the start of the last bucket
+    if (absorb)
+        QH_HIP(c, hipMemcpyAsync(&c->host->live, c->cursor + nt, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
     if (c->perm_cap < s.n) {
         // queued work may still read the old index buffer: released after the stream passes it
         QH_HIP(c, hipStreamSynchronize(c->stream));
@@ -1143,7 +1195,7 @@ int qh_sort_species(qh_ctx *c, Species &s) {
     std::swap(s.tet, s.stet); std::swap(s.id, s.sid);
     if (absorb) {
         QH_HIP(c, hipStreamSynchronize(c->stream));
-        s.n = live;  // the absorbed particles sit past the live ones and are dropped
+        s.n = c->host->live;  // the absorbed particles sit past the live ones and are dropped
         if (s.n == 0) return QH_OK;
     }
     int32_t nb = (int32_t)qh_species_blocks(s.n);

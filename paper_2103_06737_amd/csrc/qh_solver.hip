@@ -184,23 +184,45 @@ __device__ __forceinline__ int cg_state(double rr, double rz, double thr2, int s
     return CG_RUNNING;
 }
 
-// one block: totals of the init partials; threshold; convergence flag
+// one block: totals of the init partials; threshold; convergence flag. mixed: the FP32 recurrence's
+// start, from ||r0||^2 and ||b||^2 in scal[S_RES]: its target on the scaled residual is
+// (0.9 tol ||b|| / ||r0||)^2, a little below the FP64 target, which the reliable update then usually
+// confirms at once; nothing is iterated if r0 meets the FP64 target or is not finite.
 __global__ void __launch_bounds__(kThreads) k_cg_start(const double *__restrict__ part, int m,
                                                        const double *__restrict__ rz_part, int m_rz, double *scal,
-                                                       int32_t *flags, double tol2, const double *abs_thr2, int stall) {
+                                                       int32_t *flags, double tol2, const double *abs_thr2, int stall,
+                                                       int mixed, HostResults *host) {
     __shared__ double sh[1][kThreads / 64];
     double rz = sum_partials(rz_part, m_rz, sh);
     double rr = sum_partials(part + kMaxBlocks, m, sh);
-    double bb = sum_partials(part + 2 * kMaxBlocks, m, sh);
+    double bb = mixed ? 0.0 : sum_partials(part + 2 * kMaxBlocks, m, sh);
     if (threadIdx.x == 0) {
-        double thr2 = abs_thr2 ? *abs_thr2 : tol2 * bb;
+        double thr2, rr0 = rr, target;
+        int state;
+        if (mixed) {
+            rr0 = scal[S_RES];
+            bb = scal[S_RES + 1];
+            target = tol2 * bb;
+            thr2 = 0.81 * target / rr0;
+            state = cg_state(rr0, 1.0, target, 0, 0, nullptr);
+            if (!state) state = cg_state(rr, rz, thr2, stall, 0, nullptr);
+        } else {
+            target = thr2 = abs_thr2 ? *abs_thr2 : tol2 * bb;
+            state = cg_state(rr, rz, thr2, stall, 0, nullptr);
+        }
         scal[S_RZ] = rz;
         scal[S_RR] = rr;
         scal[S_BB] = bb;
         scal[S_THR2] = thr2;
         scal[S_HIST] = rr;
-        flags[0] = cg_state(rr, rz, thr2, stall, 0, nullptr);
+        flags[0] = state;
         flags[1] = 0;
+        host->flags[0] = state;
+        host->flags[1] = 0;
+        host->rr = rr;
+        host->thr2 = target;
+        host->rr0 = rr0;
+        host->bb = bb;
     }
 }
 
@@ -369,8 +391,8 @@ template <bool JAC>
 __global__ void __launch_bounds__(kThreads) k_inner_init(int32_t n, const double *__restrict__ r, const double *rr,
                                                          double *scal, float *__restrict__ r32,
                                                          float *__restrict__ x32, float *__restrict__ z32,
-                                                         float *__restrict__ p32, const float *__restrict__ dinv32,
-                                                         double *__restrict__ part) {
+                                                         float *__restrict__ p32, const double *__restrict__ dinv,
+                                                         float *__restrict__ dinv32, double *__restrict__ part) {
     const double s = sqrt(*rr), inv = 1.0 / s;
     if (blockIdx.x == 0 && threadIdx.x == 0) scal[S_SCALE] = s;
     double acc[3] = {0.0, 0.0, 0.0};
@@ -380,7 +402,9 @@ __global__ void __launch_bounds__(kThreads) k_inner_init(int32_t n, const double
         x32[i] = 0.0f;
         p32[i] = 0.0f;
         if (JAC) {
-            const float zi = (float)((double)ri * (double)dinv32[i]);
+            const float di = (float)dinv[i];
+            dinv32[i] = di;
+            const float zi = (float)((double)ri * (double)di);
             z32[i] = zi;
             acc[0] += (double)ri * (double)zi;
         }
@@ -390,8 +414,11 @@ __global__ void __launch_bounds__(kThreads) k_inner_init(int32_t n, const double
     write_partials<3>(acc, part);
 }
 
-// Reliable update, first half: x += s d in FP64 and d = 0.
-__global__ void k_refine(int32_t n, double *__restrict__ x, float *__restrict__ d, const double *scal) {
+// Reliable update, first half: x += s d in FP64 and d = 0. A batch that met non-finite values is not
+// applied.
+__global__ void k_refine(int32_t n, double *__restrict__ x, float *__restrict__ d, const double *scal,
+                         const int32_t *flags) {
+    if (flags[0] == CG_NONFINITE) return;
     const double s = scal[S_SCALE];
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         x[i] += s * (double)d[i];
@@ -432,19 +459,24 @@ __global__ void k_convert(int64_t n, const S *__restrict__ in, D *__restrict__ o
         out[i] = (D)in[i];
 }
 
-// one block, after a batch: finish the last update's convergence test
+// one block, after a batch: finish the last update's convergence test; the verdict goes to the host
 __global__ void __launch_bounds__(kThreads) k_cg_check(const double *__restrict__ upart, int m, double *scal,
-                                                       int32_t *flags, int32_t k) {
-    if (flags[0]) return;
+                                                       int32_t *flags, int32_t k, HostResults *host) {
     __shared__ double sh[1][kThreads / 64];
     double rr = sum_partials(upart + kMaxBlocks, m, sh);
     if (threadIdx.x == 0) {
-        scal[S_RR] = rr;
-        flags[1] = k;
-        // convergence or a non-finite residual; the stall rule waits for the next product
-        // kernel, which also has r.z
-        const int state = cg_state(rr, 1.0, scal[S_THR2], 0, k, nullptr);
-        if (state) flags[0] = state;
+        int state = flags[0], it = flags[1];
+        if (!state) {
+            scal[S_RR] = rr;
+            flags[1] = it = k;
+            // convergence or a non-finite residual; the stall rule waits for the next product
+            // kernel, which also has r.z
+            state = cg_state(rr, 1.0, scal[S_THR2], 0, k, nullptr);
+            if (state) flags[0] = state;
+        }
+        host->flags[0] = state;
+        host->flags[1] = it;
+        host->rr = scal[S_RR];
     }
 }
 
@@ -543,7 +575,7 @@ __global__ void __launch_bounds__(kThreads) k_gauss_rhs(int32_t n, int32_t ns, c
                                                         const int32_t *__restrict__ int_nodes, double u_q,
                                                         const double *__restrict__ dbnd,
                                                         double *__restrict__ rg, double *__restrict__ rho_out,
-                                                        double *__restrict__ part) {
+                                                        double *__restrict__ x0, double *__restrict__ part) {
     __shared__ double part_s[kSellWaves][kSlice], part_a[kSellWaves][kSlice];
     const int32_t lane = (int32_t)(threadIdx.x & 63);
     const int32_t wid = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
@@ -574,6 +606,7 @@ __global__ void __launch_bounds__(kThreads) k_gauss_rhs(int32_t n, int32_t ns, c
             double rho = u_q * (double)(Qbg[gn] - Q[gn]) + (dbnd ? dbnd[gn] : 0.0);
             double res = rho - s;
             rg[row] = res;
+            x0[row] = 0.0;  // the node solve starts from zero
             if (rho_out) rho_out[row] = rho;
             acc[0] += rho * rho;
             acc[1] += sa * sa;
@@ -584,32 +617,32 @@ __global__ void __launch_bounds__(kThreads) k_gauss_rhs(int32_t n, int32_t ns, c
     write_partials<3>(acc, part);
 }
 
-// one block: out[0] = (tol_n scale)^2, out[1] = scale, out[2] = ||r||^2, out[3] = ||rho||
+// one block: out[0] = (tol_n scale)^2, out[1] = scale, out[2] = ||r||^2, out[3] = ||rho||, also to the host
 __global__ void __launch_bounds__(kThreads) k_gauss_finish(const double *__restrict__ part, int m, double *out,
-                                                           double tol_n) {
+                                                           double tol_n, HostResults *host) {
     __shared__ double sh[1][kThreads / 64];
     double a = sum_partials(part, m, sh);
     double b = sum_partials(part + kMaxBlocks, m, sh);
     double c = sum_partials(part + 2 * kMaxBlocks, m, sh);
     if (threadIdx.x == 0) {
         double scale = sqrt(a) + sqrt(b);
-        out[0] = tol_n * tol_n * scale * scale;
-        out[1] = scale;
-        out[2] = c;
-        out[3] = sqrt(a);
+        const double v[4] = {tol_n * tol_n * scale * scale, scale, c, sqrt(a)};
+        for (int q = 0; q < 4; ++q) out[q] = host->gauss[q] = v[q];
     }
 }
 
-// e_i += delta[head] - delta[tail] (wall nodes carry 0)
+// e_i += delta[head] - delta[tail] (wall nodes carry 0); keep: the uncorrected e (or null)
 __global__ void k_gauss_apply(int32_t n, const int32_t *__restrict__ int_edges,
                               const int32_t *__restrict__ edge_nodes, const int32_t *__restrict__ int_node_of,
-                              const double *__restrict__ delta, double *__restrict__ e) {
+                              const double *__restrict__ delta, double *__restrict__ e, double *__restrict__ keep) {
     int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     int32_t ge = int_edges[i];
     int32_t a = int_node_of[edge_nodes[2 * ge]], b = int_node_of[edge_nodes[2 * ge + 1]];
     double d = (b >= 0 ? delta[b] : 0.0) - (a >= 0 ? delta[a] : 0.0);
-    e[i] += d;
+    const double ei = e[i];
+    if (keep) keep[i] = ei;
+    e[i] = ei + d;
 }
 
 // u = round((dt/2)(e_new + e_old)/u_b) per interior edge; e (global) <- e_new
@@ -631,13 +664,14 @@ __global__ void k_faraday_b(int64_t nf, const int32_t *__restrict__ fe, const in
     b[f] -= u[fe[3 * f + 2]] - u[fe[3 * f + 1]] + u[fe[3 * f]];
 }
 
-__global__ void __launch_bounds__(kThreads) k_sum2(const double *__restrict__ part, int m, double *out) {
+__global__ void __launch_bounds__(kThreads) k_sum2(const double *__restrict__ part, int m, double *out,
+                                                   HostResults *host) {
     __shared__ double sh[1][kThreads / 64];
     double a = sum_partials(part, m, sh);
     double b = sum_partials(part + kMaxBlocks, m, sh);
     if (threadIdx.x == 0) {
-        out[0] = a;
-        out[1] = b;
+        out[0] = host->res[0] = a;
+        out[1] = host->res[1] = b;
     }
 }
 
@@ -730,7 +764,7 @@ int qh_cg_alloc(qh_ctx *c, CgWork &w, int32_t n) {
     if ((rc = qh_alloc(c, &w.x, n)) || (rc = qh_alloc(c, &w.r, n)) || (rc = qh_alloc(c, &w.z, n)) ||
         (rc = qh_alloc(c, &w.q, n)) || (rc = qh_alloc(c, &w.p0, n)) || (rc = qh_alloc(c, &w.p1, n)) ||
         (rc = qh_alloc(c, &w.dinv, n)) || (rc = qh_alloc(c, &w.b, n)) ||
-        (rc = qh_alloc(c, &w.partial, 8 * kMaxBlocks)) || (rc = qh_alloc(c, &w.scal, S_NSCAL)) ||
+        (rc = qh_alloc(c, &w.partial, 9 * kMaxBlocks)) || (rc = qh_alloc(c, &w.scal, S_NSCAL)) ||
         (rc = qh_alloc(c, &w.counter, 4)) || (rc = qh_alloc(c, &w.flags, 4)))
         return rc;
     QH_HIP(c, hipMemsetAsync(w.counter, 0, 4 * sizeof(unsigned int), c->stream));
@@ -751,6 +785,14 @@ hipError_t launch_renumber(qh_ctx *c, int64_t n, const int32_t *idx, const doubl
     return hipGetLastError();
 }
 
+// Iterations until r.r has fallen by `factor` more, from the reduction so far (rr0 -> rr in k
+// iterations); 0 if there was none.
+static int iterations_for(double rr0, double rr, int k, double factor) {
+    const double drop = rr > 0 && rr0 > 0 && k > 0 ? std::log(rr / rr0) / k : 0.0;
+    if (!(drop < 0) || !(factor > 0) || factor >= 1) return 0;
+    return (int)std::min(1e6, std::ceil(std::log(factor) / drop));
+}
+
 int qh_cg_solve(qh_ctx *c, const DevSell &M, CgWork &w, double tol, int max_it, int check_every,
                 SolveResult &out, const double *abs_thr2_dev, bool node_system, bool learned) {
     const int k_spmv = node_system ? QK_NODE_SPMV : QK_CG_SPMV;
@@ -762,17 +804,28 @@ int qh_cg_solve(qh_ctx *c, const DevSell &M, CgWork &w, double tol, int max_it, 
         return QH_OK;
     }
     // partials: [0, 4K) init / update (slot 0 r.z with Jacobi, 1 r.r, 2 b.b), [4K, 5K) products,
-    // [5K, 6K) r.z of the learned preconditioner
+    // [5K, 6K) r.z of the learned preconditioner, [6K, 8K) the true residual's, taken ahead
     double *upart = w.partial, *qpart = w.partial + 4 * kMaxBlocks, *ppart = w.partial + 5 * kMaxBlocks;
     const unsigned ge = grid_elems<double>(w.n), gt = sell_grid(M.ns);
     const unsigned gp = learned ? qh_prec_grid(c) : 0;
     const int stall = learned ? 1 : 0;
+    volatile const HostResults *H = c->host;
     if (check_every <= 0) check_every = 8;
     // iterations after convergence return at once on the device; sizing the first batch from
     // the previous solve avoids most of them and most host reads of the flag
     int first = w.last_iters[learned ? 1 : 0];
     if (first > 0) ++first;  // one idle launch when the count repeats, no second batch when it grows by one
     int it = 0;
+    // true residual, recomputed with a fresh FP64 product
+    auto residual = [&]() -> int {
+        int tr = qh_tbeg(c);
+        hipLaunchKernelGGL(k_residual<false>, dim3(gt), dim3(kThreads), 0, c->stream, w.n, M.ns, M.cols(), M.val, w.x,
+                           w.b, (double *)nullptr, upart);
+        hipLaunchKernelGGL(k_sum2, dim3(1), dim3(kThreads), 0, c->stream, upart, (int)gt, w.scal + S_RES, c->host);
+        qh_tend(c, tr, QK_TRUE_RES);
+        QH_HIP(c, hipGetLastError());
+        return QH_OK;
+    };
     // Recurrence residuals drift from the true one; a solve whose recurrence converged but whose
     // recomputed residual misses the target restarts from its iterate (at most kRestarts times)
     constexpr int kRestarts = 2;
@@ -783,36 +836,40 @@ int qh_cg_solve(qh_ctx *c, const DevSell &M, CgWork &w, double tol, int max_it, 
         if (learned) QH_HIP(c, launch_prec_apply(c, w.r, w.z, ppart, nullptr));
         hipLaunchKernelGGL(k_cg_start, dim3(1), dim3(kThreads), 0, c->stream, upart, (int)gt,
                            learned ? (const double *)ppart : (const double *)upart, learned ? (int)gp : (int)gt,
-                           w.scal, w.flags, tol * tol, abs_thr2_dev, stall);
+                           w.scal, w.flags, tol * tol, abs_thr2_dev, stall, 0, c->host);
         qh_tend(c, t0, QK_CG_INIT);
         QH_HIP(c, hipGetLastError());
         // the start's verdict is read on the host only when the last solve needed no iteration
-        // (or there was none); otherwise the first batch is launched at once, and its launches
-        // return at once if the start already stopped the iteration
-        int32_t hflags[2] = {0, 0};
+        // (or there was none); otherwise the first batch is launched at once, its launches return
+        // at once if the start already stopped the iteration, and the true residual follows it
+        // before the host looks
+        const bool ahead = first > 0 && restart == 0;
+        int stopped = 0, done = 0;  // this run's flag and iterations
+        bool have_res = false, at_start = false;
+        double rr_start = 0.0;
         int m_up = (int)gt;
-        if (!(first > 0 && restart == 0)) {
-            QH_HIP(c, hipMemcpyAsync(hflags, w.flags, sizeof(hflags), hipMemcpyDeviceToHost, c->stream));
+        if (!ahead) {
             QH_HIP(c, hipStreamSynchronize(c->stream));
+            stopped = H->flags[0];
+            at_start = stopped == CG_CONVERGED;
+            rr_start = H->rr;
         }
         const int it0 = it;  // the device counts this run's iterations from 0
-        while (it < max_it && !hflags[0]) {
-            int batch = std::min(it == it0 && first > 0 && restart == 0 ? first : check_every, max_it - it);
+        int batch = ahead ? first : check_every;
+        while (it < max_it && !stopped) {
+            batch = std::min(batch, max_it - it);
             for (int k = it - it0; k < it - it0 + batch; ++k) {
                 int par = k & 1;
                 int ta = qh_tbeg(c);
-                hipLaunchKernelGGL((M.width > 0 ? k_cg_spmv<double, double, kUAll> : k_cg_spmv<double, double, kU64>), dim3(gt), dim3(kThreads), 0, c->stream, w.n, M.ns,
-                                   M.cols(), M.val, w.z, w.p0, w.q, learned ? (const double *)ppart : (const double *)upart,
-                                   learned ? (int)gp : m_up, upart + kMaxBlocks, m_up, qpart, w.scal, w.flags, k, par,
-                                   stall);
+                hipLaunchKernelGGL((M.width > 0 ? k_cg_spmv<double, double, kUAll> : k_cg_spmv<double, double, kU64>),
+                                   dim3(gt), dim3(kThreads), 0, c->stream, w.n, M.ns, M.cols(), M.val, w.z, w.p0, w.q,
+                                   learned ? (const double *)ppart : (const double *)upart, learned ? (int)gp : m_up,
+                                   upart + kMaxBlocks, m_up, qpart, w.scal, w.flags, k, par, stall);
                 qh_tend(c, ta, k_spmv);
                 int tb = qh_tbeg(c);
-                if (learned)
-                    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_cg_update<false, double>), dim3(ge), dim3(kThreads), 0, c->stream, w.n, w.x, w.r, w.z,
-                                       w.p0, w.q, w.dinv, qpart, upart, (int)gt, w.scal, w.flags, par);
-                else
-                    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_cg_update<true, double>), dim3(ge), dim3(kThreads), 0, c->stream, w.n, w.x, w.r, w.z,
-                                       w.p0, w.q, w.dinv, qpart, upart, (int)gt, w.scal, w.flags, par);
+                hipLaunchKernelGGL((learned ? k_cg_update<false, double> : k_cg_update<true, double>), dim3(ge),
+                                   dim3(kThreads), 0, c->stream, w.n, w.x, w.r, w.z, w.p0, w.q, w.dinv, qpart, upart,
+                                   (int)gt, w.scal, w.flags, par);
                 qh_tend(c, tb, k_upd);
                 m_up = (int)ge;
                 if (learned) {
@@ -821,33 +878,61 @@ int qh_cg_solve(qh_ctx *c, const DevSell &M, CgWork &w, double tol, int max_it, 
                     qh_tend(c, tp, QK_PREC);
                 }
             }
+            const bool last_guess = ahead && it == it0;
             it += batch;
             hipLaunchKernelGGL(k_cg_check, dim3(1), dim3(kThreads), 0, c->stream, upart, m_up, w.scal, w.flags,
-                               it - it0);
+                               it - it0, c->host);
             QH_HIP(c, hipGetLastError());
-            QH_HIP(c, hipMemcpyAsync(hflags, w.flags, sizeof(hflags), hipMemcpyDeviceToHost, c->stream));
+            // the residual's partials take the update's place, which a continued run still needs
+            have_res = last_guess;
+            if (last_guess) {
+                double *keep = upart;
+                upart = w.partial + 6 * kMaxBlocks;
+                int rc = residual();
+                upart = keep;
+                if (rc) return rc;
+            }
             QH_HIP(c, hipStreamSynchronize(c->stream));
+            stopped = H->flags[0];
+            done = H->flags[1];
+            // the next read after most of the iterations that the present rate leaves to do
+            if (ahead) rr_start = H->rr0;
+            batch = std::max(check_every, 3 * iterations_for(rr_start, H->rr, it - it0, H->thr2 / H->rr) / 4);
         }
-        it = it0 + hflags[1];
+        it = it0 + done;
         out.iters = it;
-        out.flag = hflags[0];
-        // true residual, recomputed with a fresh FP64 product, against the same target
-        int tr = qh_tbeg(c);
-        hipLaunchKernelGGL(k_residual<false>, dim3(gt), dim3(kThreads), 0, c->stream, w.n, M.ns, M.cols(), M.val, w.x,
-                           w.b, (double *)nullptr, upart);
-        hipLaunchKernelGGL(k_sum2, dim3(1), dim3(kThreads), 0, c->stream, upart, (int)gt, w.scal + S_RES);
-        qh_tend(c, tr, QK_TRUE_RES);
-        double sc[S_RES + 2];
-        QH_HIP(c, hipMemcpyAsync(sc, w.scal, sizeof(sc), hipMemcpyDeviceToHost, c->stream));
-        QH_HIP(c, hipStreamSynchronize(c->stream));
-        const double res2 = sc[S_RES], bb2 = sc[S_RES + 1], thr2 = sc[S_THR2];
-        out.res = bb2 > 0 ? sqrt(res2 / bb2) : 0.0;
-        out.true_ok = res2 == res2 && res2 <= thr2;
+        out.flag = stopped;
+        if (at_start) {
+            // r = b - A x was formed anew at the start: its norm is the true residual
+            const double rr = H->rr, bb = H->bb;
+            out.res = bb > 0 ? sqrt(rr / bb) : 0.0;
+            out.true_ok = true;
+        } else {
+            if (!have_res || !stopped) {
+                int rc = residual();
+                if (rc) return rc;
+                QH_HIP(c, hipStreamSynchronize(c->stream));
+            }
+            const double res2 = H->res[0], bb2 = H->res[1], thr2 = H->thr2;
+            out.res = bb2 > 0 ? sqrt(res2 / bb2) : 0.0;
+            out.true_ok = res2 == res2 && res2 <= thr2;
+        }
         out.converged = out.flag == CG_CONVERGED && out.true_ok;
         if (out.converged || out.flag != CG_CONVERGED || it >= max_it || restart == kRestarts) break;
         out.restarts = restart + 1;
     }
     if (out.converged) w.last_iters[learned ? 1 : 0] = out.iters;
+    return QH_OK;
+}
+
+// FP32 buffers of a CgWork for n unknowns (kept when large enough)
+int qh_cg_alloc32(qh_ctx *c, CgWork &w, int32_t n) {
+    if (w.n32 >= n) return QH_OK;
+    int rc;
+    if ((rc = qh_alloc(c, &w.x32, n)) || (rc = qh_alloc(c, &w.r32, n)) || (rc = qh_alloc(c, &w.z32, n)) ||
+        (rc = qh_alloc(c, &w.p32, n)) || (rc = qh_alloc(c, &w.q32, n)) || (rc = qh_alloc(c, &w.dinv32, n)))
+        return rc;
+    w.n32 = n;
     return QH_OK;
 }
 
@@ -862,18 +947,11 @@ int qh_cg_solve(qh_ctx *c, const DevSell &M, CgWork &w, double tol, int max_it, 
 // the last batch ends at the last solve's iteration count (from the second segment on, taking in
 // a remainder of at most an eighth of a segment), where the FP64 residual usually meets the
 // target already (the recurrence aims a little lower), so a step of the benchmark takes two
-// reliable updates. Without a history, batches of check_every iterations. A batch that meets non-finite values is not
-// applied (flag 3); one stopped by the stall rule is applied and the solve returns (flag 2).
-int qh_cg_alloc32(qh_ctx *c, CgWork &w, int32_t n) {
-    if (w.n32 >= n) return QH_OK;
-    int rc;
-    if ((rc = qh_alloc(c, &w.x32, n)) || (rc = qh_alloc(c, &w.r32, n)) || (rc = qh_alloc(c, &w.z32, n)) ||
-        (rc = qh_alloc(c, &w.p32, n)) || (rc = qh_alloc(c, &w.q32, n)) || (rc = qh_alloc(c, &w.dinv32, n)))
-        return rc;
-    w.n32 = n;
-    return QH_OK;
-}
-
+// reliable updates. Without a history, a first batch of check_every iterations, then what this
+// solve's own rate gives for the segment or for the rest, whichever is less (64^3, learned, to
+// 1e-12: 5 updates of 80 iterations instead of 11). The host reads once per update: the verdict
+// of the batch and the recomputed residual. A batch that meets non-finite values is not applied
+// (flag 3); one stopped by the stall rule is applied and the solve returns (flag 2).
 int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, int check_every,
                       SolveResult &out, bool learned) {
     out = SolveResult();
@@ -885,8 +963,7 @@ int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, 
     }
     int rc;
     if ((rc = qh_cg_alloc32(c, w, n))) return rc;
-    // FP32 copies: the matrix values once per time step size, the inverse diagonal every solve
-    // (a work area may serve several systems)
+    // FP32 copy of the matrix values once per time step size
     if (!M.val32 || M.val32_tau != c->tau_assembled) {
         if (!M.val32 && (rc = qh_alloc(c, &M.val32, (size_t)M.len + kSellPad))) return rc;
         const unsigned gc = (unsigned)std::min<int64_t>((M.len + 255) / 256, 8192);
@@ -894,114 +971,95 @@ int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, 
                            M.val32);
         M.val32_tau = c->tau_assembled;
     }
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_convert<double, float>), dim3(grid_elems<float>(n)), dim3(256), 0, c->stream,
-                       (int64_t)n, (const double *)w.dinv, w.dinv32);
     QH_HIP(c, hipGetLastError());
     double *upart = w.partial, *qpart = w.partial + 4 * kMaxBlocks, *ppart = w.partial + 5 * kMaxBlocks;
     const unsigned ge = grid_elems<float>(n), gt = sell_grid(M.ns);
     const unsigned gp = learned ? qh_prec_grid(c) : 0;
     const int stall = learned ? 1 : 0;
+    volatile const HostResults *H = c->host;
     if (check_every <= 0) check_every = 8;
-    // r = b - A x in FP64 with ||r||^2 and ||b||^2 on the host
-    double sc[2] = {0.0, 0.0};
+    // r = b - A x in FP64 with ||r||^2 and ||b||^2
     auto fp64_residual = [&]() -> int {
         int tr = qh_tbeg(c);
         hipLaunchKernelGGL(k_residual<true>, dim3(gt), dim3(kThreads), 0, c->stream, n, M.ns, M.cols(), M.val, w.x, w.b,
                            w.r, upart);
-        hipLaunchKernelGGL(k_sum2, dim3(1), dim3(kThreads), 0, c->stream, upart, (int)gt, w.scal + S_RES);
+        hipLaunchKernelGGL(k_sum2, dim3(1), dim3(kThreads), 0, c->stream, upart, (int)gt, w.scal + S_RES, c->host);
         qh_tend(c, tr, QK_TRUE_RES);
         QH_HIP(c, hipGetLastError());
-        QH_HIP(c, hipMemcpyAsync(sc, w.scal + S_RES, sizeof(sc), hipMemcpyDeviceToHost, c->stream));
-        QH_HIP(c, hipStreamSynchronize(c->stream));
         return QH_OK;
     };
     if ((rc = fp64_residual())) return rc;
-    const double rr0 = sc[0], bb = sc[1], thr2 = tol * tol * bb;
-    out.res = bb > 0 ? sqrt(rr0 / bb) : 0.0;
-    if (!(rr0 == rr0) || rr0 > 1.7976931348623157e308) {
-        out.flag = CG_NONFINITE;
-        return QH_OK;
-    }
-    if (rr0 <= thr2) {
-        out.converged = out.true_ok = true;
-        out.flag = CG_CONVERGED;
-        return QH_OK;
-    }
-    // start of the FP32 recurrence; its target on the scaled residual: (0.9 tol ||b|| / s)^2, a
-    // little below the FP64 target, which the reliable update then usually confirms at once
     int t0 = qh_tbeg(c);
-    if (learned) {
-        hipLaunchKernelGGL(k_inner_init<false>, dim3(ge), dim3(kThreads), 0, c->stream, n, w.r, w.scal + S_RES, w.scal,
-                           w.r32, w.x32, w.z32, w.p32, w.dinv32, upart);
-        QH_HIP(c, launch_prec_apply32(c, w.r32, w.z32, ppart, nullptr));
-    } else {
-        hipLaunchKernelGGL(k_inner_init<true>, dim3(ge), dim3(kThreads), 0, c->stream, n, w.r, w.scal + S_RES, w.scal,
-                           w.r32, w.x32, w.z32, w.p32, w.dinv32, upart);
-    }
+    hipLaunchKernelGGL((learned ? k_inner_init<false> : k_inner_init<true>), dim3(ge), dim3(kThreads), 0, c->stream, n, w.r,
+                       w.scal + S_RES, w.scal, w.r32, w.x32, w.z32, w.p32, w.dinv, w.dinv32, upart);
+    if (learned) QH_HIP(c, launch_prec_apply32(c, w.r32, w.z32, ppart, nullptr));
     hipLaunchKernelGGL(k_cg_start, dim3(1), dim3(kThreads), 0, c->stream, upart, (int)ge,
                        learned ? (const double *)ppart : (const double *)upart, learned ? (int)gp : (int)ge,
-                       w.scal, w.flags, 0.81 * thr2 / rr0, (const double *)nullptr, stall);
+                       w.scal, w.flags, tol * tol, (const double *)nullptr, stall, 1, c->host);
     qh_tend(c, t0, QK_CG_INIT);
     QH_HIP(c, hipGetLastError());
     const int prev = w.last_mixed[learned ? 1 : 0];     // iterations of the last converged solve
     const int seg = w.last_segment[learned ? 1 : 0];    // its iterations per 1e-4 of reduction
-    int k = 0, flag = CG_RUNNING;
+    int k = 0, flag = CG_RUNNING, batch_next = check_every;
+    double rr0 = 0.0, rr = 0.0;
     for (int update = 0;; ++update) {
         // a batch: to the next segment end, at most to the last solve's iteration count (from
         // the second segment on, a last remainder of at most an eighth of a segment joins the
-        // one before it), then check_every at a time
+        // one before it), then as this solve's rate says
         int target = 0;
         if (prev > 0 && seg > 0) {
             target = std::min((update + 1) * seg, prev);
             if (update > 0 && prev - target <= seg / 8) target = prev;
         }
-        const int batch = std::min(target > k ? target - k : check_every, max_it - k);
-        int32_t hflags[2] = {0, 0};
-        if (batch > 0) {
-            for (int kk = k; kk < k + batch; ++kk) {
-                const int par = kk & 1;
-                int ta = qh_tbeg(c);
-                hipLaunchKernelGGL((M.width > 0 ? k_cg_spmv<float, float, kUAll> : k_cg_spmv<float, float, kU32>), dim3(gt), dim3(kThreads), 0, c->stream, n,
-                                   M.ns, M.cols(), (const float *)M.val32, (const float *)w.z32,
-                                   w.p32, w.q32, learned ? (const double *)ppart : (const double *)upart,
-                                   learned ? (int)gp : (int)ge, upart + kMaxBlocks, (int)ge, qpart, w.scal, w.flags,
-                                   kk, par, stall);
-                qh_tend(c, ta, QK_CG_SPMV);
-                int tb = qh_tbeg(c);
-                if (learned)
-                    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_cg_update<false, float>), dim3(ge), dim3(kThreads), 0, c->stream, n,
-                                       w.x32, w.r32, w.z32, (const float *)w.p32, (const float *)w.q32,
-                                       (const float *)w.dinv32, qpart, upart, (int)gt, w.scal, w.flags, par);
-                else
-                    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_cg_update<true, float>), dim3(ge), dim3(kThreads), 0, c->stream, n,
-                                       w.x32, w.r32, w.z32, (const float *)w.p32, (const float *)w.q32,
-                                       (const float *)w.dinv32, qpart, upart, (int)gt, w.scal, w.flags, par);
-                qh_tend(c, tb, QK_CG_UPDATE);
-                if (learned) {
-                    int tp = qh_tbeg(c);
-                    QH_HIP(c, launch_prec_apply32(c, w.r32, w.z32, ppart, w.flags));
-                    qh_tend(c, tp, QK_PREC);
-                }
+        const int batch = std::min(target > k ? target - k : batch_next, max_it - k);
+        for (int kk = k; kk < k + batch; ++kk) {
+            const int par = kk & 1;
+            int ta = qh_tbeg(c);
+            hipLaunchKernelGGL((M.width > 0 ? k_cg_spmv<float, float, kUAll> : k_cg_spmv<float, float, kU32>), dim3(gt),
+                               dim3(kThreads), 0, c->stream, n, M.ns, M.cols(), (const float *)M.val32,
+                               (const float *)w.z32, w.p32, w.q32, learned ? (const double *)ppart : (const double *)upart,
+                               learned ? (int)gp : (int)ge, upart + kMaxBlocks, (int)ge, qpart, w.scal, w.flags, kk, par,
+                               stall);
+            qh_tend(c, ta, QK_CG_SPMV);
+            int tb = qh_tbeg(c);
+            hipLaunchKernelGGL((learned ? k_cg_update<false, float> : k_cg_update<true, float>), dim3(ge), dim3(kThreads),
+                               0, c->stream, n, w.x32, w.r32, w.z32, (const float *)w.p32, (const float *)w.q32,
+                               (const float *)w.dinv32, qpart, upart, (int)gt, w.scal, w.flags, par);
+            qh_tend(c, tb, QK_CG_UPDATE);
+            if (learned) {
+                int tp = qh_tbeg(c);
+                QH_HIP(c, launch_prec_apply32(c, w.r32, w.z32, ppart, w.flags));
+                qh_tend(c, tp, QK_PREC);
             }
+        }
+        if (batch > 0)
             hipLaunchKernelGGL(k_cg_check, dim3(1), dim3(kThreads), 0, c->stream, upart, (int)ge, w.scal, w.flags,
-                               k + batch);
-            QH_HIP(c, hipGetLastError());
-            QH_HIP(c, hipMemcpyAsync(hflags, w.flags, sizeof(hflags), hipMemcpyDeviceToHost, c->stream));
-            QH_HIP(c, hipStreamSynchronize(c->stream));
-            k = hflags[0] ? hflags[1] : k + batch;
-        }
-        if (hflags[0] == CG_NONFINITE) {
-            flag = CG_NONFINITE;  // the batch is not applied: x keeps the last reliable update
-            break;
-        }
+                               k + batch, c->host);
         // reliable update: x += s d, r = b - A x in FP64
         int tf = qh_tbeg(c);
-        hipLaunchKernelGGL(k_refine, dim3(ge), dim3(kThreads), 0, c->stream, n, w.x, w.x32, (const double *)w.scal);
+        hipLaunchKernelGGL(k_refine, dim3(ge), dim3(kThreads), 0, c->stream, n, w.x, w.x32, (const double *)w.scal,
+                           (const int32_t *)w.flags);
         qh_tend(c, tf, QK_TRUE_RES);
         QH_HIP(c, hipGetLastError());
         if ((rc = fp64_residual())) return rc;
+        QH_HIP(c, hipStreamSynchronize(c->stream));
+        const int stopped = H->flags[0];
+        const double bb = H->bb, thr2 = H->thr2;
+        rr0 = H->rr0;
+        if (update == 0 && (stopped == CG_NONFINITE || rr0 <= thr2) && H->flags[1] == 0 && !(rr0 > thr2 && rr0 < INFINITY)) {
+            // the start decided: r0 meets the target, or is not finite
+            out.res = bb > 0 ? sqrt(rr0 / bb) : 0.0;
+            flag = rr0 <= thr2 ? CG_CONVERGED : CG_NONFINITE;
+            break;
+        }
+        k = stopped ? H->flags[1] : k + batch;
+        if (stopped == CG_NONFINITE) {
+            flag = CG_NONFINITE;  // the batch is not applied: x keeps the last reliable update
+            if (update == 0) out.res = bb > 0 ? sqrt(rr0 / bb) : 0.0;
+            break;
+        }
         out.refinements = update + 1;
-        const double rr = sc[0];
+        rr = H->res[0];
         out.res = bb > 0 ? sqrt(rr / bb) : 0.0;
         if (rr == rr && rr <= thr2) {
             flag = CG_CONVERGED;
@@ -1011,21 +1069,18 @@ int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, 
             flag = CG_NONFINITE;
             break;
         }
-        if (hflags[0] == CG_STALLED) {
+        if (stopped == CG_STALLED) {
             flag = CG_STALLED;
             break;
         }
         if (k >= max_it) break;
+        const int per = iterations_for(rr0, rr, k, 1e-8), rest = iterations_for(rr0, rr, k, 0.81 * thr2 / rr);
+        batch_next = std::max(check_every, std::min(per, rest));
         // the recurrence continues from the FP64 residual
         int tq = qh_tbeg(c);
-        if (learned) {
-            hipLaunchKernelGGL(k_replace<false>, dim3(ge), dim3(kThreads), 0, c->stream, n, (const double *)w.r, w.scal,
-                               w.r32, w.z32, (const float *)w.dinv32, upart, w.flags);
-            QH_HIP(c, launch_prec_apply32(c, w.r32, w.z32, ppart, nullptr));
-        } else {
-            hipLaunchKernelGGL(k_replace<true>, dim3(ge), dim3(kThreads), 0, c->stream, n, (const double *)w.r, w.scal,
-                               w.r32, w.z32, (const float *)w.dinv32, upart, w.flags);
-        }
+        hipLaunchKernelGGL((learned ? k_replace<false> : k_replace<true>), dim3(ge), dim3(kThreads), 0, c->stream, n,
+                           (const double *)w.r, w.scal, w.r32, w.z32, (const float *)w.dinv32, upart, w.flags);
+        if (learned) QH_HIP(c, launch_prec_apply32(c, w.r32, w.z32, ppart, nullptr));
         qh_tend(c, tq, QK_CG_INIT);
         QH_HIP(c, hipGetLastError());
     }
@@ -1035,9 +1090,8 @@ int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, 
     if (out.converged) {
         w.last_mixed[learned ? 1 : 0] = k;
         // iterations per 1e-4 of residual reduction (1e-8 of r.r), at least check_every
-        const double drop = sc[0] > 0 && k > 0 ? std::log(sc[0] / rr0) / k : 0.0;
-        w.last_segment[learned ? 1 : 0] =
-            drop < 0 ? (int)std::max<double>(check_every, std::min(1e6, std::ceil(std::log(1e-8) / drop))) : 0;
+        const int per = iterations_for(rr0, rr, k, 1e-8);
+        w.last_segment[learned ? 1 : 0] = per > 0 ? std::max(check_every, per) : 0;
     }
     return QH_OK;
 }
@@ -1090,8 +1144,9 @@ hipError_t launch_gauss_rhs(qh_ctx *c, double *out3, double tol_n) {
     const unsigned gr = gauss_grid(M.ns);
     hipLaunchKernelGGL(k_gauss_rhs, dim3(gr), dim3(kThreads), 0, c->stream, M.n, M.ns, M.cols(), M.val, c->cge.x,
                        c->Q_bg, c->Q, c->int_nodes, c->phys.u_q, (const double *)c->dbnd, c->cgn.b, c->rho,
-                       c->cgn.partial);
-    hipLaunchKernelGGL(k_gauss_finish, dim3(1), dim3(kThreads), 0, c->stream, c->cgn.partial, (int)gr, out3, tol_n);
+                       c->cgn.x, c->cgn.partial);
+    hipLaunchKernelGGL(k_gauss_finish, dim3(1), dim3(kThreads), 0, c->stream, c->cgn.partial, (int)gr, out3, tol_n,
+                       c->host);
     return hipGetLastError();
 }
 
@@ -1102,8 +1157,9 @@ hipError_t launch_div_e(qh_ctx *c, double *out3, double tol_n) {
     const unsigned gr = gauss_grid(M.ns);
     hipLaunchKernelGGL(k_gauss_rhs, dim3(gr), dim3(kThreads), 0, c->stream, M.n, M.ns, M.cols(), M.val, c->cge.x,
                        (const int64_t *)c->Q, (const int64_t *)c->Q, c->int_nodes, 0.0, (const double *)nullptr,
-                       c->cgn.b, (double *)nullptr, c->cgn.partial);
-    hipLaunchKernelGGL(k_gauss_finish, dim3(1), dim3(kThreads), 0, c->stream, c->cgn.partial, (int)gr, out3, tol_n);
+                       c->cgn.b, (double *)nullptr, c->cgn.x, c->cgn.partial);
+    hipLaunchKernelGGL(k_gauss_finish, dim3(1), dim3(kThreads), 0, c->stream, c->cgn.partial, (int)gr, out3, tol_n,
+                       c->host);
     return hipGetLastError();
 }
 
@@ -1111,14 +1167,17 @@ hipError_t launch_div_e(qh_ctx *c, double *out3, double tol_n) {
 hipError_t launch_grad_add(qh_ctx *c, const double *delta, double *e_int) {
     int32_t n = c->A.n;
     hipLaunchKernelGGL(k_gauss_apply, dim3((n + 255) / 256), dim3(256), 0, c->stream, n, c->int_edges, c->edge_nodes,
-                       c->int_node_of, delta, e_int);
+                       c->int_node_of, delta, e_int, (double *)nullptr);
     return hipGetLastError();
 }
 
-hipError_t launch_gauss_apply(qh_ctx *c) {
+hipError_t launch_gauss_apply(qh_ctx *c, bool delta) {
     int32_t n = c->A.n;
+    if (n == 0) return hipSuccess;
+    if (!delta)
+        return hipMemcpyAsync(c->e_star, c->cge.x, sizeof(double) * n, hipMemcpyDeviceToDevice, c->stream);
     hipLaunchKernelGGL(k_gauss_apply, dim3((n + 255) / 256), dim3(256), 0, c->stream, n, c->int_edges, c->edge_nodes,
-                       c->int_node_of, c->cgn.x, c->cge.x);
+                       c->int_node_of, c->cgn.x, c->cge.x, c->e_star);
     return hipGetLastError();
 }
 
