@@ -1814,7 +1814,6 @@ int qh_precond_train(qh_ctx *c, const qh_train_params_t *P, int32_t n_pairs, con
     QH_HIP(c, hipEventRecord(e0, c->stream));
     qh_train_stats_t S;
     std::memset(&S, 0, sizeof(S));
-    QH_HIP(c, launch_diag_inv(c, c->As, w.dinv));
     if (n_val > 0 && (rc = validate(false, &S.val_iters_jacobi))) return rc;
     int best = 1 << 30;
     if (n_val > 0) {
@@ -1841,13 +1840,8 @@ int qh_precond_train(qh_ctx *c, const qh_train_params_t *P, int32_t n_pairs, con
             }
         if ((rc = qh_learned_loss_grad(c, L.V, true, use_pairs ? P->pair_weight : 0.0, use_pairs ? idx : nullptr)))
             return rc;
-        if (step == 1) {
-            double lf[3];
-            QH_HIP(c, hipMemcpyAsync(lf, L.loss, sizeof(lf), hipMemcpyDeviceToHost, c->stream));
-            QH_HIP(c, hipStreamSynchronize(c->stream));
-            S.loss_first = lf[0];
-            S.pair_loss_first = use_pairs ? lf[2] : 0.0;
-        }
+        if (step == 1)
+            QH_HIP(c, hipMemcpyAsync(c->host->loss[0], L.loss, sizeof(c->host->loss[0]), hipMemcpyDeviceToHost, c->stream));
         L.adam_t += 1;
         if ((rc = qh_learned_adam(c, P->lr, L.adam_t))) return rc;
         S.steps_done = step;
@@ -1861,16 +1855,20 @@ int qh_precond_train(qh_ctx *c, const qh_train_params_t *P, int32_t n_pairs, con
             }
         }
     }
-    double ll[3];
-    QH_HIP(c, hipMemcpyAsync(ll, L.loss, sizeof(ll), hipMemcpyDeviceToHost, c->stream));
+    QH_HIP(c, hipMemcpyAsync(c->host->loss[1], L.loss, sizeof(c->host->loss[1]), hipMemcpyDeviceToHost, c->stream));
     if (n_val > 0) QH_HIP(c, hipMemcpyAsync(L.w, L.best_w, 4 * QH_MLP_NPARAM, hipMemcpyDeviceToDevice, c->stream));
     QH_HIP(c, hipEventRecord(e1, c->stream));
     QH_HIP(c, hipStreamSynchronize(c->stream));
     (void)hipEventElapsedTime(&S.ms, e0, e1);
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    S.loss_last = ll[0];
-    S.pair_loss_last = use_pairs ? ll[2] : 0.0;
+    const double(*loss)[3] = c->host->loss;
+    if (S.steps_done > 0) {
+        S.loss_first = loss[0][0];
+        S.pair_loss_first = use_pairs ? loss[0][2] : 0.0;
+    }
+    S.loss_last = loss[1][0];
+    S.pair_loss_last = use_pairs ? loss[1][2] : 0.0;
     S.val_iters_best = n_val > 0 ? best : 0;
     L.factor_valid = false;
     // energy-norm error of the kept network on the validation pairs, ||x - M b||_A / ||x||_A,

@@ -194,6 +194,7 @@ struct HostResults {
     double gauss[4];            // k_gauss_finish
     unsigned long long step[6]; // crossings, wall hits, lost, posted pieces, continuity, D b violations
     int32_t live;               // particles left after a sort that drops absorbed ones
+    double loss[2][3];          // a training call's first and last losses
     unsigned long long call[4]; // totals of the step call: headroom, lost, continuity, D b
 };
 
