@@ -1682,7 +1682,7 @@ int qh_precond_apply(qh_ctx *c, const double *r, double *z) {
     // r in the standalone solve's residual slot, z in its preconditioned slot; the r.z partials
     // go to its partial buffer (unused here)
     if ((rc = edge_from_host(c, r, c->cgx.q, c->cgx.r))) return rc;
-    QH_HIP(c, launch_prec_apply(c, c->cgx.r, c->cgx.z, c->cgx.partial, nullptr));
+    QH_HIP(c, launch_prec_apply(c, c->cgx.r, c->cgx.z, c->cgx.partial));
     if ((rc = edge_to_host(c, c->cgx.z, c->cgx.q, z))) return rc;
     return sync(c);
 }
@@ -1882,7 +1882,7 @@ int qh_precond_train(qh_ctx *c, const qh_train_params_t *P, int32_t n_pairs, con
         double worst = 0.0;
         for (int k = 0; k < n_val; ++k) {
             if ((rc = edge_from_host(c, rhs + (int64_t)k * n, w.q, w.r))) return rc;
-            QH_HIP(c, launch_prec_apply(c, w.r, w.z, w.partial, nullptr));
+            QH_HIP(c, launch_prec_apply(c, w.r, w.z, w.partial));
             if ((rc = edge_to_host(c, w.z, w.q, z.data()))) return rc;
             QH_HIP(c, hipStreamSynchronize(c->stream));
             const double *x = sol + (int64_t)k * n;

@@ -418,9 +418,13 @@ int qh_upload_sell(qh_ctx *c, DevSell &d, const SellHost &h);
 int qh_learned_setup(qh_ctx *c);
 int qh_learned_factor(qh_ctx *c);
 unsigned qh_prec_grid(qh_ctx *c);
-hipError_t launch_prec_apply(qh_ctx *c, const double *r, double *z, double *part, const int32_t *done);
+// y = G r (c->lp.y), z = G^T y, partials of r.z = y.y
+hipError_t launch_prec_apply(qh_ctx *c, const double *r, double *z, double *part);
 // the same on FP32 vectors (the mixed-precision solve's inner iterations)
-hipError_t launch_prec_apply32(qh_ctx *c, const float *r, float *z, double *part, const int32_t *done);
+hipError_t launch_prec_apply32(qh_ctx *c, const float *r, float *z, double *part);
+// z = G^T y for the y the iteration keeps
+hipError_t launch_prec_gt(qh_ctx *c, double *z, const int32_t *done);
+hipError_t launch_prec_gt32(qh_ctx *c, float *z, const int32_t *done);
 int qh_learned_loss_grad(qh_ctx *c, const float *V_dev, bool want_grad, double pair_weight = 0.0,
                          const int32_t *pair_idx = nullptr);
 // records the edge system's (rhs, solution) into the next slot of the pair bank (interior-edge

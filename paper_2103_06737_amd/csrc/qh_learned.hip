@@ -228,32 +228,29 @@ __global__ void k_pack_slices(int64_t len, const int32_t *__restrict__ src, cons
 }
 
 // ---------------------------------------------------------------------------------------
-// Preconditioner application: y = G r (rows of G), then z = G^T y (rows of G^T) with the
-// partials of r.z, from BF16 copies of G and G^T (the network's own precision; the products
+// Preconditioner application: y = G r (rows of G) with the partials of y.y = r.z, then z = G^T y
+// (rows of G^T), from BF16 copies of G and G^T (the network's own precision; the products
 // and sums are FP64, so M = G^T G stays one fixed SPD operator), both as products over slices of
 // 64 rows (qh_sell.h), the unknowns in device numbering.
 // T: the vectors' type (FP64, or FP32 in the inner iterations of the mixed-precision solve; the
-// products and sums are FP64 either way, and the dot product takes the stored values).
-constexpr int kUPrec = 8;  // entries in flight per lane
-template <bool DOT, typename T>
+// products and sums are FP64 either way, and the sum takes the stored values).
+template <bool SELF, int U, typename T>
 __global__ void __launch_bounds__(kSellThreads) k_prec_g(int32_t n, int32_t ns, const SellCols S,
                                                          const uint32_t *__restrict__ pk,
                                                          const T *__restrict__ in, T *__restrict__ out,
-                                                         const T *__restrict__ r, double *__restrict__ part,
-                                                         const int32_t *__restrict__ done) {
+                                                         double *__restrict__ part, const int32_t *__restrict__ done) {
     if (done && done[0]) return;  // the solve has converged: nothing left to precondition
     const SellRange sr = sell_range(ns);
     double acc = 0.0;
     for (int32_t s = sr.begin; s < sr.end; s += sr.step) {
         const int32_t row = s * kSlice + (int32_t)(threadIdx.x & 63);
-        const double rr = DOT && row < n ? (double)r[row] : 0.0;
-        const T st = (T)sell_dot_pk<kUPrec>(S, pk, in, s);
+        const T st = (T)sell_dot_pk<U>(S, pk, in, s);
         if (row < n) {
             out[row] = st;
-            if (DOT) acc += (double)st * rr;
+            if (SELF) acc += (double)st * (double)st;
         }
     }
-    if (DOT) {
+    if (SELF) {
         __shared__ double sh[kSellWaves];
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
@@ -894,7 +891,7 @@ int qh_learned_factor(qh_ctx *c) {
     return QH_OK;
 }
 
-unsigned qh_prec_grid(qh_ctx *c) { return sell_grid(c->lp.ts.ns); }
+unsigned qh_prec_grid(qh_ctx *c) { return sell_grid(c->lp.gs.ns); }
 
 // The packed copies of the present factor: made when an application first needs them (training
 // steps, which change the factor every time, do not).
@@ -909,24 +906,32 @@ static void pack_factor(qh_ctx *c) {
 }
 
 template <typename T>
-static void prec_apply(qh_ctx *c, const T *r, T *y, T *z, double *part, const int32_t *done) {
+static hipError_t prec_gt(qh_ctx *c, const T *y, T *z, const int32_t *done) {
     LearnedPrec &L = c->lp;
-    if (L.n == 0) return;
-    pack_factor(c);
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_prec_g<false, T>), dim3(sell_grid(L.gs.ns)), dim3(kSellThreads), 0, c->stream,
-                       L.n, L.gs.ns, L.gs.cols(), L.gpk, r, y, (const T *)nullptr, (double *)nullptr, done);
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_prec_g<true, T>), dim3(sell_grid(L.ts.ns)), dim3(kSellThreads), 0, c->stream,
-                       L.n, L.ts.ns, L.ts.cols(), L.tpk, (const T *)y, z, r, part, done);
-}
-
-// z = G^T (G r); part[block] = partial r.z (qh_prec_grid blocks). With done != null both
-// passes return at once when done[0] is set (a converged solve).
-hipError_t launch_prec_apply(qh_ctx *c, const double *r, double *z, double *part, const int32_t *done) {
-    prec_apply<double>(c, r, c->lp.y, z, part, done);
+    if (L.n == 0) return hipSuccess;
+    hipLaunchKernelGGL((L.ts.width > 0 ? k_prec_g<false, kUPrecAll, T> : k_prec_g<false, kUPrec, T>),
+                       dim3(sell_grid(L.ts.ns)), dim3(kSellThreads), 0, c->stream, L.n, L.ts.ns, L.ts.cols(), L.tpk, y, z,
+                       (double *)nullptr, done);
     return hipGetLastError();
 }
 
-hipError_t launch_prec_apply32(qh_ctx *c, const float *r, float *z, double *part, const int32_t *done) {
+template <typename T>
+static hipError_t prec_apply(qh_ctx *c, const T *r, T *y, T *z, double *part) {
+    LearnedPrec &L = c->lp;
+    if (L.n == 0) return hipSuccess;
+    pack_factor(c);
+    hipLaunchKernelGGL((L.gs.width > 0 ? k_prec_g<true, kUPrecAll, T> : k_prec_g<true, kUPrec, T>),
+                       dim3(sell_grid(L.gs.ns)), dim3(kSellThreads), 0, c->stream, L.n, L.gs.ns, L.gs.cols(), L.gpk, r, y,
+                       part, (const int32_t *)nullptr);
+    return prec_gt<T>(c, y, z, nullptr);
+}
+
+// y = G r, z = G^T y; part[block] = partial r.z = y.y (qh_prec_grid blocks).
+hipError_t launch_prec_apply(qh_ctx *c, const double *r, double *z, double *part) {
+    return prec_apply<double>(c, r, c->lp.y, z, part);
+}
+
+hipError_t launch_prec_apply32(qh_ctx *c, const float *r, float *z, double *part) {
     LearnedPrec &L = c->lp;
     if (!L.y32) {
         float *y = nullptr;
@@ -935,9 +940,12 @@ hipError_t launch_prec_apply32(qh_ctx *c, const float *r, float *z, double *part
         c->allocations.push_back((void *)y);
         L.y32 = y;
     }
-    prec_apply<float>(c, r, L.y32, z, part, done);
-    return hipGetLastError();
+    return prec_apply<float>(c, r, L.y32, z, part);
 }
+
+// z = G^T y for the y that the iteration keeps (c->lp.y, y32). Returns at once when done[0] is set.
+hipError_t launch_prec_gt(qh_ctx *c, double *z, const int32_t *done) { return prec_gt<double>(c, c->lp.y, z, done); }
+hipError_t launch_prec_gt32(qh_ctx *c, float *z, const int32_t *done) { return prec_gt<float>(c, c->lp.y32, z, done); }
 
 // Loss and gradient for the current weights with probes V (device, [n][16] floats).
 int qh_learned_record_pair(qh_ctx *c, const double *rhs, const double *sol, const int32_t *pos) {

@@ -21,6 +21,9 @@
 constexpr int kSlice = 64;                     // rows per slice: one per lane
 constexpr int kSellThreads = 512;
 constexpr int kSellWaves = kSellThreads / 64;  // slices a block works on side by side
+// Entries of the learned factor in flight per lane: a whole row (at most 16 on the box meshes) of a
+// small matrix, fewer for larger ones (more waves).
+constexpr int kUPrec = 8, kUPrecAll = 16;
 constexpr int kSellPad = 20 * kSlice;          // entries past the last that rounds of loads may touch
 constexpr int kSellOneWidth = 2048;            // matrices of at most this many slices get one width for all
 constexpr int kSellMaxBlocks = 1024;           // 8192 waves: what the 256 CUs hold at eight waves per SIMD
