@@ -418,6 +418,7 @@ int qh_upload_sell(qh_ctx *c, DevSell &d, const SellHost &h);
 int qh_learned_setup(qh_ctx *c);
 int qh_learned_factor(qh_ctx *c);
 unsigned qh_prec_grid(qh_ctx *c);
+hipError_t launch_prec_pack(qh_ctx *c);  // the packed copies of the present factor, if they are not there
 // y = G r (c->lp.y), z = G^T y, partials of r.z = y.y
 hipError_t launch_prec_apply(qh_ctx *c, const double *r, double *z, double *part);
 // the same on FP32 vectors (the mixed-precision solve's inner iterations)

@@ -252,8 +252,7 @@ __global__ void __launch_bounds__(kSellThreads) k_prec_g(int32_t n, int32_t ns, 
     }
     if (SELF) {
         __shared__ double sh[kSellWaves];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+        acc = wave_sum(acc);
         if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -903,6 +902,11 @@ static void pack_factor(qh_ctx *c) {
     hipLaunchKernelGGL(k_pack_slices, dim3((unsigned)((L.ts.len + 255) / 256)), dim3(256), 0, c->stream, L.ts.len,
                        L.ts.src, L.gval, L.ts.c16, L.tpk);
     L.pk_valid = true;
+}
+
+hipError_t launch_prec_pack(qh_ctx *c) {
+    pack_factor(c);
+    return hipGetLastError();
 }
 
 template <typename T>

@@ -33,6 +33,28 @@ constexpr int kSellMaxBlocks = 1024;           // 8192 waves: what the 256 CUs h
 void qh_build_sell(int32_t n, const int32_t *ptr, const int32_t *col, const int32_t *rows, const int32_t *cpos,
                    SellHost &out);
 
+// Sum over the wave's 64 lanes, the same in every lane: shifts within rows of 16, then across rows, as
+// data-parallel moves (a shuffle through LDS costs several times a move's latency, six in a chain:
+// about 0.2 us of a solver kernel's 3 to 7 us).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double wave_move(double v) {
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, true);
+    return __builtin_bit_cast(double, (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+__device__ __forceinline__ double wave_sum(double v) {
+    v += wave_move<0x111, 0xf>(v);  // row_shr:1, 2, 4, 8: lane 15 of each row has the row's sum
+    v += wave_move<0x112, 0xf>(v);
+    v += wave_move<0x114, 0xf>(v);
+    v += wave_move<0x118, 0xf>(v);
+    v += wave_move<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+    v += wave_move<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3: lane 63 has the total
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_readlane((int)b, 63), hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+    return __builtin_bit_cast(double, (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
 // Entry values: FP64, FP32, or BF16 (the high half of a packed word), all widened to FP64.
 __device__ __forceinline__ double sell_val(double v) { return v; }
 __device__ __forceinline__ double sell_val(float v) { return (double)v; }

@@ -92,8 +92,7 @@ __device__ __forceinline__ void block_sums(double (&v)[NV], double (*sh)[kThread
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
+        v[k] = wave_sum(v[k]);
         if (lane == 0) sh[k][wid] = v[k];
     }
     __syncthreads();
@@ -121,9 +120,7 @@ __device__ __forceinline__ void write_partials(double (&v)[NV], double *__restri
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-        double s = v[k];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+        const double s = wave_sum(v[k]);
         if (lane == 0) sh[k][wid] = s;
     }
     __syncthreads();
@@ -510,6 +507,210 @@ __global__ void __launch_bounds__(kThreads) k_replace(int32_t n, const double *_
     write_partials<2>(acc, part);
 }
 
+// A whole solve in one launch, for systems of at most kSmallSlices slices (3072 rows): one block of
+// sixteen waves, each with its slices' x, r, p, q in registers and the gathered vectors in LDS, so an
+// iteration costs two block barriers (three with the learned preconditioner) instead of as many
+// launches with their chains of cold loads, and the host waits once. Matrix entries stream from L2:
+// on one CU the product of 3072 rows takes about 3 us, less than the launches of an iteration; beyond
+// that the whole chip is faster. FP64 throughout (also for mixed-precision solves: the matrix is
+// cached, so FP32 saves nothing here). The same recurrences, tests and restarts as the launches.
+// 4^3 box (316 edges, 27 nodes): a solve of nine iterations 80 -> 24 us.
+constexpr int kSmallWaves = 16, kSmallThreads = 64 * kSmallWaves;
+constexpr int kRestarts = 2;  // from the iterate, when the recomputed residual misses the target
+
+inline bool small_system(const DevSell &M, bool learned) { return M.ns <= (learned ? 24 : 32); }
+
+template <int NV>
+__device__ __forceinline__ void small_sums(double (&v)[NV], double (*sh)[kSmallWaves]) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        v[k] = wave_sum(v[k]);
+        if (lane == 0) sh[k][wid] = v[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < kSmallWaves; ++w) t += sh[k][w];
+        v[k] = t;
+    }
+}
+
+// RES (Jacobi, one slice per wave, rows of at most 20 entries): the entries stay in registers from
+// iteration to iteration (with the learned factor they do not fit: 182 registers spilled).
+constexpr int kResA = 20;
+template <bool LEARNED, int NS, bool RES>
+__global__ void __launch_bounds__(kSmallThreads) k_solve_small(
+    int32_t n, int32_t ns, const SellCols S, const double *__restrict__ val, const SellCols SG,
+    const uint32_t *__restrict__ gpk, const SellCols ST, const uint32_t *__restrict__ tpk, double *__restrict__ xg,
+    const double *__restrict__ b, const double *__restrict__ dinv, double tol2, const double *abs_thr2, int max_it,
+    HostResults *host) {
+    constexpr int UA = LEARNED ? 4 : 10, UG = 4;  // entries in flight per lane, within 128 registers
+    static_assert(!RES || (NS == 1 && !LEARNED), "resident entries: Jacobi, one slice per wave");
+    extern __shared__ double lds[];  // two vectors of ns slices
+    __shared__ double sh_a[3][kSmallWaves], sh_b[1][kSmallWaves], sh_c[2][kSmallWaves];
+    __shared__ double hist[kHist];
+    const int lane = threadIdx.x & 63;
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    double *va = lds, *vb = lds + ns * kSlice;
+    double x[NS], r[NS], p[NS], q[NS], d[NS], z[NS], y[NS];  // d: D^-1 (Jacobi); y = G r (learned)
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        const int row = (wid + j * kSmallWaves) * kSlice + lane;
+        x[j] = r[j] = p[j] = q[j] = d[j] = z[j] = y[j] = 0.0;
+        if (row < n) {
+            x[j] = xg[row];
+            if (!LEARNED) d[j] = dinv[row];
+        }
+    }
+    // resident entries: FP64 values with two 16-bit columns to a word
+    double av[RES ? kResA : 1];
+    uint32_t ac[RES ? kResA / 2 : 1];
+    if (RES && wid < ns) {
+        int32_t c[kResA];
+        const double *vp = val + (int64_t)wid * S.width * kSlice + lane;
+        sell_cols<kResA>(S, wid * S.width, S.width, sell_base(S, wid), lane, 0, c);
+#pragma unroll
+        for (int u = 0; u < kResA; ++u) av[u] = u < S.width ? vp[u * kSlice] : 0.0;
+#pragma unroll
+        for (int u = 0; u < kResA / 2; ++u) ac[u] = (uint32_t)c[2 * u] | (uint32_t)c[2 * u + 1] << 16;
+    }
+    auto prod_a = [&](const double *v, int sl) {
+        if constexpr (RES) {
+            double acc = 0.0;
+#pragma unroll
+            for (int u = 0; u < kResA; ++u)
+                if (u < S.width) acc = fma(av[u], v[u & 1 ? ac[u / 2] >> 16 : ac[u / 2] & 0xffffu], acc);
+            return acc;
+        } else {
+            return sell_dot<UA>(S, val, v, sl);
+        }
+    };
+    // each(f): f(j, slice, row) for this wave's slices; f's row may lie past n (vectors hold 0 there)
+    auto each = [&](auto &&f) {
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            const int sl = wid + j * kSmallWaves;
+            if (sl < ns) f(j, sl, sl * kSlice + lane);
+        }
+    };
+    double thr2 = 0.0, rr0 = 0.0, bb0 = 0.0, res2 = 0.0, bb2 = 0.0;
+    int it = 0, state = CG_RUNNING;
+    for (int restart = 0;; ++restart) {
+        each([&](int j, int, int row) { va[row] = x[j]; });
+        __syncthreads();
+        double sa[3] = {0.0, 0.0, 0.0};  // r.z, r.r, b.b
+        each([&](int j, int sl, int row) {
+            const double ax = prod_a(va, sl), bi = row < n ? b[row] : 0.0;
+            r[j] = row < n ? bi - ax : 0.0;
+            p[j] = q[j] = 0.0;
+            z[j] = r[j] * d[j];
+            sa[0] += r[j] * z[j];
+            sa[1] += r[j] * r[j];
+            sa[2] += bi * bi;
+        });
+        if (LEARNED) {
+            each([&](int j, int, int row) { vb[row] = r[j]; });
+            __syncthreads();
+            each([&](int j, int sl, int row) {
+                y[j] = row < n ? sell_dot_pk<UG>(SG, gpk, vb, sl) : 0.0;
+                sa[0] += y[j] * y[j];
+            });
+            __syncthreads();
+            each([&](int j, int, int row) { vb[row] = y[j]; });
+            __syncthreads();
+            each([&](int j, int sl, int row) { z[j] = row < n ? sell_dot_pk<UG>(ST, tpk, vb, sl) : 0.0; });
+        }
+        small_sums<3>(sa, sh_a);
+        double rz = sa[0], rr = sa[1];
+        if (restart == 0) {
+            thr2 = abs_thr2 ? *abs_thr2 : tol2 * sa[2];
+            rr0 = rr;
+            bb0 = sa[2];
+        }
+        state = cg_state(rr, rz, thr2, LEARNED ? 1 : 0, 0, nullptr);
+        if (threadIdx.x == 0) hist[0] = rr;
+        each([&](int j, int, int row) { va[row] = z[j]; });
+        __syncthreads();
+        double beta = 0.0;
+        for (int k = 1; !state && it < max_it; ++k) {
+            double sb[1] = {0.0};
+            each([&](int j, int sl, int row) {
+                const double w = prod_a(va, sl);
+                p[j] = z[j] + beta * p[j];
+                q[j] = row < n ? w + beta * q[j] : 0.0;
+                sb[0] += p[j] * q[j];
+                if (LEARNED) vb[row] = q[j];
+            });
+            small_sums<1>(sb, sh_b);  // z is no longer read, q is there for all
+            const double alpha = rz / sb[0];
+            double sc[2] = {0.0, 0.0};  // r.z, r.r
+            each([&](int j, int sl, int row) {
+                x[j] += alpha * p[j];
+                r[j] -= alpha * q[j];
+                if (LEARNED) {
+                    const double u = sell_dot_pk<UG>(SG, gpk, vb, sl);
+                    y[j] = row < n ? y[j] - alpha * u : 0.0;
+                    va[row] = y[j];
+                    sc[0] += y[j] * y[j];
+                } else {
+                    z[j] = r[j] * d[j];
+                    va[row] = z[j];
+                    sc[0] += r[j] * z[j];
+                }
+                sc[1] += r[j] * r[j];
+            });
+            small_sums<2>(sc, sh_c);
+            if (LEARNED) {  // z = G^T y into the other vector
+                each([&](int j, int sl, int row) {
+                    z[j] = row < n ? sell_dot_pk<UG>(ST, tpk, va, sl) : 0.0;
+                    vb[row] = z[j];
+                });
+                __syncthreads();
+                double *t = va;
+                va = vb;
+                vb = t;
+            }
+            ++it;
+            beta = sc[0] / rz;
+            rz = sc[0];
+            rr = sc[1];
+            state = cg_state(rr, rz, thr2, LEARNED ? 1 : 0, k, hist);
+            if (threadIdx.x == 0) hist[k & (kHist - 1)] = rr;  // read ten iterations on
+        }
+        // true residual, recomputed
+        __syncthreads();
+        each([&](int j, int, int row) { va[row] = x[j]; });
+        __syncthreads();
+        double st[3] = {0.0, 0.0, 0.0};
+        each([&](int, int sl, int row) {
+            const double ax = prod_a(va, sl);
+            const double bi = row < n ? b[row] : 0.0, ri = row < n ? bi - ax : 0.0;
+            st[0] += ri * ri;
+            st[1] += bi * bi;
+        });
+        small_sums<3>(st, sh_a);
+        res2 = st[0];
+        bb2 = st[1];
+        __syncthreads();
+        if (state != CG_CONVERGED || res2 <= thr2 || it >= max_it || restart == kRestarts) break;
+    }
+    each([&](int j, int, int row) {
+        if (row < n) xg[row] = x[j];
+    });
+    if (threadIdx.x == 0) {
+        host->flags[0] = state;
+        host->flags[1] = it;
+        host->thr2 = thr2;
+        host->rr0 = rr0;
+        host->bb = bb0;
+        host->res[0] = res2;
+        host->res[1] = bb2;
+    }
+}
+
 template <typename S, typename D>
 __global__ void k_convert(int64_t n, const S *__restrict__ in, D *__restrict__ out) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
@@ -851,6 +1052,42 @@ static void launch_update_g(qh_ctx *c, T *x, T *r, T *y, const T *p, const T *q,
                        (const uint32_t *)L.gpk, x, r, y, p, q, qpart, m, yy_part, rr_part, scal, flags, par);
 }
 
+// The one-launch solve of a small system, from w.x; fills `out`.
+static int solve_small(qh_ctx *c, const DevSell &M, CgWork &w, double tol, int max_it, SolveResult &out,
+                       const double *abs_thr2_dev, int timer, bool learned) {
+    const LearnedPrec &L = c->lp;
+    if (learned) QH_HIP(c, launch_prec_pack(c));
+    const size_t bytes = sizeof(double) * 2 * kSlice * (size_t)M.ns;
+    int t0 = qh_tbeg(c);
+    auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(kSmallThreads), bytes, c->stream, w.n, M.ns, M.cols(),
+                           (const double *)M.val, L.gs.cols(), (const uint32_t *)L.gpk, L.ts.cols(),
+                           (const uint32_t *)L.tpk, w.x, (const double *)w.b, (const double *)w.dinv, tol * tol,
+                           abs_thr2_dev, max_it, c->host);
+    };
+    const int per = (M.ns + kSmallWaves - 1) / kSmallWaves;
+    const bool res = per == 1 && M.width > 0 && M.width <= kResA;
+    if (learned) {
+        if (per == 1) run(k_solve_small<true, 1, false>);
+        else run(k_solve_small<true, 2, false>);
+    } else {
+        if (res) run(k_solve_small<false, 1, true>);
+        else if (per == 1) run(k_solve_small<false, 1, false>);
+        else run(k_solve_small<false, 2, false>);
+    }
+    qh_tend(c, t0, timer);
+    QH_HIP(c, hipGetLastError());
+    QH_HIP(c, hipStreamSynchronize(c->stream));
+    volatile const HostResults *H = c->host;
+    const double res2 = H->res[0], bb2 = H->res[1], thr2 = H->thr2;
+    out.flag = H->flags[0];
+    out.iters = H->flags[1];
+    out.res = bb2 > 0 ? sqrt(res2 / bb2) : 0.0;
+    out.true_ok = res2 == res2 && res2 <= thr2;
+    out.converged = out.flag == CG_CONVERGED && out.true_ok;
+    return QH_OK;
+}
+
 // Iterations until r.r has fallen by `factor` more, from the reduction so far (rr0 -> rr in k
 // iterations); 0 if there was none.
 static int iterations_for(double rr0, double rr, int k, double factor) {
@@ -867,6 +1104,12 @@ int qh_cg_solve(qh_ctx *c, const DevSell &M, CgWork &w, double tol, int max_it, 
     if (w.n == 0) {
         out.converged = true;
         out.flag = CG_CONVERGED;
+        return QH_OK;
+    }
+    if (small_system(M, learned)) {
+        int rc = solve_small(c, M, w, tol, max_it, out, abs_thr2_dev, k_spmv, learned);
+        if (rc) return rc;
+        if (out.converged) w.last_iters[learned ? 1 : 0] = out.iters;
         return QH_OK;
     }
     // partials: [0, 4K) init / update (slot 0 r.z with Jacobi, 1 r.r, 2 b.b), [4K, 5K) products,
@@ -894,7 +1137,6 @@ int qh_cg_solve(qh_ctx *c, const DevSell &M, CgWork &w, double tol, int max_it, 
     };
     // Recurrence residuals drift from the true one; a solve whose recurrence converged but whose
     // recomputed residual misses the target restarts from its iterate (at most kRestarts times)
-    constexpr int kRestarts = 2;
     for (int restart = 0;; ++restart) {
         int t0 = qh_tbeg(c);
         hipLaunchKernelGGL(k_cg_init, dim3(gt), dim3(kThreads), 0, c->stream, w.n, M.ns, M.cols(), M.val,
@@ -1032,6 +1274,12 @@ int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, 
         return QH_OK;
     }
     int rc;
+    if (small_system(M, learned)) {
+        rc = solve_small(c, M, w, tol, max_it, out, nullptr, QK_CG_SPMV, learned);
+        // one FP64 residual after the start, the final one, unless the start met the target
+        out.refinements = out.flag == CG_NONFINITE || (out.converged && out.iters == 0) ? 0 : 1;
+        return rc;
+    }
     if ((rc = qh_cg_alloc32(c, w, n))) return rc;
     // FP32 copy of the matrix values once per time step size
     if (!M.val32 || M.val32_tau != c->tau_assembled) {

@@ -67,3 +67,38 @@ def test_node_solve(n):
         x, st = ctx.field_solve(qh.SYS_NODE, rhs, tol=1e-10, solver=solver)
         assert np.linalg.norm(K @ x - rhs) <= 1e-10 * np.linalg.norm(rhs) + 1e-13 * np.linalg.norm(abs(K) @ abs(x))
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [4, 7, 12])  # one launch with entries in registers, one launch, many launches
+@pytest.mark.parametrize("learned", [False, True])
+def test_iteration_cap_and_start_at_the_solution(n, learned):
+    """A solve stops at its iteration cap with the iterate of that many steps (the residual it
+    reports is that iterate's), takes none from a start that meets the target, and continues from
+    a start to the same solution."""
+    import paper_2103_06737_amd as qh
+    mesh = qi.BoxMesh(n)
+    dt = 10 * 7.68e-10 / n
+    ctx = qh.Context(0)
+    ctx.mesh_upload(mesh.xyz, mesh.tets)
+    ctx.set_physics(qi.EPS0, qi.MU0, dt, qi.QE * 2.0 ** -40, 2.0 ** -56)
+    A = systems(mesh, dt, False)
+    rhs = A @ np.random.default_rng(n).standard_normal(A.shape[0])
+    pc = qh.PC_LEARNED if learned else qh.PC_JACOBI
+    if learned:
+        ctx.precond_train(steps=20, lr=3e-3, seed=1, validate_every=0)
+    for solver in (qh.SOLVER_FP64, qh.SOLVER_MIXED):
+        if solver == qh.SOLVER_FP64 and not learned:  # (the others restart as FP64 Jacobi at their cap)
+            x3, st = ctx.field_solve(qh.SYS_EDGE, rhs, tol=1e-10, max_it=3, precond=pc, solver=solver,
+                                     allow=(qh.QH_ENOTCONV,))
+            res = np.linalg.norm(A @ x3 - rhs) / np.linalg.norm(rhs)
+            # the reported norm is of the same residual with the library's matrix: 1e-12 of rounding
+            assert st["iters"] == 3 and abs(res - st["res"]) <= 1e-12 and st["res"] > 1e-10
+        x, st = ctx.field_solve(qh.SYS_EDGE, rhs, tol=1e-10, precond=pc, solver=solver)
+        assert st["iters"] > 3 and st["res"] <= 1e-10 and st["fallback"] == 0
+        y, st0 = ctx.field_solve(qh.SYS_EDGE, rhs, x0=x, tol=2e-10, precond=pc, solver=solver)
+        assert st0["iters"] == 0 and np.array_equal(x, y)
+        # half way: fewer iterations from there, to the same target
+        h, st1 = ctx.field_solve(qh.SYS_EDGE, rhs, tol=1e-5, precond=pc, solver=solver)
+        z, st2 = ctx.field_solve(qh.SYS_EDGE, rhs, x0=h, tol=1e-10, precond=pc, solver=solver)
+        assert 0 < st2["iters"] < st["iters"] and st2["res"] <= 1e-10
+    ctx.close()
