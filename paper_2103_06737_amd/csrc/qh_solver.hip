@@ -507,14 +507,15 @@ __global__ void __launch_bounds__(kThreads) k_replace(int32_t n, const double *_
     write_partials<2>(acc, part);
 }
 
-// A whole solve in one launch, for systems of at most kSmallSlices slices (3072 rows): one block of
-// sixteen waves, each with its slices' x, r, p, q in registers and the gathered vectors in LDS, so an
-// iteration costs two block barriers (three with the learned preconditioner) instead of as many
-// launches with their chains of cold loads, and the host waits once. Matrix entries stream from L2:
-// on one CU the product of 3072 rows takes about 3 us, less than the launches of an iteration; beyond
-// that the whole chip is faster. FP64 throughout (also for mixed-precision solves: the matrix is
-// cached, so FP32 saves nothing here). The same recurrences, tests and restarts as the launches.
-// 4^3 box (316 edges, 27 nodes): a solve of nine iterations 80 -> 24 us.
+// A whole solve in one launch, for systems of at most 32 slices (2048 rows; 24 slices, 1536 rows, with
+// the learned preconditioner): one block of sixteen waves, each with its slices' x, r, p, q in registers
+// and the gathered vectors in LDS, so an iteration costs two block barriers (three with the learned
+// preconditioner) instead of as many launches with their chains of cold loads, and the host waits
+// once. FP64 throughout (also for mixed-precision solves: the matrix is cached, so FP32 saves nothing
+// here). The same recurrences, tests and restarts as the launches.
+// The limits are where one CU stops being faster than the chip. A step with 70-90 edge iterations, one
+// launch against many: Jacobi 7^3 925 against 1018 us, 8^3 1495 against 1049; learned 7^3 812 against
+// 696 (6^3: 562).
 constexpr int kSmallWaves = 16, kSmallThreads = 64 * kSmallWaves;
 constexpr int kRestarts = 2;  // from the iterate, when the recomputed residual misses the target
 
@@ -1260,8 +1261,7 @@ int qh_cg_alloc32(qh_ctx *c, CgWork &w, int32_t n) {
 // a remainder of at most an eighth of a segment), where the FP64 residual usually meets the
 // target already (the recurrence aims a little lower), so a step of the benchmark takes two
 // reliable updates. Without a history, a first batch of check_every iterations, then what this
-// solve's own rate gives for the segment or for the rest, whichever is less (64^3, learned, to
-// 1e-12: 5 updates of 80 iterations instead of 11). The host reads once per update: the verdict
+// solve's own rate gives for the segment or for the rest, whichever is less. The host reads once per update: the verdict
 // of the batch and the recomputed residual. A batch that meets non-finite values is not applied
 // (flag 3); one stopped by the stall rule is applied and the solve returns (flag 2).
 int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, int check_every,
