@@ -116,7 +116,7 @@ def algorithmic_bytes(kernel: str, mi, n_particles: int, crossings: float, learn
 
 
 # HIP kernels behind each timed entry (one entry may launch several kernels)
-HIP_KERNELS = {"particle_step": ["k_particle_step<false>", "k_mail_apply", "k_gather<0, 2>", "k_gather<6, 8>"],
+HIP_KERNELS = {"particle_step": ["k_particle_step<false>", "k_mail_apply", "k_gather<2, 8>"],
                "edge_rhs": ["k_edge_rhs_e", "k_edge_rhs_b"], "field_prep": ["k_field_prep"]}
 
 
