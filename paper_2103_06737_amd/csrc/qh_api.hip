@@ -63,7 +63,7 @@ int upload_sell_values(qh_ctx *c, DevSell &d, const HostCsr &h, const int32_t *r
     qh_build_sell((int32_t)h.nrow, h.ptr.data(), h.col.data(), rows, cpos, sh);
     int rc = qh_upload_sell(c, d, sh);
     if (rc) return rc;
-    std::vector<double> v(sh.src.size() + kSellPad, 0.0);
+    std::vector<double> v(sh.src.size(), 0.0);
     for (size_t i = 0; i < sh.src.size(); ++i)
         if (sh.src[i] >= 0) v[i] = h.val[sh.src[i]];
     if ((rc = upload(c, &d.val, v.data(), v.size()))) return rc;
@@ -119,8 +119,8 @@ int ensure_assembled(qh_ctx *c) {
             SellHost sh;
             qh_build_sell(c->A.n, c->hA.ptr.data(), c->hA.col.data(), m.order.data(), m.pos_of.data(), sh);
             c->nnz_edge_c16 = sh.nnz_c16;
-            if ((rc = qh_upload_sell(c, c->As, sh)) || (rc = qh_alloc(c, &c->As.val, (size_t)c->As.len + kSellPad)) ||
-                (rc = qh_alloc(c, &c->A_rhs, (size_t)c->As.len + kSellPad)))
+            if ((rc = qh_upload_sell(c, c->As, sh)) || (rc = qh_alloc(c, &c->As.val, (size_t)c->As.len)) ||
+                (rc = qh_alloc(c, &c->A_rhs, (size_t)c->As.len)))
                 return rc;
             QH_HIP(c, hipStreamSynchronize(c->stream));
         }
@@ -255,14 +255,14 @@ int qh_upload_sell(qh_ctx *c, DevSell &d, const SellHost &h) {
     d.ns = h.ns;
     d.width = h.width;
     d.len = (int64_t)h.src.size();
-    const size_t len = h.src.size(), room = len + kSellPad;  // rounds of loads run past the last slice
+    const size_t len = h.src.size();
     int rc;
     if ((rc = upload(c, &d.off, h.off.data(), h.off.size())) || (rc = upload(c, &d.base, h.base.data(), h.base.size())) ||
-        (rc = upload(c, &d.src, h.src.data(), len)) || (rc = qh_alloc(c, &d.c16, room)))
+        (rc = upload(c, &d.src, h.src.data(), len)) || (rc = qh_alloc(c, &d.c16, len)))
         return rc;
     QH_HIP(c, hipMemcpyAsync(d.c16, h.c16.data(), sizeof(uint16_t) * len, hipMemcpyHostToDevice, c->stream));
     if (h.wide) {
-        if ((rc = qh_alloc(c, &d.c32, room))) return rc;
+        if ((rc = qh_alloc(c, &d.c32, len))) return rc;
         QH_HIP(c, hipMemcpyAsync(d.c32, h.c32.data(), sizeof(int32_t) * len, hipMemcpyHostToDevice, c->stream));
     }
     QH_HIP(c, hipStreamSynchronize(c->stream));  // h may go

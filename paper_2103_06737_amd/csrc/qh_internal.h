@@ -73,14 +73,12 @@ void qh_assemble(const HostMesh &m, double eps0, double mu0, HostCsr &A, HostCsr
 // ---------------------------------------------------------------------------------------
 // Device containers
 // A sparse matrix in slices of 64 rows (qh_sell.h): off[s] .. off[s + 1], in units of 64 entries,
-// are slice s's entries, entry k of its 64 rows side by side. A slice whose columns lie in at most
-// four windows [w_k, w_k + 2^14) keeps each as 16 bits: the window number in the top two bits, the
-// offset from its start in the low fourteen (base[s] = {w_0, w_1, w_2, w_3}); a row couples a few
-// index clusters (on a box mesh: the layers below, at and above it), each narrow. Any other slice
-// reads 32-bit columns (base[s].x = -1).
+// are slice s's entries, entry k of its 64 rows side by side. base[off[s] + k] is the smallest of the
+// 64 columns there; a slice where every entry's columns lie within 2^16 of it keeps the differences,
+// 16 bits each. Any other slice reads 32-bit columns (its bases are -1).
 struct SellCols {
     const int32_t *off;
-    const int4 *base;
+    const int32_t *base;        // per entry of a slice: what its 64 16-bit columns count from (-1: 32-bit)
     const uint16_t *c16;
     const int32_t *c32;
     int32_t width;              // every slice's width, or 0: they differ (off)
@@ -92,7 +90,7 @@ struct SellHost {
     std::vector<int32_t> src;   // CSR entry of each stored one, -1: padding
     std::vector<int32_t> c32;
     std::vector<uint16_t> c16;
-    std::vector<int4> base;
+    std::vector<int32_t> base;
     int64_t nnz_c16 = 0;        // entries (without padding) read with 16-bit columns
     bool wide = false;          // some slice reads 32-bit columns
 };
@@ -101,7 +99,7 @@ struct DevSell {
     int32_t n = 0, ns = 0, width = 0;
     int64_t len = 0;            // stored entries, padding included
     int32_t *off = nullptr, *src = nullptr, *c32 = nullptr;
-    int4 *base = nullptr;
+    int32_t *base = nullptr;
     uint16_t *c16 = nullptr;
     double *val = nullptr;
     float *val32 = nullptr;     // FP32 copy of val for the mixed-precision solve (allocated on first use)

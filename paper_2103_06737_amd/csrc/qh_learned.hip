@@ -244,7 +244,7 @@ __global__ void __launch_bounds__(kSellThreads) k_prec_g(int32_t n, int32_t ns, 
     double acc = 0.0;
     for (int32_t s = sr.begin; s < sr.end; s += sr.step) {
         const int32_t row = s * kSlice + (int32_t)(threadIdx.x & 63);
-        const T st = (T)sell_dot_pk<U>(S, pk, in, s);
+        const T st = (T)sell_dot<U>(S, pk, in, s);
         if (row < n) {
             out[row] = st;
             if (SELF) acc += (double)st * (double)st;
@@ -785,7 +785,7 @@ int qh_learned_setup(qh_ctx *c) {
             if (q >= 0) q = tsrc[q];
         L.nnz_c16 = gh.nnz_c16 + th.nnz_c16;
         if ((rc = qh_upload_sell(c, L.gs, gh)) || (rc = qh_upload_sell(c, L.ts, th)) ||
-            (rc = qh_alloc(c, &L.gpk, (size_t)L.gs.len + kSellPad)) || (rc = qh_alloc(c, &L.tpk, (size_t)L.ts.len + kSellPad)))
+            (rc = qh_alloc(c, &L.gpk, (size_t)L.gs.len)) || (rc = qh_alloc(c, &L.tpk, (size_t)L.ts.len)))
             return rc;
         QH_HIP(c, hipStreamSynchronize(c->stream));
         if (!L.have_weights) {

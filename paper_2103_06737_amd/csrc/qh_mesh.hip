@@ -438,11 +438,39 @@ void qh_assemble(const HostMesh &m, double eps0, double mu0, HostCsr &A, HostCsr
     (void)local_edge;
 }
 
-// The windows of a slice are laid greedily from its smallest column up (each starts at the smallest
-// column not yet covered); a slice that needs more than four keeps 32-bit columns.
+namespace {
+// Slots for a row of cnt entries in a slice whose longest row has fw: increasing, the entries' column
+// distances d(k) as near as possible to that row's t(slot) (least sum of differences). A row at the
+// mesh boundary lacks some of its neighbours' entries; beside theirs, the others of its entries keep
+// the columns of a slot close together.
+template <typename D, typename T>
+void place_row(int32_t cnt, int32_t fw, D &&d, T &&t, std::vector<int32_t> &slots) {
+    slots.resize(cnt);
+    if (cnt == fw || cnt == 0) {
+        for (int32_t k = 0; k < cnt; ++k) slots[k] = k;
+        return;
+    }
+    // cost[k][i]: entries 0..k placed, entry k in slot k + i (i <= gap) at the latest
+    const int32_t gap = fw - cnt;
+    std::vector<int64_t> cost((size_t)cnt * (gap + 1));
+    for (int32_t k = 0; k < cnt; ++k)
+        for (int32_t i = 0; i <= gap; ++i) {
+            const int64_t here = std::abs((int64_t)d(k) - t(k + i)) + (k > 0 ? cost[(size_t)(k - 1) * (gap + 1) + i] : 0);
+            int64_t &c = cost[(size_t)k * (gap + 1) + i];
+            c = i > 0 ? std::min(here, cost[(size_t)k * (gap + 1) + i - 1]) : here;
+        }
+    int32_t i = gap;
+    for (int32_t k = cnt - 1; k >= 0; --k) {
+        const int64_t *c = &cost[(size_t)k * (gap + 1)];
+        while (i > 0 && c[i] == c[i - 1]) --i;
+        slots[k] = k + i;
+    }
+}
+}  // namespace
+
 void qh_build_sell(int32_t n, const int32_t *ptr, const int32_t *col, const int32_t *rows, const int32_t *cpos,
                    SellHost &o) {
-    constexpr int32_t kSpan = 1 << 14;
+    constexpr int32_t kSpan = 1 << 16;
     o = SellHost();
     o.n = n;
     o.ns = (n + kSlice - 1) / kSlice;
@@ -468,54 +496,76 @@ void qh_build_sell(int32_t n, const int32_t *ptr, const int32_t *col, const int3
     o.src.assign(len, -1);
     o.c32.assign(len, 0);
     o.c16.assign(len, 0);
-    o.base.assign((size_t)std::max(o.ns, 1), make_int4(-1, 0, 0, 0));
-    std::vector<int32_t> cs;
+    o.base.assign((size_t)std::max(o.off[o.ns], 1), -1);
+    std::vector<int32_t> slots, lo, hi;
     for (int32_t s = 0; s < o.ns; ++s) {
         const size_t e0 = (size_t)o.off[s] * kSlice;
         const int32_t w = o.off[s + 1] - o.off[s];
         if (w == 0) continue;
-        cs.clear();
+        auto row_of = [&](int l) {
+            const int32_t p = s * kSlice + l;
+            return p < n ? (rows ? rows[p] : p) : -1;
+        };
+        auto column = [&](int32_t j) { return cpos ? cpos[col[j]] : col[j]; };
+        int full = 0;  // the slice's longest row: the others' entries are placed beside its
+        for (int l = 1; l < kSlice; ++l) {
+            const int32_t r = row_of(l), f = row_of(full);
+            if (r >= 0 && ptr[r + 1] - ptr[r] > ptr[f + 1] - ptr[f]) full = l;
+        }
+        const int32_t f0 = ptr[row_of(full)], fw = ptr[row_of(full) + 1] - f0;
+        lo.assign(w, INT32_MAX);
+        hi.assign(w, -1);
         int64_t real = 0;
         for (int l = 0; l < kSlice; ++l) {
-            const int32_t p = s * kSlice + l;
-            const int32_t r = p < n ? (rows ? rows[p] : p) : -1;
+            const int32_t r = row_of(l);
             const int32_t j0 = r < 0 ? 0 : ptr[r], cnt = r < 0 ? 0 : ptr[r + 1] - ptr[r];
+            place_row(
+                cnt, fw, [&](int32_t k) { return column(j0 + k) - l; },
+                [&](int32_t k) { return column(f0 + k) - full; }, slots);
             for (int32_t k = 0; k < cnt; ++k) {
-                const int32_t c = cpos ? cpos[col[j0 + k]] : col[j0 + k];
-                o.src[e0 + (size_t)k * kSlice + l] = j0 + k;
-                o.c32[e0 + (size_t)k * kSlice + l] = c;
-                cs.push_back(c);
+                const size_t e = e0 + (size_t)slots[k] * kSlice + l;
+                o.src[e] = j0 + k;
+                o.c32[e] = column(j0 + k);
+                lo[slots[k]] = std::min(lo[slots[k]], o.c32[e]);
+                hi[slots[k]] = std::max(hi[slots[k]], o.c32[e]);
             }
             real += cnt;
         }
-        std::sort(cs.begin(), cs.end());
-        // padding reads the row's own first column (positions past the last row: the slice's)
-        for (int l = 0; l < kSlice; ++l) {
-            const int32_t c0 = o.src[e0 + l] >= 0 ? o.c32[e0 + l] : cs[0];
-            for (int32_t k = 0; k < w; ++k)
-                if (o.src[e0 + (size_t)k * kSlice + l] < 0) o.c32[e0 + (size_t)k * kSlice + l] = c0;
-        }
-        int32_t win[4];
-        int nw = 0;
-        bool fits = true;
-        for (int32_t v : cs) {
-            if (nw > 0 && v < win[nw - 1] + kSpan) continue;
-            if (nw == 4) {
-                fits = false;
-                break;
+        // padding reads the row's own column nearest to the slot's (positions past the last row and
+        // empty rows: any of the slot's)
+        for (int32_t k = 0; k < w; ++k) {
+            const int32_t a = lo[k], b = hi[k];
+            for (int l = 0; l < kSlice; ++l) {
+                const size_t e = e0 + (size_t)k * kSlice + l;
+                if (o.src[e] >= 0) continue;
+                const int32_t r = row_of(l);
+                int32_t best = b >= 0 ? a : fw > 0 ? lo[0] : 0;
+                int64_t far = INT64_MAX;
+                for (int32_t j = r < 0 ? 0 : ptr[r]; r >= 0 && j < ptr[r + 1]; ++j) {
+                    const int32_t c = column(j);
+                    const int64_t d = b < 0 ? 0 : c < a ? (int64_t)a - c : c > b ? (int64_t)c - b : 0;
+                    if (d < far) {
+                        far = d;
+                        best = c;
+                    }
+                }
+                o.c32[e] = best;
+                lo[k] = std::min(lo[k], best);
+                hi[k] = std::max(hi[k], best);
             }
-            win[nw++] = v;
         }
+        bool fits = true;
+        for (int32_t k = 0; k < w; ++k) fits = fits && (int64_t)hi[k] - lo[k] < kSpan;
         if (!fits) {
             o.wide = true;
             continue;
         }
-        for (int i = nw; i < 4; ++i) win[i] = win[nw - 1];
-        o.base[s] = make_int4(win[0], win[1], win[2], win[3]);
-        for (size_t e = e0; e < e0 + (size_t)w * kSlice; ++e) {
-            int i = nw - 1;
-            while (o.c32[e] < win[i]) --i;  // the last window starting at or below the column
-            o.c16[e] = (uint16_t)((uint32_t)i << 14 | (uint32_t)(o.c32[e] - win[i]));
+        for (int32_t k = 0; k < w; ++k) {
+            o.base[o.off[s] + k] = lo[k];
+            for (int l = 0; l < kSlice; ++l) {
+                const size_t e = e0 + (size_t)k * kSlice + l;
+                o.c16[e] = (uint16_t)(o.c32[e] - lo[k]);
+            }
         }
         o.nnz_c16 += real;
     }

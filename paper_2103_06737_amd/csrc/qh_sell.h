@@ -3,15 +3,18 @@
 // qh_learned.hip.
 //
 // Layout: rows in slices of 64, one row per lane of a wave; entry k of a slice's 64 rows is stored
-// side by side (shorter rows padded with zero values on their own first column), so a wave reads a
+// side by side (shorter rows padded with zero values on columns of their own), so a wave reads a
 // slice's values and columns coalesced, sums each row in its lane's registers and needs neither LDS
 // nor a block barrier. The edge unknowns are numbered on the device so that the 64 rows of a slice
 // are edges of one kind at consecutive nodes (HostMesh::order): the k-th entries of a slice then
 // gather from a few runs of neighbouring vector entries. What bounds the products is the gathers'
 // misses in the first-level cache; the entries of a tile of rows in storage order (products in LDS,
 // then one thread per row) touched about 25 cache lines per 64 gathers, these slices about 4 on
-// the box meshes (8.5 with the rows in edge-number order; 1024-node groups instead of 256: 3.8, but
-// the columns of a slice then no longer fit four windows at 96^3).
+// the box meshes (8.5 with the rows in edge-number order). Columns are 16 bits from a scalar base per slice entry, and a
+// round of loads has exactly as many entries as it needs: with four column windows per slice to select
+// from and a test per entry, the products at 64^3 (FP32, learned; us) took 54.4 for A, 28.9 for the
+// update with G, 23.0 for G^T, now 50.6, 24.9, 19.9; at 48^3 19.4, 12.9, 10.3, now 16.3, 10.9, 8.3.
+// At 64^3 the three read about 350 MB, more than the last-level cache holds, at 3.7 TB/s.
 #pragma once
 
 #include <type_traits>
@@ -22,9 +25,9 @@ constexpr int kSlice = 64;                     // rows per slice: one per lane
 constexpr int kSellThreads = 512;
 constexpr int kSellWaves = kSellThreads / 64;  // slices a block works on side by side
 // Entries of the learned factor in flight per lane: a whole row (at most 16 on the box meshes) of a
-// small matrix, fewer for larger ones (more waves).
+// small matrix, fewer for larger ones (more waves). 5 / 8 / 12 / 16 for the update with G: 26.8 / 24.9 /
+// 28.0 / 28.0 us at 64^3, 11.7 / 10.9 / 10.4 / 14.1 at 48^3.
 constexpr int kUPrec = 8, kUPrecAll = 16;
-constexpr int kSellPad = 20 * kSlice;          // entries past the last that rounds of loads may touch
 constexpr int kSellOneWidth = 2048;            // matrices of at most this many slices get one width for all
 constexpr int kSellMaxBlocks = 1024;           // 8192 waves: what the 256 CUs hold at eight waves per SIMD
 
@@ -100,47 +103,94 @@ __device__ __forceinline__ void sell_extent(const SellCols &S, int32_t s, int32_
     }
 }
 
-__device__ __forceinline__ int4 sell_base(const SellCols &S, int32_t s) {
-    const int4 v = S.base[s];
-    return make_int4(__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y),
-                     __builtin_amdgcn_readfirstlane(v.z), __builtin_amdgcn_readfirstlane(v.w));
+// What the 16-bit columns of the slice entries from o0 on count from, -1: they are 32-bit. Read-only
+// and the same for the whole wave: scalar loads and registers.
+typedef const __attribute__((address_space(4))) int32_t *SellScalars;
+__device__ __forceinline__ SellScalars sell_bases(const SellCols &S, int32_t o0) {
+    return (SellScalars)(uintptr_t)(S.base + o0);
 }
 
-// Gather index of a 16-bit column.
-__device__ __forceinline__ int32_t sell_col(uint32_t h, int4 base) {
-    const uint32_t q = h >> 14;
-    return (q == 0 ? base.x : q == 1 ? base.y : q == 2 ? base.z : base.w) + (int32_t)(h & 0x3fffu);
-}
-
-// Rounds of U entries per lane: U entries' loads, then U gathers are in flight together. Loads run
-// past a slice's end without a test (the arrays have kSellPad entries to spare), at constant
-// distances from one address per array; gathers past it take column `safe`, and their terms are
-// left out.
-template <int U>
-__device__ __forceinline__ void sell_cols(const SellCols &S, int32_t o0, int32_t left, int4 base, int32_t lane,
-                                          int32_t safe, int32_t (&c)[U]) {
-    static_assert(U * kSlice <= kSellPad, "a round stays inside the padding");
-    if (base.x >= 0) {
-        const uint16_t *cp = S.c16 + (int64_t)o0 * kSlice + lane;
+// A round of H entries per lane: their loads, then H gathers, are in flight together. With 16-bit
+// columns a gather's address is a scalar one (x + base) and a 32-bit offset.
+template <int H, typename VT, typename XT, typename Op>
+__device__ __forceinline__ void sell_round(const SellCols &S, const VT *__restrict__ val, const XT *__restrict__ x,
+                                           int32_t o0, bool wide, Op &op) {
+    const uint32_t lane = threadIdx.x & 63;
+    const int64_t e0 = (int64_t)o0 * kSlice;
+    const VT *vp = val + e0;
+    VT v[H];
+    XT xv[H];
 #pragma unroll
-        for (int u = 0; u < U; ++u) c[u] = cp[u * kSlice];
+    for (int u = 0; u < H; ++u) v[u] = vp[u * kSlice + lane];
+    if (!wide) {
+        const uint16_t *cp = S.c16 + e0;
+        const SellScalars base = sell_bases(S, o0);
+        uint32_t c[H];
 #pragma unroll
-        for (int u = 0; u < U; ++u) c[u] = u < left ? sell_col((uint32_t)c[u], base) : safe;
+        for (int u = 0; u < H; ++u) c[u] = cp[u * kSlice + lane];
+#pragma unroll
+        for (int u = 0; u < H; ++u) xv[u] = (x + base[u])[c[u]];
     } else {
-        const int32_t *cp = S.c32 + (int64_t)o0 * kSlice + lane;
+        const int32_t *cp = S.c32 + e0;
+        int32_t c[H];
 #pragma unroll
-        for (int u = 0; u < U; ++u) c[u] = cp[u * kSlice];
+        for (int u = 0; u < H; ++u) c[u] = cp[u * kSlice + lane];
 #pragma unroll
-        for (int u = 0; u < U; ++u) c[u] = u < left ? c[u] : safe;
+        for (int u = 0; u < H; ++u) xv[u] = x[c[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < H; ++u) op(sell_val(v[u]), (double)xv[u]);
+}
+
+// The same with BF16 entries packed with their 16-bit columns (value bits << 16 | column), one load
+// per entry; in a slice without 16-bit columns the low half is unused.
+template <int H, typename XT, typename Op>
+__device__ __forceinline__ void sell_round(const SellCols &S, const uint32_t *__restrict__ pk,
+                                           const XT *__restrict__ x, int32_t o0, bool wide, Op &op) {
+    const uint32_t lane = threadIdx.x & 63;
+    const int64_t e0 = (int64_t)o0 * kSlice;
+    const uint32_t *ep = pk + e0;
+    uint32_t e[H];
+    XT xv[H];
+#pragma unroll
+    for (int u = 0; u < H; ++u) e[u] = ep[u * kSlice + lane];
+    if (!wide) {
+        const SellScalars base = sell_bases(S, o0);
+#pragma unroll
+        for (int u = 0; u < H; ++u) xv[u] = (x + base[u])[e[u] & 0xffffu];
+    } else {
+        const int32_t *cp = S.c32 + e0;
+        int32_t c[H];
+#pragma unroll
+        for (int u = 0; u < H; ++u) c[u] = cp[u * kSlice + lane];
+#pragma unroll
+        for (int u = 0; u < H; ++u) xv[u] = x[c[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < H; ++u) op((double)__uint_as_float(e[u] & 0xffff0000u), (double)xv[u]);
+}
+
+// The round of h entries, 1 <= LO <= h <= HI: each length has its own straight code, found in
+// log2(HI) scalar branches. (One code for all lengths, with a test per entry, became branches with
+// waits for all loads between them.)
+template <int LO, int HI, typename VT, typename XT, typename Op>
+__device__ __forceinline__ void sell_pick(int32_t h, const SellCols &S, const VT *__restrict__ val,
+                                          const XT *__restrict__ x, int32_t o0, bool wide, Op &op) {
+    if constexpr (LO == HI) {
+        sell_round<LO>(S, val, x, o0, wide, op);
+    } else {
+        constexpr int MID = (LO + HI) / 2;
+        if (h <= MID) sell_pick<LO, MID>(h, S, val, x, o0, wide, op);
+        else sell_pick<MID + 1, HI>(h, S, val, x, o0, wide, op);
     }
 }
 
 // op(value, x) for every entry of this lane's row of slice s, in the row's order (padding: zero
-// values). part of parts: the entries k of [w part / parts, w (part + 1) / parts) only.
+// values), in rounds of at most U entries, as equal as they can be. part of parts: the entries k of
+// [w part / parts, w (part + 1) / parts) only.
 template <int U, typename VT, typename XT, typename Op>
 __device__ __forceinline__ void sell_each(const SellCols &S, const VT *__restrict__ val, const XT *__restrict__ x,
                                           int32_t s, Op &&op, int32_t part = 0, int32_t parts = 1) {
-    const int32_t lane = (int32_t)(threadIdx.x & 63);
     int32_t o0, w;
     sell_extent(S, s, o0, w);
     if (parts > 1) {
@@ -148,20 +198,13 @@ __device__ __forceinline__ void sell_each(const SellCols &S, const VT *__restric
         o0 += lo;
         w = hi - lo;
     }
-    const int4 base = sell_base(S, s);
-    for (; w > 0; w -= U, o0 += U) {
-        const VT *vp = val + (int64_t)o0 * kSlice + lane;
-        VT v[U];
-        int32_t c[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = vp[u * kSlice];
-        sell_cols<U>(S, o0, w, base, lane, 0, c);
-        XT xv[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) xv[u] = x[c[u]];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (u < w) op(sell_val(v[u]), (double)xv[u]);
+    if (w <= 0) return;
+    const bool wide = *sell_bases(S, o0) < 0;
+    for (int32_t rounds = (w + U - 1) / U; rounds > 0; --rounds) {
+        const int32_t h = (w + rounds - 1) / rounds;
+        sell_pick<1, U>(h, S, val, x, o0, wide, op);
+        o0 += h;
+        w -= h;
     }
 }
 
@@ -171,37 +214,5 @@ __device__ __forceinline__ double sell_dot(const SellCols &S, const VT *__restri
                                            int32_t s) {
     double acc = 0.0;
     sell_each<U>(S, val, x, s, [&](double v, double xv) { acc = fma(v, xv, acc); });
-    return acc;
-}
-
-// The same with BF16 entries packed with their 16-bit columns (value bits << 16 | column), one
-// load per entry; in a slice without 16-bit columns the low half is unused.
-template <int U, typename XT>
-__device__ __forceinline__ double sell_dot_pk(const SellCols &S, const uint32_t *__restrict__ pk,
-                                              const XT *__restrict__ x, int32_t s) {
-    const int32_t lane = (int32_t)(threadIdx.x & 63);
-    int32_t o0, w;
-    sell_extent(S, s, o0, w);
-    const int4 base = sell_base(S, s);
-    double acc = 0.0;
-    for (; w > 0; w -= U, o0 += U) {
-        const uint32_t *ep = pk + (int64_t)o0 * kSlice + lane;
-        uint32_t e[U];
-        int32_t c[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) e[u] = ep[u * kSlice];
-        if (base.x >= 0) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) c[u] = u < w ? sell_col(e[u] & 0xffffu, base) : 0;
-        } else {
-            sell_cols<U>(S, o0, w, base, lane, 0, c);
-        }
-        XT xv[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) xv[u] = x[c[u]];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (u < w) acc = fma((double)__uint_as_float(e[u] & 0xffff0000u), (double)xv[u], acc);
-    }
     return acc;
 }

@@ -19,7 +19,9 @@ constexpr int kMaxBlocks = kSellMaxBlocks;  // grids of the reducing kernels (fi
 static_assert(kMaxBlocks == 2 * kThreads, "a sum of partials takes two per thread");
 // Entries in flight per lane. Small matrices (one width for all slices, one slice per wave): a
 // launch is one chain of loads, so a row's entries (at most 19 on the box meshes) are issued
-// together; larger ones: fewer registers, more waves.
+// together; larger ones: fewer registers, more waves. FP32 10: 7 / 8 / 12 take 48.4 / 56.3 / 51.1 us at
+// 64^3 (10: 50.6) and 16.6 / 16.8 / 16.2 at 48^3 (16.3). FP64 8: 20 entries in the residual and the
+// right-hand side at 48^3 take 32.6 and 48.0 us (8: 29.7, 42.4); 5 to 10 are alike.
 constexpr int kU64 = 8;   // FP64 products
 constexpr int kU32 = 10;  // FP32 products
 constexpr int kUAll = 20; // small matrices
@@ -145,6 +147,7 @@ __device__ __forceinline__ void sell_rows(int32_t n, int32_t ns, const SellCols 
 }
 
 // init: r = b - A x, z = D^-1 r, p_old = 0; partials of r.z, r.r, b.b
+template <int U>
 __global__ void __launch_bounds__(kThreads) k_cg_init(int32_t n, int32_t ns, const SellCols S,
                                                       const double *__restrict__ val,
                                                       const double *__restrict__ x,
@@ -153,7 +156,7 @@ __global__ void __launch_bounds__(kThreads) k_cg_init(int32_t n, int32_t ns, con
                                                       double *__restrict__ r, double *__restrict__ z,
                                                       double *__restrict__ p_old, double *__restrict__ part) {
     double acc[3] = {0.0, 0.0, 0.0};
-    sell_rows<kUAll>(n, ns, S, val, x, [&](int32_t row, double s) {
+    sell_rows<U>(n, ns, S, val, x, [&](int32_t row, double s) {
         const double bb = b[row];
         const double rr = bb - s;
         const double zz = rr * dinv[row];
@@ -393,7 +396,7 @@ __global__ void __launch_bounds__(kThreads) k_cg_update_g(int32_t n, int32_t ns,
             pi = (double)p[row];
             qi = (double)q[row];
         }
-        u = sell_dot_pk<U>(S, pk, q, s);
+        u = sell_dot<U>(S, pk, q, s);
     };
     if (sr.begin < sr.end) load(sr.begin);
     block_sums<1>(pq, sh);
@@ -422,13 +425,13 @@ __global__ void __launch_bounds__(kThreads) k_cg_update_g(int32_t n, int32_t ns,
 
 // ||b - A x||^2 and ||b||^2 (partials). STORE: also r = b - A x (the mixed-precision solve's
 // reliable updates).
-template <bool STORE>
+template <bool STORE, int U>
 __global__ void __launch_bounds__(kThreads) k_residual(int32_t n, int32_t ns, const SellCols S,
                                                        const double *__restrict__ val, const double *__restrict__ x,
                                                        const double *__restrict__ b, double *__restrict__ r,
                                                        double *__restrict__ part) {
     double acc[2] = {0.0, 0.0};
-    sell_rows<kUAll>(n, ns, S, val, x, [&](int32_t row, double s) {
+    sell_rows<U>(n, ns, S, val, x, [&](int32_t row, double s) {
         const double bb = b[row];
         const double ri = bb - s;
         if (STORE) r[row] = ri;
@@ -571,10 +574,14 @@ __global__ void __launch_bounds__(kSmallThreads) k_solve_small(
     uint32_t ac[RES ? kResA / 2 : 1];
     if (RES && wid < ns) {
         int32_t c[kResA];
-        const double *vp = val + (int64_t)wid * S.width * kSlice + lane;
-        sell_cols<kResA>(S, wid * S.width, S.width, sell_base(S, wid), lane, 0, c);
+        const int32_t o0 = wid * S.width;
+        const int64_t e0 = (int64_t)o0 * kSlice + lane;
+        const bool wide = *sell_bases(S, o0) < 0;
 #pragma unroll
-        for (int u = 0; u < kResA; ++u) av[u] = u < S.width ? vp[u * kSlice] : 0.0;
+        for (int u = 0; u < kResA; ++u) {
+            av[u] = u < S.width ? val[e0 + u * kSlice] : 0.0;
+            c[u] = u >= S.width ? 0 : wide ? S.c32[e0 + u * kSlice] : S.base[o0 + u] + (int32_t)S.c16[e0 + u * kSlice];
+        }
 #pragma unroll
         for (int u = 0; u < kResA / 2; ++u) ac[u] = (uint32_t)c[2 * u] | (uint32_t)c[2 * u + 1] << 16;
     }
@@ -616,13 +623,13 @@ __global__ void __launch_bounds__(kSmallThreads) k_solve_small(
             each([&](int j, int, int row) { vb[row] = r[j]; });
             __syncthreads();
             each([&](int j, int sl, int row) {
-                y[j] = row < n ? sell_dot_pk<UG>(SG, gpk, vb, sl) : 0.0;
+                y[j] = row < n ? sell_dot<UG>(SG, gpk, vb, sl) : 0.0;
                 sa[0] += y[j] * y[j];
             });
             __syncthreads();
             each([&](int j, int, int row) { vb[row] = y[j]; });
             __syncthreads();
-            each([&](int j, int sl, int row) { z[j] = row < n ? sell_dot_pk<UG>(ST, tpk, vb, sl) : 0.0; });
+            each([&](int j, int sl, int row) { z[j] = row < n ? sell_dot<UG>(ST, tpk, vb, sl) : 0.0; });
         }
         small_sums<3>(sa, sh_a);
         double rz = sa[0], rr = sa[1];
@@ -652,7 +659,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_solve_small(
                 x[j] += alpha * p[j];
                 r[j] -= alpha * q[j];
                 if (LEARNED) {
-                    const double u = sell_dot_pk<UG>(SG, gpk, vb, sl);
+                    const double u = sell_dot<UG>(SG, gpk, vb, sl);
                     y[j] = row < n ? y[j] - alpha * u : 0.0;
                     va[row] = y[j];
                     sc[0] += y[j] * y[j];
@@ -666,7 +673,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_solve_small(
             small_sums<2>(sc, sh_c);
             if (LEARNED) {  // z = G^T y into the other vector
                 each([&](int j, int sl, int row) {
-                    z[j] = row < n ? sell_dot_pk<UG>(ST, tpk, va, sl) : 0.0;
+                    z[j] = row < n ? sell_dot<UG>(ST, tpk, va, sl) : 0.0;
                     vb[row] = z[j];
                 });
                 __syncthreads();
@@ -740,20 +747,37 @@ __global__ void __launch_bounds__(kThreads) k_cg_check(const double *__restrict_
 }
 
 __global__ void k_diag_inv(int32_t n, const SellCols S, const double *__restrict__ val, double *__restrict__ dinv) {
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x, s = i / kSlice, l = i % kSlice;
+    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int32_t s = __builtin_amdgcn_readfirstlane(i / kSlice), l = i % kSlice;
     if (i >= n) return;
-    const int4 b = S.base[s];
     double d = 0.0;
-    for (int32_t k = S.off[s]; k < S.off[s + 1]; ++k) {
-        const int64_t e = (int64_t)k * kSlice + l;
-        int32_t c;
-        if (b.x >= 0) {
-            const uint32_t h = S.c16[e], q = h >> 14;
-            c = (q == 0 ? b.x : q == 1 ? b.y : q == 2 ? b.z : b.w) + (int32_t)(h & 0x3fffu);
+    int32_t o0, w;
+    sell_extent(S, s, o0, w);
+    if (w > 0) {
+        const SellScalars base = sell_bases(S, o0);
+        const bool wide = base[0] < 0;
+        const int64_t e0 = (int64_t)o0 * kSlice + l;
+        auto take = [&](int32_t k) {
+            const double v = val[e0 + (int64_t)k * kSlice];
+            if (v != 0.0) d = v;  // padding holds zeros
+        };
+        if (wide) {
+            for (int32_t k = 0; k < w; ++k)
+                if (S.c32[e0 + (int64_t)k * kSlice] == i) take(k);
         } else {
-            c = S.c32[e];
+            const uint16_t *cp = S.c16 + e0;
+            int32_t k = 0;
+            for (; k + 4 <= w; k += 4) {  // four columns' loads in flight
+                uint32_t c[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) c[u] = cp[(int64_t)(k + u) * kSlice];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (base[k + u] + (int32_t)c[u] == i) take(k + u);
+            }
+            for (; k < w; ++k)
+                if (base[k] + (int32_t)cp[(int64_t)k * kSlice] == i) take(k);
         }
-        if (c == i && val[e] != 0.0) d = val[e];  // padding holds zeros
     }
     dinv[i] = d != 0.0 ? 1.0 / d : 0.0;
 }
@@ -790,6 +814,7 @@ __global__ void k_renumber(int64_t n, const int32_t *__restrict__ idx, const dou
 // The second takes its rows in interior-edge order (pos: their place in rhs): face fluxes are kept
 // by face number, a dozen per node, and the edges of one node share most of them. Rows in device
 // numbering would gather 96 bytes apart (48^3: 93 us for both passes in one kernel, 86 us so).
+template <int U>
 __global__ void __launch_bounds__(kThreads) k_edge_rhs_e(int32_t n, int32_t ns, const SellCols S,
                                                          const double *__restrict__ mval,
                                                          const double *__restrict__ e,
@@ -799,11 +824,12 @@ __global__ void __launch_bounds__(kThreads) k_edge_rhs_e(int32_t n, int32_t ns, 
     const SellRange r = sell_range(ns);
     for (int32_t s = r.begin; s < r.end; s += r.step) {
         const int32_t row = s * kSlice + (int32_t)(threadIdx.x & 63);
-        const double a = sell_dot<kUAll>(S, mval, e, s);
+        const double a = sell_dot<U>(S, mval, e, s);
         if (row < n) rhs[row] = a - u_q * (double)g[int_edges[row]];
     }
 }
 
+template <int U>
 __global__ void __launch_bounds__(kThreads) k_edge_rhs_b(int32_t n, int32_t ns, const SellCols S,
                                                          const double *__restrict__ cval,
                                                          const int64_t *__restrict__ b, double dtub,
@@ -811,7 +837,7 @@ __global__ void __launch_bounds__(kThreads) k_edge_rhs_b(int32_t n, int32_t ns, 
     const SellRange r = sell_range(ns);
     for (int32_t s = r.begin; s < r.end; s += r.step) {
         const int32_t row = s * kSlice + (int32_t)(threadIdx.x & 63);
-        const double t = sell_dot<kUAll>(S, cval, b, s);
+        const double t = sell_dot<U>(S, cval, b, s);
         if (row < n) {
             double *d = rhs + pos[row];
             *d += dtub * t;
@@ -937,6 +963,7 @@ __global__ void __launch_bounds__(kThreads) k_sum2(const double *__restrict__ pa
 // Right-hand side of the wave-equation update (eq. wave_cont, Newmark beta = 1/4, gamma = 1/2)
 // on the interior edges:
 //   rhs = 2 ([*eps] - tau S) e^n - ([*eps] + tau S) e^{n-1} - u_q (g^{n+1/2} - g^{n-1/2}).
+template <int U>
 __global__ void __launch_bounds__(kThreads) k_wave_rhs(int32_t n, int32_t ns, const SellCols S,
                                                        const double *__restrict__ arhs,
                                                        const double *__restrict__ aval,
@@ -949,8 +976,8 @@ __global__ void __launch_bounds__(kThreads) k_wave_rhs(int32_t n, int32_t ns, co
     const SellRange r = sell_range(ns);
     for (int32_t s = r.begin; s < r.end; s += r.step) {
         const int32_t row = s * kSlice + (int32_t)(threadIdx.x & 63);
-        const double a = sell_dot<kUAll>(S, arhs, e, s);
-        const double ap = sell_dot<kUAll>(S, aval, e_prev, s);
+        const double a = sell_dot<U>(S, arhs, e, s);
+        const double ap = sell_dot<U>(S, aval, e_prev, s);
         if (row < n) {
             const int32_t ge = int_edges[row];
             rhs[row] = (2.0 * a - u_q * (double)(g[ge] - g_prev[ge])) - ap;
@@ -1129,7 +1156,7 @@ int qh_cg_solve(qh_ctx *c, const DevSell &M, CgWork &w, double tol, int max_it, 
     // true residual, recomputed with a fresh FP64 product
     auto residual = [&]() -> int {
         int tr = qh_tbeg(c);
-        hipLaunchKernelGGL(k_residual<false>, dim3(gt), dim3(kThreads), 0, c->stream, w.n, M.ns, M.cols(), M.val, w.x,
+        hipLaunchKernelGGL((M.width > 0 ? k_residual<false, kUAll> : k_residual<false, kU64>), dim3(gt), dim3(kThreads), 0, c->stream, w.n, M.ns, M.cols(), M.val, w.x,
                            w.b, (double *)nullptr, upart);
         hipLaunchKernelGGL(k_sum2, dim3(1), dim3(kThreads), 0, c->stream, upart, (int)gt, w.scal + S_RES, c->host);
         qh_tend(c, tr, QK_TRUE_RES);
@@ -1140,7 +1167,7 @@ int qh_cg_solve(qh_ctx *c, const DevSell &M, CgWork &w, double tol, int max_it, 
     // recomputed residual misses the target restarts from its iterate (at most kRestarts times)
     for (int restart = 0;; ++restart) {
         int t0 = qh_tbeg(c);
-        hipLaunchKernelGGL(k_cg_init, dim3(gt), dim3(kThreads), 0, c->stream, w.n, M.ns, M.cols(), M.val,
+        hipLaunchKernelGGL((M.width > 0 ? k_cg_init<kUAll> : k_cg_init<kU64>), dim3(gt), dim3(kThreads), 0, c->stream, w.n, M.ns, M.cols(), M.val,
                            w.x, w.b, w.dinv, w.r, w.z, w.p0, upart);
         if (learned) QH_HIP(c, launch_prec_apply(c, w.r, w.z, ppart));
         hipLaunchKernelGGL(k_cg_start, dim3(1), dim3(kThreads), 0, c->stream, upart, (int)gt,
@@ -1283,7 +1310,7 @@ int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, 
     if ((rc = qh_cg_alloc32(c, w, n))) return rc;
     // FP32 copy of the matrix values once per time step size
     if (!M.val32 || M.val32_tau != c->tau_assembled) {
-        if (!M.val32 && (rc = qh_alloc(c, &M.val32, (size_t)M.len + kSellPad))) return rc;
+        if (!M.val32 && (rc = qh_alloc(c, &M.val32, (size_t)M.len))) return rc;
         const unsigned gc = (unsigned)std::min<int64_t>((M.len + 255) / 256, 8192);
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_convert<double, float>), dim3(gc), dim3(256), 0, c->stream, M.len, M.val,
                            M.val32);
@@ -1299,7 +1326,7 @@ int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, 
     // r = b - A x in FP64 with ||r||^2 and ||b||^2
     auto fp64_residual = [&]() -> int {
         int tr = qh_tbeg(c);
-        hipLaunchKernelGGL(k_residual<true>, dim3(gt), dim3(kThreads), 0, c->stream, n, M.ns, M.cols(), M.val, w.x, w.b,
+        hipLaunchKernelGGL((M.width > 0 ? k_residual<true, kUAll> : k_residual<true, kU64>), dim3(gt), dim3(kThreads), 0, c->stream, n, M.ns, M.cols(), M.val, w.x, w.b,
                            w.r, upart);
         hipLaunchKernelGGL(k_sum2, dim3(1), dim3(kThreads), 0, c->stream, upart, (int)gt, w.scal + S_RES, c->host);
         qh_tend(c, tr, QK_TRUE_RES);
@@ -1433,16 +1460,16 @@ hipError_t launch_assemble_A(qh_ctx *c, double tau) {
 
 hipError_t launch_edge_rhs(qh_ctx *c) {
     const DevSell &A = c->As, &C = c->CMb;
-    hipLaunchKernelGGL(k_edge_rhs_e, dim3(sell_grid(A.ns)), dim3(kThreads), 0,
+    hipLaunchKernelGGL((A.width > 0 ? k_edge_rhs_e<kUAll> : k_edge_rhs_e<kU64>), dim3(sell_grid(A.ns)), dim3(kThreads), 0,
                        c->stream, A.n, A.ns, A.cols(), c->A_rhs, c->cge.x, c->g, c->int_edges, c->phys.u_q, c->cge.b);
-    hipLaunchKernelGGL(k_edge_rhs_b, dim3(sell_grid(C.ns)), dim3(kThreads), 0,
+    hipLaunchKernelGGL((C.width > 0 ? k_edge_rhs_b<kUAll> : k_edge_rhs_b<kU64>), dim3(sell_grid(C.ns)), dim3(kThreads), 0,
                        c->stream, C.n, C.ns, C.cols(), C.val, c->b, c->phys.dt * c->phys.u_b, c->pos_of, c->cge.b);
     return hipGetLastError();
 }
 
 hipError_t launch_wave_rhs(qh_ctx *c) {
     const DevSell &A = c->As;
-    hipLaunchKernelGGL(k_wave_rhs, dim3(sell_grid(A.ns)), dim3(kThreads), 0, c->stream, A.n, A.ns, A.cols(), c->A_rhs,
+    hipLaunchKernelGGL((A.width > 0 ? k_wave_rhs<kUAll> : k_wave_rhs<kU64>), dim3(sell_grid(A.ns)), dim3(kThreads), 0, c->stream, A.n, A.ns, A.cols(), c->A_rhs,
                        A.val, c->cge.x, c->e_prev, c->g, c->g_prev, c->int_edges, c->phys.u_q, c->cge.b);
     return hipGetLastError();
 }

@@ -19,8 +19,10 @@ def systems(mesh, dt, natural):
     return A
 
 
-# interior edges 26, 117, 316, 1981, 9519 with PEC walls; every edge (98, 1115) with natural ones
-@pytest.mark.parametrize("n,natural", [(2, False), (3, False), (4, False), (7, False), (12, False), (2, True), (5, True)])
+# interior edges 26, 117, 316, 1981, 9519 with PEC walls; every edge (98, 1115) with natural ones; and
+# 2293 slices (146,692 edges), past the 2048 with one width for all: rounds of several lengths
+@pytest.mark.parametrize("n,natural", [(2, False), (3, False), (4, False), (7, False), (12, False), (2, True), (5, True),
+                                       (28, False)])
 def test_edge_solves_and_application(n, natural):
     import paper_2103_06737_amd as qh
     mesh = qi.BoxMesh(n)
