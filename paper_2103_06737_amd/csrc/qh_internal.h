@@ -168,8 +168,8 @@ struct LearnedPrec {
     double *y = nullptr;
     float *y32 = nullptr;  // the application's intermediate G r on FP32 vectors (allocated on first use)
     float *w = nullptr, *best_w = nullptr, *adam_m = nullptr, *adam_v = nullptr, *grad = nullptr;
-    float *gpart = nullptr, *W = nullptr, *AW = nullptr, *V = nullptr;
-    double *tpart = nullptr, *lpart = nullptr, *loss = nullptr, *gpart2 = nullptr;
+    float *W = nullptr, *AW = nullptr, *V = nullptr;
+    double *tpart = nullptr, *lpart = nullptr, *loss = nullptr, *gpart = nullptr, *gpart2 = nullptr;
     int32_t adam_t = 0;
     // (rhs, solution) pairs of the edge system recorded from field steps, FP32, pair-major
     // [k][n], with x.b of each (= ||x||_A^2 for A x = b), and the training's pair products

@@ -51,10 +51,11 @@ __device__ __forceinline__ bf16x4 bf16x4_of(float a, float b, float c, float d) 
     const u32x2 u = {pk_bf16(a, b), pk_bf16(c, d)};
     return __builtin_bit_cast(bf16x4, u);
 }
+// one instruction (fmaxf takes two: it quiets its operand first); NaN gives 0
+__device__ __forceinline__ float relu(float v) { return __builtin_amdgcn_fmed3f(v, 0.f, __builtin_inff()); }
 __device__ __forceinline__ bf16x4 bf16x4_relu(f32x4 z) {
-    return bf16x4_of(fmaxf(z[0], 0.f), fmaxf(z[1], 0.f), fmaxf(z[2], 0.f), fmaxf(z[3], 0.f));
+    return bf16x4_of(relu(z[0]), relu(z[1]), relu(z[2]), relu(z[3]));
 }
-__device__ __forceinline__ float relu(float v) { return v > 0.f ? v : 0.f; }
 // K = 16: A lane l holds A[l%16][4(l/16)+j], B lane l holds B[4(l/16)+j][l%16]
 __device__ __forceinline__ f32x4 mfma16(bf16x4 a, bf16x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
@@ -80,23 +81,32 @@ __device__ __forceinline__ void wave_lds_sync() {
 __device__ __forceinline__ float softplus_f(float x) { return x > 20.f ? x : log1pf(expf(x)); }
 __device__ __forceinline__ float sigmoid_f(float x) { return 1.f / (1.f + expf(-x)); }
 
-// Weight fragments of one wave. Layer 1: Z1^T = W1 X^T (A = rows 16mb.. of W1, k = features);
-// layer 2: Z2^T = W2 H1^T (A = rows 16mb.. of W2, k block q = hidden units 32q + hid32).
-struct Frags {
-    bf16x4 w1[4];
-    bf16x8s w2[4][2];
-};
+// Weight fragments. Layer 1: Z1^T = W1 X^T (A = rows 16mb.. of W1, k = features), in registers;
+// layer 2: Z2^T = W2 H1^T (A = rows 16mb.. of W2, k block q = hidden units 32q + hid32), in LDS by
+// lane: in registers they take 32 a layer and direction, a wave per SIMD in either kernel.
+typedef bf16x8s W2Frags[4][2][64];
 
-__device__ __forceinline__ void load_frags(const float *__restrict__ w, Frags &F) {
+__device__ __forceinline__ void load_w1(const float *__restrict__ w, bf16x4 (&w1)[4]) {
     const int l = threadIdx.x & 63, r = l & 15, g = l >> 4;
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
+    for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) F.w1[mb][j] = f2bf(w[kOffW1 + (16 * mb + r) * kF + 4 * g + j]);
+        for (int j = 0; j < 4; ++j) w1[mb][j] = f2bf(w[kOffW1 + (16 * mb + r) * kF + 4 * g + j]);
+}
+
+// W2, or W2^T (k block q = outputs 32q + hid32); the caller synchronises the block.
+template <bool TRANSPOSED, int WAVES>
+__device__ __forceinline__ void load_w2(const float *__restrict__ w, W2Frags &w2) {
+    const int l = threadIdx.x & 63, r = l & 15, g = l >> 4;
+    for (int k = threadIdx.x >> 6; k < 8; k += WAVES) {
+        const int row = 16 * (k >> 1) + r;
+        bf16x8s a;
 #pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) F.w2[mb][q][j] = f2bf(w[kOffW2 + (16 * mb + r) * kH + 32 * q + hid32(g, j)]);
+        for (int j = 0; j < 8; ++j) {
+            const int col = 32 * (k & 1) + hid32(g, j);
+            a[j] = f2bf(w[kOffW2 + (TRANSPOSED ? col * kH + row : row * kH + col)]);
+        }
+        w2[k >> 1][k & 1][l] = a;
     }
 }
 
@@ -126,26 +136,31 @@ __device__ __forceinline__ bf16x4 load_x(const unsigned short *__restrict__ feat
     return __builtin_bit_cast(bf16x4, u);
 }
 
-// Forward pass of one 16-entry tile (entries e0 + l%16, features x). Returns o for entry
-// e0 + l%16 in every lane; z1, z2 (pre-activations, feature-major) and H1 in BF16 are kept
-// for the backward pass. Biases initialise the accumulators.
-__device__ __forceinline__ float tile_forward(const Frags &F, const float *vec, bf16x4 x, f32x4 (&z1)[4],
-                                              f32x4 (&z2)[4], bf16x4 (&h1b)[4]) {
+// Hidden layers of one 16-entry tile (entries e0 + l%16, features x): z1, z2 (pre-activations,
+// feature-major) and H1 in BF16. Biases initialise the accumulators.
+__device__ __forceinline__ void tile_forward(const bf16x4 (&w1)[4], const W2Frags &w2, const float *vec,
+                                              bf16x4 x, f32x4 (&z1)[4], f32x4 (&z2)[4], bf16x4 (&h1b)[4]) {
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb) {
-        z1[mb] = mfma16(F.w1[mb], x, vec4(vec, kVecB1, mb));
+        z1[mb] = mfma16(w1[mb], x, vec4(vec, kVecB1, mb));
         h1b[mb] = bf16x4_relu(z1[mb]);
     }
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb) {
+        z2[mb] = vec4(vec, kVecB2, mb);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) z2[mb] = mfma32(w2[mb][q][threadIdx.x & 63], cat8(h1b[2 * q], h1b[2 * q + 1]), z2[mb]);
+    }
+}
+
+// The network's output for entry e0 + l%16, in every lane.
+__device__ __forceinline__ float tile_output(const float *vec, const f32x4 (&z2)[4]) {
     float s = 0.f;
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb) {
-        f32x4 c = vec4(vec, kVecB2, mb);
-#pragma unroll
-        for (int q = 0; q < 2; ++q) c = mfma32(F.w2[mb][q], cat8(h1b[2 * q], h1b[2 * q + 1]), c);
-        z2[mb] = c;
         const f32x4 w3 = vec4(vec, kVecW3, mb);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) s += relu(c[j]) * w3[j];
+        for (int j = 0; j < 4; ++j) s += relu(z2[mb][j]) * w3[j];
     }
     s += __shfl_xor(s, 16, 64);
     s += __shfl_xor(s, 32, 64);
@@ -161,16 +176,21 @@ __device__ __forceinline__ float g_of(float o, bool diag, float scale) {
 
 // ---------------------------------------------------------------------------------------
 // Inference: G values for all pattern entries (and G^T values through the permutation).
-__global__ void __launch_bounds__(64 * kWaves) k_mlp_factor(const float *__restrict__ w,
-                                                            const unsigned short *__restrict__ feats,
-                                                            const int32_t *__restrict__ grow,
-                                                            const int32_t *__restrict__ gcol,
-                                                            const float *__restrict__ gscale, int64_t nnz,
-                                                            float *__restrict__ o_out, float *__restrict__ gval) {
+// Four waves per SIMD; with W2 in registers three (121 and 36 accumulation registers): 0.77 M entries
+// (24^3) 29.0 us, now 23.1.
+__global__ void __launch_bounds__(64 * kWaves, 4) k_mlp_factor(const float *__restrict__ w,
+                                                               const unsigned short *__restrict__ feats,
+                                                               const int32_t *__restrict__ grow,
+                                                               const int32_t *__restrict__ gcol,
+                                                               const float *__restrict__ gscale, int64_t nnz,
+                                                               float *__restrict__ o_out, float *__restrict__ gval) {
     __shared__ __align__(16) float vec[196];
+    __shared__ W2Frags w2;
     load_vecs(w, vec);
-    Frags F;
-    load_frags(w, F);
+    load_w2<false, kWaves>(w, w2);
+    bf16x4 w1[4];
+    load_w1(w, w1);
+    __syncthreads();
     const int l = threadIdx.x & 63;
     const int64_t wave = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
     const int64_t nwaves = (int64_t)gridDim.x * kWaves;
@@ -190,6 +210,7 @@ __global__ void __launch_bounds__(64 * kWaves) k_mlp_factor(const float *__restr
     bool dgn;
     load_out(wave * 32, gsn, dgn);
     for (int64_t e0 = wave * 32; e0 < nnz; e0 += nwaves * 32) {
+        wave_lds_sync();  // keeps the fragments and vectors in LDS: hoisted, they would cost a wave per SIMD
         const bf16x4 x0 = xn[0], x1 = xn[1];
         const float gs = gsn;
         const bool dg = dgn;
@@ -198,8 +219,10 @@ __global__ void __launch_bounds__(64 * kWaves) k_mlp_factor(const float *__restr
         load_out(e0 + nwaves * 32, gsn, dgn);
         f32x4 z1[4], z2[4];
         bf16x4 h1b[4];
-        const float o0 = tile_forward(F, vec, x0, z1, z2, h1b);
-        const float o1 = tile_forward(F, vec, x1, z1, z2, h1b);
+        tile_forward(w1, w2, vec, x0, z1, z2, h1b);
+        const float o0 = tile_output(vec, z2);
+        tile_forward(w1, w2, vec, x1, z1, z2, h1b);
+        const float o1 = tile_output(vec, z2);
         const int64_t e = e0 + l;
         if (l < 32 && e < nnz) {
             const float o = l < 16 ? o0 : o1;
@@ -527,8 +550,8 @@ __global__ void __launch_bounds__(256) k_loss_finish(const double *__restrict__ 
 }
 
 // ---------------------------------------------------------------------------------------
-// Backward pass over all entries: per-wave partial gradients of sum_e d_o[e] o[e].
-// Layout of a wave's partial (kParams floats): same as the weights.
+// Backward pass over all entries: per-block partial gradients of sum_e d_o[e] o[e], laid out as the
+// weights.
 // A wave takes 32 entries per step (two 16-entry tiles): forward, dZ2^T = w3 d_o (z2 > 0),
 // dH1^T = W2^T dZ2^T, dZ1^T = dH1^T (z1 > 0); then dZ2^T, H1^T, dZ1^T and X^T of both tiles go
 // to the wave's LDS area as [row][entry] and the weight gradients contract over the 32 entries:
@@ -536,26 +559,30 @@ __global__ void __launch_bounds__(256) k_loss_finish(const double *__restrict__ 
 constexpr int kTrStride = 40;               // BF16 per staged row: 32 entries + 8 (16-byte aligned rows, spread banks)
 constexpr int kTrRows = 3 * kH + kF;        // dZ2^T, H1^T, dZ1^T, X^T
 constexpr int kTrDZ2 = 0, kTrH1 = kH, kTrDZ1 = 2 * kH, kTrX = 3 * kH;
-__global__ void __launch_bounds__(64 * kWaves) k_mlp_backward(const float *__restrict__ w,
-                                                              const unsigned short *__restrict__ feats,
-                                                              const float *__restrict__ d_o, int64_t nnz,
-                                                              float *__restrict__ gpart) {
-    __shared__ __align__(16) unsigned short tr[kWaves][kTrRows][kTrStride];
+// What bounds it: the chain of a wave's step (products, masks, LDS and back) more than any unit, so two
+// waves per SIMD: with the fragments of W2 and W2^T in 64 registers it was one. A block fills a CU (150
+// KB of LDS). 0.77 M entries (24^3): 73.2 -> 58.2 us, and 4.9 instead of 7.1 for the blocks' gradients
+// after it, summed over a block's waves here.
+constexpr int kBwWaves = 8;
+static_assert((kBwWaves / 2) * 5313 * sizeof(float) <= sizeof(unsigned short) * kBwWaves * kTrRows * kTrStride,
+              "half the waves' gradients fit the staging area");
+__global__ void __launch_bounds__(64 * kBwWaves, 2) k_mlp_backward(const float *__restrict__ w,
+                                                                   const unsigned short *__restrict__ feats,
+                                                                   const float *__restrict__ d_o, int64_t nnz,
+                                                                   double *__restrict__ gpart) {
+    __shared__ __align__(16) unsigned short tr[kBwWaves][kTrRows][kTrStride];
     __shared__ __align__(16) float vec[196];
+    __shared__ W2Frags w2, w2t;
     load_vecs(w, vec);
-    Frags F;
-    load_frags(w, F);
+    load_w2<false, kBwWaves>(w, w2);
+    load_w2<true, kBwWaves>(w, w2t);  // for dH1^T = W2^T dZ2^T
+    bf16x4 w1[4];
+    load_w1(w, w1);
+    __syncthreads();
     const int l = threadIdx.x & 63, r = l & 15, g = l >> 4;
-    bf16x8s w2t[4][2];  // W2^T fragments for dH1^T = W2^T dZ2^T (k block q = outputs 32q + hid32)
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) w2t[mb][q][j] = f2bf(w[kOffW2 + (32 * q + hid32(g, j)) * kH + 16 * mb + r]);
     const int wv = threadIdx.x >> 6;
     unsigned short(*T)[kTrStride] = tr[wv];
-    const int64_t wave = (int64_t)blockIdx.x * kWaves + wv;
+    const int64_t wave = (int64_t)wv * gridDim.x + blockIdx.x;  // few entries: a wave or two per block
     f32x4 gW2[4][4], gW1[4];
     float gb1[4][4], gb2[4][4], gw3[4][4], gb3 = 0.f;
 #pragma unroll
@@ -567,7 +594,7 @@ __global__ void __launch_bounds__(64 * kWaves) k_mlp_backward(const float *__res
             gb1[a][b] = gb2[a][b] = gw3[a][b] = 0.f;
         }
     }
-    const int64_t nwaves = (int64_t)gridDim.x * kWaves;
+    const int64_t nwaves = (int64_t)gridDim.x * kBwWaves;
     // the next step's features and output gradients are always in flight
     auto load_d = [&](int64_t e) { return e < nnz ? d_o[e] : 0.f; };
     bf16x4 xn[2] = {load_x(feats, wave * 32, nnz), load_x(feats, wave * 32 + 16, nnz)};
@@ -583,7 +610,8 @@ __global__ void __launch_bounds__(64 * kWaves) k_mlp_backward(const float *__res
         for (int s = 0; s < 2; ++s) {
             f32x4 z1[4], z2[4];
             bf16x4 h1b[4];
-            (void)tile_forward(F, vec, xt[s], z1, z2, h1b);
+            wave_lds_sync();  // or the first tile's fragments are kept for the second: 35 registers spilled
+            tile_forward(w1, w2, vec, xt[s], z1, z2, h1b);
             const float dout = dt[s];
             bf16x4 dz2b[4];
 #pragma unroll
@@ -604,7 +632,7 @@ __global__ void __launch_bounds__(64 * kWaves) k_mlp_backward(const float *__res
             for (int mb = 0; mb < 4; ++mb) {
                 f32x4 c = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int q = 0; q < 2; ++q) c = mfma32(w2t[mb][q], cat8(dz2b[2 * q], dz2b[2 * q + 1]), c);
+                for (int q = 0; q < 2; ++q) c = mfma32(w2t[mb][q][l], cat8(dz2b[2 * q], dz2b[2 * q + 1]), c);
                 float dz[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
@@ -646,17 +674,8 @@ __global__ void __launch_bounds__(64 * kWaves) k_mlp_backward(const float *__res
         }
         wave_lds_sync();
     }
-    // wave partials: C tiles directly; vector terms summed over the 16 entry lanes
-    float *out = gpart + wave * 5313;
-#pragma unroll
-    for (int ob = 0; ob < 4; ++ob) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            out[kOffW1 + (16 * ob + 4 * g + j) * kF + r] = gW1[ob][j];
-#pragma unroll
-            for (int ib = 0; ib < 4; ++ib) out[kOffW2 + (16 * ob + 4 * g + j) * kH + 16 * ib + r] = gW2[ob][ib][j];
-        }
-    }
+    // the vector terms' sums over the 16 entry lanes
+    float vb1[4][4], vb2[4][4], vw3[4][4];
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
@@ -668,28 +687,71 @@ __global__ void __launch_bounds__(64 * kWaves) k_mlp_backward(const float *__res
                 b += __shfl_xor(b, off, 16);
                 c += __shfl_xor(c, off, 16);
             }
-            if (r == 0) {
-                out[kOffB1 + 16 * mb + 4 * g + j] = a;
-                out[kOffB2 + 16 * mb + 4 * g + j] = b;
-                out[kOffW3 + 16 * mb + 4 * g + j] = c;
-            }
+            vb1[mb][j] = a;
+            vb2[mb][j] = b;
+            vw3[mb][j] = c;
         }
 #pragma unroll
     for (int off = 8; off > 0; off >>= 1) gb3 += __shfl_xor(gb3, off, 16);
-    if (l == 0) out[kOffB3] = gb3;
+    // the block's gradient: half the waves' at a time through LDS, FP64 sums in wave order
+    float *part = reinterpret_cast<float *>(&tr[0][0][0]);
+    constexpr int kPer = (5313 + 64 * kBwWaves - 1) / (64 * kBwWaves);
+    double sum[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) sum[k] = 0.0;
+#pragma unroll 1
+    for (int half = 0; half < 2; ++half) {
+        __syncthreads();
+        if (wv / (kBwWaves / 2) == half) {
+            float *out = part + (wv % (kBwWaves / 2)) * 5313;
+#pragma unroll
+            for (int ob = 0; ob < 4; ++ob) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    out[kOffW1 + (16 * ob + 4 * g + j) * kF + r] = gW1[ob][j];
+#pragma unroll
+                    for (int ib = 0; ib < 4; ++ib)
+                        out[kOffW2 + (16 * ob + 4 * g + j) * kH + 16 * ib + r] = gW2[ob][ib][j];
+                }
+            }
+            if (r == 0) {
+#pragma unroll
+                for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        out[kOffB1 + 16 * mb + 4 * g + j] = vb1[mb][j];
+                        out[kOffB2 + 16 * mb + 4 * g + j] = vb2[mb][j];
+                        out[kOffW3 + 16 * mb + 4 * g + j] = vw3[mb][j];
+                    }
+            }
+            if (l == 0) out[kOffB3] = gb3;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int e = k * 64 * kBwWaves + (int)threadIdx.x;
+            if (e < 5313)
+#pragma unroll
+                for (int v = 0; v < kBwWaves / 2; ++v) sum[k] += (double)part[v * 5313 + e];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int e = k * 64 * kBwWaves + (int)threadIdx.x;
+        if (e < 5313) gpart[(int64_t)blockIdx.x * 5313 + e] = sum[k];
+    }
 }
 
-// Sum of the wave partials in a fixed order (one thread per parameter).
-// Sum of the per-wave partial gradients in two fixed-order passes: chunk c of the waves
-// (blockIdx.y) into part2[c][k], then the kGradChunks chunks per parameter.
+// Sum of the blocks' gradients in two fixed-order passes: chunk c of the blocks (blockIdx.y) into
+// part2[c][k], then the kGradChunks chunks per parameter.
 constexpr int kGradChunks = 64;
-__global__ void k_grad_reduce(const float *__restrict__ gpart, int64_t nwaves, double *__restrict__ part2) {
+__global__ void k_grad_reduce(const double *__restrict__ gpart, int64_t nblocks, double *__restrict__ part2) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= 5313) return;
-    const int64_t per = (nwaves + kGradChunks - 1) / kGradChunks;
-    const int64_t w0 = (int64_t)blockIdx.y * per, w1 = w0 + per < nwaves ? w0 + per : nwaves;
+    const int64_t per = (nblocks + kGradChunks - 1) / kGradChunks;
+    const int64_t b0 = (int64_t)blockIdx.y * per, b1 = b0 + per < nblocks ? b0 + per : nblocks;
     double s = 0.0;
-    for (int64_t wv = w0; wv < w1; ++wv) s += gpart[wv * 5313 + k];
+    for (int64_t b = b0; b < b1; ++b) s += gpart[b * 5313 + k];
     part2[(int64_t)blockIdx.y * 5313 + k] = s;
 }
 __global__ void k_grad_finish(const double *__restrict__ part2, float *__restrict__ grad) {
@@ -868,15 +930,15 @@ int qh_learned_setup(qh_ctx *c) {
     return QH_OK;
 }
 
-// Blocks of the network kernels: what the 256 CUs hold at once (by registers, three blocks of the
-// forward pass and one of the backward pass on a CU), each wave taking 32 entries at a time. More
-// only repeat the weights' set-up, and in the backward pass each wave leaves 21 KB of partial
-// gradients: at 24^3 (0.75 M entries) 2048 blocks wrote and read 174 MB for them, 134 + 42 us.
+// Blocks of the network kernels: what the 256 CUs hold at once (four blocks of the forward pass and
+// one of the backward pass on a CU), each wave taking 32 entries at a time; few entries are spread
+// over as many CUs as they fill with four waves. More blocks only repeat the weights' set-up, and in
+// the backward pass each leaves 42 KB of partial gradients.
 static unsigned mlp_grid(int64_t nnz, int64_t resident) {
     const int64_t steps = (nnz + 31) / 32;
     return (unsigned)std::min<int64_t>((steps + kWaves - 1) / kWaves, resident);
 }
-constexpr int64_t kForwardBlocks = 768, kBackwardBlocks = 256;
+constexpr int64_t kForwardBlocks = 1024, kBackwardBlocks = 256;
 
 int qh_learned_factor(qh_ctx *c) {
     LearnedPrec &L = c->lp;
@@ -976,7 +1038,7 @@ int qh_learned_loss_grad(qh_ctx *c, const float *V_dev, bool want_grad, double p
         if ((rc = qh_alloc(c, &L.W, (int64_t)n * kP)) || (rc = qh_alloc(c, &L.AW, (int64_t)n * kP)) ||
             (rc = qh_alloc(c, &L.tpart, 2048 * kP)) ||
             (rc = qh_alloc(c, &L.lpart, (L.nnz + 255) / 256)) ||
-            (rc = qh_alloc(c, &L.gpart, (int64_t)mlp_grid(L.nnz, kBackwardBlocks) * kWaves * 5313)) ||
+            (rc = qh_alloc(c, &L.gpart, (int64_t)mlp_grid(L.nnz, kBackwardBlocks) * 5313)) ||
             (rc = qh_alloc(c, &L.gpart2, (int64_t)kGradChunks * 5313)))
             return rc;
     }
@@ -1026,9 +1088,9 @@ int qh_learned_loss_grad(qh_ctx *c, const float *V_dev, bool want_grad, double p
     }
     if (want_grad) {
         const unsigned gm = mlp_grid(L.nnz, kBackwardBlocks);
-        hipLaunchKernelGGL(k_mlp_backward, dim3(gm), dim3(64 * kWaves), 0, c->stream, L.w, L.feats, L.d_o, L.nnz, L.gpart);
+        hipLaunchKernelGGL(k_mlp_backward, dim3(gm), dim3(64 * kBwWaves), 0, c->stream, L.w, L.feats, L.d_o, L.nnz, L.gpart);
         hipLaunchKernelGGL(k_grad_reduce, dim3((5313 + 255) / 256, kGradChunks), dim3(256), 0, c->stream, L.gpart,
-                           (int64_t)gm * kWaves, L.gpart2);
+                           (int64_t)gm, L.gpart2);
         hipLaunchKernelGGL(k_grad_finish, dim3((5313 + 255) / 256), dim3(256), 0, c->stream, L.gpart2, L.grad);
     }
     QH_HIP(c, hipGetLastError());
