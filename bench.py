@@ -76,25 +76,32 @@ def phase_bytes(mi, n_particles: int, crossings: float, n_occ: int) -> int:
     return 56 * n_particles + 160 * n_occ + 160 * crossings + 16 * (mi.n_edges + mi.n_nodes)
 
 
+def factor_pass_bytes(mi):
+    """Entries of G or of G^T: one 32-bit word of BF16 value and 16-bit column (a 32-bit column
+    beside it in slices without), and a column base per 64."""
+    return 4 * mi.nnz_factor + 4 * (2 * mi.nnz_factor - mi.nnz_factor_c16) // 2 + mi.nnz_factor // 16
+
+
 def algorithmic_bytes(kernel: str, mi, n_particles: int, crossings: float, learned: bool = False,
                       mixed: bool = False, n_species: int = 1):
     """Bytes one launch must move at least (each datum read or written once). mixed: the inner
     iterations of the mixed-precision edge solve (FP32 matrix values and vectors)."""
     v = 4 if mixed else 8   # bytes per vector entry (and per value of A) in the edge iterations
     if kernel in ("cg_spmv",):
-        # A: value + column (2 bytes in tiles read with 16-bit offsets, else 4); rowptr;
-        # z, p_old, q_old in; p_new, q out
+        # A: value + column (2 bytes in slices read with 16-bit columns, else 4), a column base per
+        # 64 entries; z, p_old, q_old in; p_new, q out
         n, nnz, c16 = mi.n_int_edges, mi.nnz_edge, mi.nnz_edge_c16
-        return v * nnz + 2 * c16 + 4 * (nnz - c16) + 4 * (n + 1) + 5 * v * n
+        return v * nnz + 2 * c16 + 4 * (nnz - c16) + nnz // 16 + 5 * v * n
     if kernel in ("node_spmv",):
         n, nnz = mi.n_int_nodes, mi.nnz_node
-        return 12 * nnz + 4 * (n + 1) + 32 * n
+        return 10 * nnz + nnz // 16 + 32 * n
     if kernel == "node_update":
         return 64 * mi.n_int_nodes
     if kernel == "cg_update":
         n = mi.n_int_edges
         if learned:
-            return 6 * v * n                             # x, r rw; p, q in (z comes from the factor)
+            # x, r, y = G r rw; p, q in; and the product G q (its entries as in precond)
+            return factor_pass_bytes(mi) + 8 * v * n
         return 8 * v * n                                 # x, r rw; p, q, dinv in; z out
     if kernel == "particle_step":
         # one launch per species: particle state in+out (28 B each way), per tet: geometry 48 +
@@ -105,11 +112,8 @@ def algorithmic_bytes(kernel: str, mi, n_particles: int, crossings: float, learn
                     + 152 * crossings)
         return per_step / n_species
     if kernel == "precond":
-        # z = G^T (G r): two CSR passes over the lower factor and its transpose (BF16 value,
-        # column of 2 or 4 bytes as in cg_spmv); per row: r in, y out, y in, z out, r in (dot),
-        # row pointers
-        n, nnz_l, c16 = mi.n_int_edges, mi.nnz_factor, mi.nnz_factor_c16
-        return 4 * nnz_l + 2 * c16 + 4 * (2 * nnz_l - c16) + 5 * v * n + 8 * (n + 1)
+        # z = G^T y (y = G r is kept by the update): y in, z out
+        return factor_pass_bytes(mi) + 2 * v * mi.n_int_edges
     if kernel == "field_prep":
         return (48 + 24 + 16 + 48) * mi.n_tets + 8 * mi.n_edges + 8 * mi.n_faces
     return None
@@ -117,20 +121,24 @@ def algorithmic_bytes(kernel: str, mi, n_particles: int, crossings: float, learn
 
 # HIP kernels behind each timed entry (one entry may launch several kernels)
 HIP_KERNELS = {"particle_step": ["k_particle_step<false>", "k_mail_apply", "k_gather<2, 8>"],
-               "edge_rhs": ["k_edge_rhs_e", "k_edge_rhs_b"], "field_prep": ["k_field_prep"]}
+               "field_prep": ["k_field_prep"]}
 
 
-def hip_kernels(entry: str, mixed: bool = False, learned: bool = False):
+def hip_kernels(entry: str, mi, mixed: bool = False, learned: bool = False):
     """HIP kernels behind a timed entry; the edge iterations' kernels are instantiated on FP64
-    vectors, or FP32 in the mixed-precision solve, and the update computes z = D^-1 r only with
-    Jacobi."""
+    vectors, or FP32 in the mixed-precision solve, and on the entries they keep in flight (more in
+    matrices of at most 2048 slices of 64 rows). With the learned preconditioner the update also
+    forms G q."""
     t = "float" if mixed else "double"
+    small = mi.n_int_edges <= 2048 * 64
     if entry == "cg_spmv":
-        return [f"k_cg_spmv<{t}, {t}>"]
+        return [f"k_cg_spmv<{t}, {t}, {20 if small else 10 if mixed else 8}>"]
     if entry == "cg_update":
-        return [f"k_cg_update<{'false' if learned else 'true'}, {t}>"]
+        return [f"k_cg_update_g<{t}, {16 if small else 8}>" if learned else f"k_cg_update<{t}>"]
     if entry == "precond":
-        return [f"k_prec_g<false, {t}>", f"k_prec_g<true, {t}>"]
+        return [f"k_prec_g<false, {16 if small else 8}, {t}>"]
+    if entry == "edge_rhs":
+        return [f"k_edge_rhs_{k}<{20 if small else 8}>" for k in "eb"]
     return HIP_KERNELS.get(entry, [])
 
 
@@ -589,7 +597,7 @@ def main():
         n_work = its if k in ("cg_spmv", "cg_update", "precond") and its else kern[k]["launches"]
         avg_s = kern[k]["ms_total"] / n_work * 1e-3
         ach = by / avg_s / 1e9
-        hk = hip_kernels(k, r["solver"] == "mixed", r["precond"] == "learned")
+        hk = hip_kernels(k, mi, r["solver"] == "mixed", r["precond"] == "learned")
         return {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": measured_traffic(k, args.workload, hk), "kernel": k,
                 "hip_kernels": hk, "algorithmic_bytes_per_launch": int(by),
