@@ -369,7 +369,8 @@ __global__ void __launch_bounds__(kThreads) k_cg_update(int32_t n, XT *__restric
 // y -= alpha G q, so the pass gathers q, which needs no alpha, and r.z of the new iterate is y.y.
 // (y is formed anew from r wherever r is: at the start and at every reliable update.) Against an
 // update and a product of their own this saves a launch and its chain of loads per iteration, and
-// the entries are in flight beside the sums: 64^3, FP32: 10.9 + 24.2 -> 29.8 us.
+// the entries are in flight beside the sums: 64^3, FP32: 10.9 + 24.2 -> 29.8 us (24.9 with
+// the present rounds of loads).
 // Partials: y.y and r.r of the stored values.
 template <typename XT, int U>
 __global__ void __launch_bounds__(kThreads) k_cg_update_g(int32_t n, int32_t ns, const SellCols S,
@@ -813,7 +814,8 @@ __global__ void k_renumber(int64_t n, const int32_t *__restrict__ idx, const dou
 //   rhs_i += dt u_b sum_f (C^T [*mu^-1])_if b_f                          (k_edge_rhs_b)
 // The second takes its rows in interior-edge order (pos: their place in rhs): face fluxes are kept
 // by face number, a dozen per node, and the edges of one node share most of them. Rows in device
-// numbering would gather 96 bytes apart (48^3: 93 us for both passes in one kernel, 86 us so).
+// numbering would gather 96 bytes apart (48^3: 93 us for both passes in one kernel, 86 us so; 83
+// with the present rounds of loads).
 template <int U>
 __global__ void __launch_bounds__(kThreads) k_edge_rhs_e(int32_t n, int32_t ns, const SellCols S,
                                                          const double *__restrict__ mval,
@@ -851,7 +853,7 @@ __global__ void __launch_bounds__(kThreads) k_edge_rhs_b(int32_t n, int32_t ns, 
 // the tolerance stays above the FP64 rounding floor when the charge is small against E.
 // Rows are few and long (about 50 entries: every edge of the tets around the node), so the eight
 // waves of a block share each slice, a part of its entries each: one wave per slice left most of
-// the chip idle behind seven dependent rounds of loads (25^3: 16.1 us a launch).
+// the chip idle behind seven dependent rounds of loads (25^3: 16.1 us a launch, 5.4 so).
 __global__ void __launch_bounds__(kThreads) k_gauss_rhs(int32_t n, int32_t ns, const SellCols S,
                                                         const double *__restrict__ val,
                                                         const double *__restrict__ e,
