@@ -61,12 +61,12 @@ int upload(qh_ctx *c, T **dst, const T *src, size_t n) {
 int upload_sell_values(qh_ctx *c, DevSell &d, const HostCsr &h, const int32_t *rows, const int32_t *cpos) {
     SellHost sh;
     qh_build_sell((int32_t)h.nrow, h.ptr.data(), h.col.data(), rows, cpos, sh);
-    int rc = qh_upload_sell(c, d, sh);
-    if (rc) return rc;
     std::vector<double> v(sh.src.size(), 0.0);
     for (size_t i = 0; i < sh.src.size(); ++i)
         if (sh.src[i] >= 0) v[i] = h.val[sh.src[i]];
-    if ((rc = upload(c, &d.val, v.data(), v.size()))) return rc;
+    sh.src.clear();  // the values stay: the device needs no map from the CSR entries
+    int rc = qh_upload_sell(c, d, sh);
+    if (rc || (rc = upload(c, &d.val, v.data(), v.size()))) return rc;
     QH_HIP(c, hipStreamSynchronize(c->stream));
     return QH_OK;
 }
@@ -254,11 +254,11 @@ int qh_upload_sell(qh_ctx *c, DevSell &d, const SellHost &h) {
     d.n = h.n;
     d.ns = h.ns;
     d.width = h.width;
-    d.len = (int64_t)h.src.size();
-    const size_t len = h.src.size();
+    const size_t len = h.c16.size();
+    d.len = (int64_t)len;
     int rc;
     if ((rc = upload(c, &d.off, h.off.data(), h.off.size())) || (rc = upload(c, &d.base, h.base.data(), h.base.size())) ||
-        (rc = upload(c, &d.src, h.src.data(), len)) || (rc = qh_alloc(c, &d.c16, len)))
+        (!h.src.empty() && (rc = upload(c, &d.src, h.src.data(), len))) || (rc = qh_alloc(c, &d.c16, len)))
         return rc;
     QH_HIP(c, hipMemcpyAsync(d.c16, h.c16.data(), sizeof(uint16_t) * len, hipMemcpyHostToDevice, c->stream));
     if (h.wide) {
