@@ -1411,10 +1411,12 @@ int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, 
         const int stopped = H->flags[0];
         const double bb = H->bb, thr2 = H->thr2;
         rr0 = H->rr0;
-        if (update == 0 && (stopped == CG_NONFINITE || rr0 <= thr2) && H->flags[1] == 0 && !(rr0 > thr2 && rr0 < INFINITY)) {
-            // the start decided: r0 meets the target, or is not finite
+        // the start decided: r0 is not finite (an overflowing ||b||^2 makes its target infinite too),
+        // or meets its target
+        const bool finite0 = rr0 <= 1.7976931348623157e308;
+        if (update == 0 && (!finite0 || rr0 <= thr2)) {
             out.res = bb > 0 ? sqrt(rr0 / bb) : 0.0;
-            flag = rr0 <= thr2 ? CG_CONVERGED : CG_NONFINITE;
+            flag = finite0 ? CG_CONVERGED : CG_NONFINITE;
             break;
         }
         k = stopped ? H->flags[1] : k + batch;
