@@ -1164,7 +1164,7 @@ int qh_pic_step(qh_ctx *c, const qh_step_params_t *P, int32_t n_steps, qh_step_s
                 if (c->cgn.last_iters[0] == 0) {
                     QH_HIP(c, hipStreamSynchronize(c->stream));
                     const double thr2 = H->gauss[0], rr = H->gauss[2];
-                    correct = !(rr <= thr2);
+                    correct = !(rr <= thr2 && rr <= 1.7976931348623157e308);  // inf is no target met
                     sn.converged = sn.true_ok = !correct;
                     sn.res = rr > 0 ? 1.0 : 0.0;
                 }
