@@ -37,6 +37,15 @@ enum { CG_RUNNING = 0, CG_CONVERGED = 1, CG_STALLED = 2, CG_NONFINITE = 3 };
 // stall rule of the learned solve: r.z <= 0, or ||r|| not 10 % lower than ten iterations before
 constexpr int kStallWindow = 10;
 constexpr double kStallRatio2 = 0.81;  // (1 - 0.1)^2 on r.r
+// FP32 recurrence of the mixed-precision solve: the iterations between two reliable updates end, on the
+// device, where r.r has fallen by this much since the last one. Batches are laid out for 1e-8 (1e-4 of
+// the residual); far past that the vectors' rounding is what is left of r, and the recurrence no longer
+// converges (a constant right-hand side, node system of 33^3 to 1e-12, its last 77 iterations in one
+// segment: 20,000 iterations and a Jacobi restart; 141 so, 101 in FP64). Iterations of a point source on
+// the node system of 32^3 to 1e-12 (FP64 102) with 1e-10 / 1e-9 / 1e-8: 226 / 163 / 142; with 1e-8 a
+// step of the benchmark's kind stops just before its second update and takes a third (48^3, learned: 1961 / 1930
+// / 2081 us).
+constexpr double kSegment2 = 1e-9;
 
 // Consecutive vector entries per thread in the element-wise kernels: 16 bytes.
 template <typename T>
@@ -187,7 +196,8 @@ __device__ __forceinline__ int cg_state(double rr, double rz, double thr2, int s
 // one block: totals of the init partials; threshold; convergence flag. mixed: the FP32 recurrence's
 // start, from ||r0||^2 and ||b||^2 in scal[S_RES]: its target on the scaled residual is
 // (0.9 tol ||b|| / ||r0||)^2, a little below the FP64 target, which the reliable update then usually
-// confirms at once; nothing is iterated if r0 meets the FP64 target or is not finite.
+// confirms at once, or the end of the first segment (kSegment2); nothing is iterated if r0 meets the FP64
+// target or is not finite.
 __global__ void __launch_bounds__(kThreads) k_cg_start(const double *__restrict__ part, int m,
                                                        const double *__restrict__ rz_part, int m_rz, double *scal,
                                                        int32_t *flags, double tol2, const double *abs_thr2, int stall,
@@ -203,7 +213,7 @@ __global__ void __launch_bounds__(kThreads) k_cg_start(const double *__restrict_
             rr0 = scal[S_RES];
             bb = scal[S_RES + 1];
             target = tol2 * bb;
-            thr2 = 0.81 * target / rr0;
+            thr2 = fmax(0.81 * target / rr0, kSegment2);
             state = cg_state(rr0, 1.0, target, 0, 0, nullptr);
             if (!state) state = cg_state(rr, rz, thr2, stall, 0, nullptr);
         } else {
@@ -487,14 +497,14 @@ __global__ void k_refine(int32_t n, double *__restrict__ x, float *__restrict__ 
 // Reliable update, second half (after r = b - A x in FP64): the recurrence's residual replaced by
 // r32 = r / s, with Jacobi z = D^-1 r32, and the partials of r.z (Jacobi) and r.r written where
 // the update kernel writes them, so the iteration continues with the next product (its beta
-// from the new r.z), and the stop flag is cleared. The stall rule's history of r.r goes on: the
+// from the new r.z), the stop flag is cleared and thr2 is the next segment's target. The stall rule's history of r.r goes on: the
 // replaced residual differs from the recurrence's by its FP32 drift only, far below the rule's
 // 10 % over ten iterations while the solve converges, and a stalled solve stays stalled.
 template <bool JAC>
 __global__ void __launch_bounds__(kThreads) k_replace(int32_t n, const double *__restrict__ r, double *scal,
                                                       float *__restrict__ r32, float *__restrict__ z32,
                                                       const float *__restrict__ dinv32, double *__restrict__ part,
-                                                      int32_t *flags) {
+                                                      int32_t *flags, double thr2) {
     const double inv = 1.0 / scal[S_SCALE];
     double acc[2] = {0.0, 0.0};
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
@@ -507,7 +517,10 @@ __global__ void __launch_bounds__(kThreads) k_replace(int32_t n, const double *_
         }
         acc[1] += (double)ri * (double)ri;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) flags[0] = CG_RUNNING;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        flags[0] = CG_RUNNING;
+        scal[S_THR2] = thr2;
+    }
     write_partials<2>(acc, part);
 }
 
@@ -1316,7 +1329,9 @@ int qh_cg_alloc32(qh_ctx *c, CgWork &w, int32_t n) {
 // a remainder of at most an eighth of a segment), where the FP64 residual usually meets the
 // target already (the recurrence aims a little lower), so a step of the benchmark takes two
 // reliable updates. Without a history, a first batch of check_every iterations, then what this
-// solve's own rate gives for the segment or for the rest, whichever is less. The host reads once per update: the verdict
+// solve's own rate gives for the segment or for the rest, whichever is less (iterations_ahead). These are
+// estimates: the device ends a segment that has reduced the residual by 3e-5 (kSegment2), which takes less
+// than the batch where the residual falls faster than before. The host reads once per update: the verdict
 // of the batch and the recomputed residual. A batch that meets non-finite values is not applied
 // (flag 3); one stopped by the stall rule is applied and the solve returns (flag 2).
 int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, int check_every,
@@ -1375,7 +1390,7 @@ int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, 
     const int seg = w.last_segment[learned ? 1 : 0];    // its iterations per 1e-4 of reduction
     int m_up = (int)ge;  // blocks that left the last partials of r.r
     int k = 0, flag = CG_RUNNING, batch_next = check_every;
-    double rr0 = 0.0, rr = 0.0;
+    double rr0 = 0.0, rr = 0.0, rr_last = 0.0;
     for (int update = 0;; ++update) {
         // a batch: to the next segment end, at most to the last solve's iteration count (from
         // the second segment on, a last remainder of at most an eighth of a segment joins the
@@ -1433,6 +1448,7 @@ int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, 
             flag = finite0 ? CG_CONVERGED : CG_NONFINITE;
             break;
         }
+        const int k_last = k;
         k = stopped ? H->flags[1] : k + batch;
         if (stopped == CG_NONFINITE) {
             flag = CG_NONFINITE;  // the batch is not applied: x keeps the last reliable update
@@ -1440,6 +1456,7 @@ int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, 
             break;
         }
         out.refinements = update + 1;
+        rr_last = update == 0 ? rr0 : rr;
         rr = H->res[0];
         out.res = bb > 0 ? sqrt(rr / bb) : 0.0;
         if (rr == rr && rr <= thr2) {
@@ -1455,12 +1472,12 @@ int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, 
             break;
         }
         if (k >= max_it) break;
-        const int per = iterations_for(rr0, rr, k, 1e-8), rest = iterations_for(rr0, rr, k, 0.81 * thr2 / rr);
-        batch_next = std::max(check_every, std::min(per, rest));
+        batch_next = std::max(check_every, iterations_ahead(rr0, k, rr_last, k - k_last, rr, std::max(1e-8, 0.81 * thr2 / rr)));
         // the recurrence continues from the FP64 residual
         int tq = qh_tbeg(c);
         hipLaunchKernelGGL((learned ? k_replace<false> : k_replace<true>), dim3(ge), dim3(kThreads), 0, c->stream, n,
-                           (const double *)w.r, w.scal, w.r32, w.z32, (const float *)w.dinv32, upart, w.flags);
+                           (const double *)w.r, w.scal, w.r32, w.z32, (const float *)w.dinv32, upart, w.flags,
+                           std::max(0.81 * thr2, kSegment2 * rr) / rr0);
         m_up = (int)ge;
         if (learned) QH_HIP(c, launch_prec_apply32(c, w.r32, w.z32, ppart));
         qh_tend(c, tq, QK_CG_INIT);

@@ -39,3 +39,25 @@ def test_fp64_solve_launches_what_it_needs(system, n, mult, kind):
         ctx.timing(False)
         assert st["res"] <= tol and st["iters"] <= launched <= 3 * st["iters"] + 8, (launched, st)
     ctx.close()
+
+
+# the same in mixed precision: a segment between reliable updates reduces the residual by 3e-5 at most
+# (FP32 vectors hold no more), so a slow start followed by a fast end takes about the FP64 solve's
+# iterations; twice as many would be a recurrence that has lost its directions
+@pytest.mark.parametrize("kind", ["constant", "point", "noise"])
+@pytest.mark.parametrize("system,n,mult", [("node", 20, 10.0), ("node", 33, 10.0), ("edge", 14, 40.0)])
+def test_mixed_solve_keeps_its_segments(system, n, mult, kind):
+    import paper_2103_06737_amd as qh
+    ctx = gpu_context(qi.BoxMesh(n), mult * 7.68e-10 / n)
+    node = system == "node"
+    M = ctx.matrix(5 if node else 0)
+    rhs, which = _rhs(kind, M), qh.SYS_NODE if node else qh.SYS_EDGE
+    for tol in (1e-8, 1e-12):
+        _, ref = ctx.field_solve(which, rhs, tol=tol, max_it=20000)
+        ctx.timing(True)
+        x, st = ctx.field_solve(which, rhs, tol=tol, max_it=20000, solver=qh.SOLVER_MIXED)
+        launched = ctx.timing_read()["cg_spmv"][1]
+        ctx.timing(False)
+        assert st["res"] <= tol and st["fallback"] == 0 and st["iters"] <= 2 * ref["iters"], (st, ref)
+        assert launched <= 3 * st["iters"] + 8, (launched, st)
+    ctx.close()
