@@ -1400,7 +1400,7 @@ int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, 
             target = std::min((update + 1) * seg, prev);
             if (update > 0 && prev - target <= seg / 8) target = prev;
         }
-        const int batch = std::min(target > k ? target - k : batch_next, max_it - k);
+        const int batch = std::max(0, std::min(target > k ? target - k : batch_next, max_it - k));
         for (int kk = k; kk < k + batch; ++kk) {
             const int par = kk & 1;
             int ta = qh_tbeg(c);

@@ -61,3 +61,18 @@ def test_mixed_solve_keeps_its_segments(system, n, mult, kind):
         assert st["res"] <= tol and st["fallback"] == 0 and st["iters"] <= 2 * ref["iters"], (st, ref)
         assert launched <= 3 * st["iters"] + 8, (launched, st)
     ctx.close()
+
+
+def test_step_with_no_iterations_allowed():
+    """A cap of zero or below: no iteration, whichever solver and size, and none is counted."""
+    import paper_2103_06737_amd as qh
+    for n in (4, 12):
+        ctx = gpu_context(qi.BoxMesh(n), 10 * 7.68e-10 / n)
+        mi = ctx.mesh_info()
+        ctx.fields_init_synthetic(qi.white(mi.n_edges, 0, 3), qi.white(mi.n_edges, 0, 5), 1e2, 0.1, 0.0)
+        for sv in (qh.SOLVER_FP64, qh.SOLVER_MIXED):
+            for cap in (0, -5):
+                p = ctx.step_params(field_mode=qh.FIELDS_SOLVE, solver=sv, gauss=0, max_it_edge=cap)
+                st = ctx.pic_step(p, 1, allow=(qh.QH_ENOTCONV,))[0]
+                assert st["edge_iters"] == 0, (n, sv, cap, st["edge_iters"])
+        ctx.close()
