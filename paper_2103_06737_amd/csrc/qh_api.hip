@@ -105,24 +105,26 @@ int ensure_assembled(qh_ctx *c) {
     }
     if (!c->assembled) {
         qh_assemble(c->hm, c->phys.eps0, c->phys.mu0, c->hA, c->hCMb, c->hGtM, c->hK);
-        // A: val2 = [*eps], A_S = S, val = [*eps] + tau S (device)
+        // A: val2 = [*eps], A_S = S (CSR); both and [*eps] +- tau S on the slices
         const HostMesh &m = c->hm;
         c->A.n = (int32_t)c->hA.nrow;
         c->A.nnz = (int64_t)c->hA.col.size();
         if ((rc = upload(c, &c->A.ptr, c->hA.ptr.data(), c->hA.ptr.size())) ||
             (rc = upload(c, &c->A.col, c->hA.col.data(), c->hA.col.size())) ||
             (rc = upload(c, &c->A.val2, c->hA.val.data(), c->hA.val.size())) ||
-            (rc = upload(c, &c->A_S, c->hA.val2.data(), c->hA.val2.size())) ||
-            (rc = qh_alloc(c, &c->A.val, c->A.nnz)))
+            (rc = upload(c, &c->A_S, c->hA.val2.data(), c->hA.val2.size())))
             return rc;
         {
             SellHost sh;
             qh_build_sell(c->A.n, c->hA.ptr.data(), c->hA.col.data(), m.order.data(), m.pos_of.data(), sh);
             c->nnz_edge_c16 = sh.nnz_c16;
             if ((rc = qh_upload_sell(c, c->As, sh)) || (rc = qh_alloc(c, &c->As.val, (size_t)c->As.len)) ||
-                (rc = qh_alloc(c, &c->A_rhs, (size_t)c->As.len)))
+                (rc = qh_alloc(c, &c->A_rhs, (size_t)c->As.len)) || (rc = qh_alloc(c, &c->As_eps, (size_t)c->As.len)) ||
+                (rc = qh_alloc(c, &c->As_S, (size_t)c->As.len)))
                 return rc;
+            QH_HIP(c, launch_A_to_slices(c));
             QH_HIP(c, hipStreamSynchronize(c->stream));
+            qh_release(c, c->As.src);  // the map has done its work
         }
         if ((rc = upload_sell_values(c, c->CMb, c->hCMb, nullptr, nullptr)) ||
             (rc = upload_sell_values(c, c->GtM, c->hGtM, nullptr, m.pos_of.data())) ||

@@ -232,12 +232,14 @@ struct qh_ctx {
     unsigned int *mail_cnt = nullptr;            // per mailbox (run of kMailTets tets): records posted
     int32_t *mail = nullptr;                     // mailboxes: ceil(Nt / kMailTets) x kMailCap x kMailWords int32
 
-    // A in CSR, interior-edge numbering (training, energy): val = [*eps] + tau S, val2 = [*eps];
+    // A in CSR, interior-edge numbering: val = [*eps] + tau S (training; allocated and filled by
+    // qh_learned_setup), val2 = [*eps] (energy);
     // the products of the field update on slices, edge unknowns in device numbering
     DevCsr A;
     DevSell As, CMb, GtM, K;
     int64_t nnz_edge_c16 = 0;  // entries of A with 16-bit columns (without padding)
     double *A_S = nullptr;  // S values on the pattern of A
+    double *As_eps = nullptr, *As_S = nullptr;  // [*eps] and S on the slices of A
     double *A_rhs = nullptr;  // [*eps] - tau S on the slices of A (right-hand side)
     double tau_assembled = -1.0;
     int32_t last_refinements = 0;  // the last step's reliable updates (mixed-precision edge solve)
@@ -436,7 +438,11 @@ int qh_learned_probes(qh_ctx *c, float *V_dev, uint64_t seed);
 // back (idx = pos_of)
 hipError_t launch_renumber(qh_ctx *c, int64_t n, const int32_t *idx, const double *in, double *out);
 hipError_t launch_diag_inv(qh_ctx *c, const DevSell &M, double *dinv);
+// [*eps] and S on the slices of A from their CSR values; A and the right-hand side's matrix on the slices
+// for tau; A's CSR values for tau
+hipError_t launch_A_to_slices(qh_ctx *c);
 hipError_t launch_assemble_A(qh_ctx *c, double tau);
+hipError_t launch_assemble_A_csr(qh_ctx *c, double tau);
 hipError_t launch_edge_rhs(qh_ctx *c);
 hipError_t launch_wave_rhs(qh_ctx *c);
 hipError_t launch_plane_wave(qh_ctx *c, bool wave);

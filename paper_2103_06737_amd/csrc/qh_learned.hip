@@ -862,7 +862,9 @@ int qh_learned_setup(qh_ctx *c) {
         }
         L.built = true;
     }
-    // features and scales depend on dt
+    // features, scales and A's CSR values (training) depend on dt
+    if (!c->A.val && (rc = qh_alloc(c, &c->A.val, c->A.nnz))) return rc;
+    QH_HIP(c, launch_assemble_A_csr(c, tau));
     const int64_t nnz = L.nnz;
     std::vector<double> dA(n), dM(n), dS(n), off(n, 0.0), rl(n);
     for (int32_t i = 0; i < n; ++i) {

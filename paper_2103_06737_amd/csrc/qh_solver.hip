@@ -803,15 +803,21 @@ __global__ void k_axpy_vals(int64_t n, const double *__restrict__ a, const doubl
     if (i < n) out[i] = a[i] + tau * s[i];
 }
 
-// A = [*eps] + tau S and the right-hand-side matrix [*eps] - tau S on the slices (src: CSR entry,
-// -1: padding)
-__global__ void k_axpy_slices(int64_t len, const int32_t *__restrict__ src, const double *__restrict__ a,
-                              const double *__restrict__ s, double tau, double *__restrict__ out,
-                              double *__restrict__ out_m) {
+// CSR values on slices (src: CSR entry, -1: padding)
+__global__ void k_to_slices(int64_t len, const int32_t *__restrict__ src, const double *__restrict__ a,
+                            double *__restrict__ out) {
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < len) out[i] = src[i] >= 0 ? a[src[i]] : 0.0;
+}
+
+// A = [*eps] + tau S and the right-hand-side matrix [*eps] - tau S on the slices, from both there: a
+// change of dt streams four arrays of A's size. (From the CSR values through src instead, every lane
+// another row, and the CSR copy of A filled beside them: 395 + 121 us at 64^3.)
+__global__ void k_axpy_slices(int64_t len, const double *__restrict__ a, const double *__restrict__ s, double tau,
+                              double *__restrict__ out, double *__restrict__ out_m) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= len) return;
-    const int32_t e = src[i];
-    const double ae = e >= 0 ? a[e] : 0.0, se = e >= 0 ? s[e] : 0.0;
+    const double ae = a[i], se = s[i];
     out[i] = ae + tau * se;
     out_m[i] = ae - tau * se;
 }
@@ -1495,13 +1501,28 @@ int qh_cg_solve_mixed(qh_ctx *c, DevSell &M, CgWork &w, double tol, int max_it, 
     return QH_OK;
 }
 
+hipError_t launch_A_to_slices(qh_ctx *c) {
+    const int64_t len = c->As.len;
+    if (len == 0) return hipSuccess;
+    const dim3 grid((unsigned)((len + 255) / 256));
+    hipLaunchKernelGGL(k_to_slices, grid, dim3(256), 0, c->stream, len, c->As.src, c->A.val2, c->As_eps);
+    hipLaunchKernelGGL(k_to_slices, grid, dim3(256), 0, c->stream, len, c->As.src, c->A_S, c->As_S);
+    return hipGetLastError();
+}
+
 hipError_t launch_assemble_A(qh_ctx *c, double tau) {
-    int64_t nnz = c->A.nnz, len = c->As.len;
+    const int64_t len = c->As.len;
+    if (len == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_axpy_slices, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, c->stream, len, c->As_eps,
+                       c->As_S, tau, c->As.val, c->A_rhs);
+    return hipGetLastError();
+}
+
+hipError_t launch_assemble_A_csr(qh_ctx *c, double tau) {
+    const int64_t nnz = c->A.nnz;
     if (nnz == 0) return hipSuccess;
     hipLaunchKernelGGL(k_axpy_vals, dim3((unsigned)((nnz + 255) / 256)), dim3(256), 0, c->stream, nnz, c->A.val2,
                        c->A_S, tau, c->A.val);
-    hipLaunchKernelGGL(k_axpy_slices, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, c->stream, len, c->As.src,
-                       c->A.val2, c->A_S, tau, c->As.val, c->A_rhs);
     return hipGetLastError();
 }
 
