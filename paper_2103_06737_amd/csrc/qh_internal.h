@@ -50,6 +50,7 @@ struct HostMesh {
     // device numbering of the edge unknowns (qh_sell.h): position -> interior index and back, and
     // position -> global edge
     std::vector<int32_t> order, pos_of, dev_edges;
+    bool in_space = false;                      // order follows a space-filling curve, not the node numbers
     std::vector<double> grad;                   // 12*Nt: grad lambda_0..3
     std::vector<double> vol;                    // Nt
     std::vector<double> cen;                    // 3*Nt

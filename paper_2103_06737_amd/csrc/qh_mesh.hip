@@ -25,6 +25,139 @@ inline int local_edge(int i, int j) {
     return tab[i][j];
 }
 
+// Device numbering of the edge unknowns (HostMesh::order), in groups of kGroup nodes.
+constexpr int32_t kGroup = 256;
+
+// By an edge's rank among the edges whose lower node is theirs, then by that node: on meshes numbered line
+// by line those of one rank are edges of one direction at consecutive nodes.
+std::vector<int32_t> order_by_rank(const HostMesh &m) {
+    const size_t n = m.int_edges.size();
+    std::vector<int32_t> rank(m.Ne, 0), order(n);
+    for (int64_t e = 1; e < m.Ne; ++e) rank[e] = m.edges[2 * e] == m.edges[2 * e - 2] ? rank[e - 1] + 1 : 0;
+    auto group = [&](size_t i) { return m.edges[2 * (int64_t)m.int_edges[i]] / kGroup; };
+    std::iota(order.begin(), order.end(), 0);
+    for (size_t i0 = 0, i1; i0 < n; i0 = i1) {
+        for (i1 = i0 + 1; i1 < n && group(i1) == group(i0);) ++i1;
+        std::stable_sort(order.begin() + i0, order.begin() + i1,
+                         [&](int32_t a, int32_t b) { return rank[m.int_edges[a]] < rank[m.int_edges[b]]; });
+    }
+    return order;
+}
+
+// The nodes along a space-filling (Morton) curve instead of by number, and in a group of them the edges with
+// the most tets first (their rows are the longest: three entries per tet), then along the curve.
+std::vector<int32_t> order_in_space(const HostMesh &m) {
+    double lo[3], inv[3];
+    for (int d = 0; d < 3; ++d) {
+        double a = INFINITY, b = -INFINITY;
+        for (int64_t v = 0; v < m.Nn; ++v) {
+            a = std::min(a, m.xyz[3 * v + d]);
+            b = std::max(b, m.xyz[3 * v + d]);
+        }
+        lo[d] = a;
+        inv[d] = b > a ? 2097151.0 / (b - a) : 0.0;
+    }
+    std::vector<std::pair<uint64_t, int32_t>> key(m.Nn);
+    for (int64_t v = 0; v < m.Nn; ++v) {
+        uint64_t k = 0;
+        for (int d = 0; d < 3; ++d) {  // 21 bits of each coordinate, every third bit of the key
+            uint64_t q = std::min<uint64_t>((uint64_t)((m.xyz[3 * v + d] - lo[d]) * inv[d]), 2097151);
+            q = (q | q << 32) & 0x1f00000000ffffull;
+            q = (q | q << 16) & 0x1f0000ff0000ffull;
+            q = (q | q << 8) & 0x100f00f00f00f00full;
+            q = (q | q << 4) & 0x10c30c30c30c30c3ull;
+            q = (q | q << 2) & 0x1249249249249249ull;
+            k |= q << d;
+        }
+        key[v] = {k, (int32_t)v};
+    }
+    std::sort(key.begin(), key.end());
+    std::vector<int32_t> at(m.Nn);
+    for (int64_t p = 0; p < m.Nn; ++p) at[key[p].second] = (int32_t)p;
+    struct Item {
+        int32_t group, tets, lo, hi, i;
+    };
+    std::vector<Item> item(m.int_edges.size());
+    for (size_t i = 0; i < item.size(); ++i) {
+        const int64_t e = m.int_edges[i];
+        const int32_t a = at[m.edges[2 * e]], b = at[m.edges[2 * e + 1]];
+        item[i] = {std::min(a, b) / kGroup, m.e2t_ptr[e + 1] - m.e2t_ptr[e], std::min(a, b), std::max(a, b), (int32_t)i};
+    }
+    std::sort(item.begin(), item.end(), [](const Item &a, const Item &b) {
+        if (a.group != b.group) return a.group < b.group;
+        if (a.tets != b.tets) return a.tets > b.tets;
+        return a.lo != b.lo ? a.lo < b.lo : a.hi < b.hi;
+    });
+    std::vector<int32_t> order(item.size());
+    for (size_t i = 0; i < order.size(); ++i) order[i] = item[i].i;
+    return order;
+}
+
+std::vector<int32_t> inverse(const std::vector<int32_t> &order) {
+    std::vector<int32_t> pos(order.size());
+    for (size_t p = 0; p < order.size(); ++p) pos[order[p]] = (int32_t)p;
+    return pos;
+}
+
+// What a numbering costs the products with the edge matrix: 128-byte lines that the gathers of a slice touch,
+// per matrix entry, over a sample of slices (k-th entries of 64 rows side by side; a row shorter than the
+// longest gathers its last column again).
+double lines_per_entry(const HostMesh &m, const std::vector<int32_t> &order, const std::vector<int32_t> &pos) {
+    constexpr int32_t kSample = 128;
+    const int32_t n = (int32_t)order.size(), ns = n / kSlice;
+    int64_t lines = 0, entries = 0;
+    std::vector<int32_t> col[kSlice], at;
+    for (int32_t q = 0; q < std::min(ns, kSample); ++q) {
+        const int32_t s = (int32_t)((int64_t)q * ns / std::min(ns, kSample));
+        size_t w = 0;
+        for (int l = 0; l < kSlice; ++l) {
+            const int32_t e = m.int_edges[order[s * kSlice + l]];
+            col[l].clear();
+            for (int32_t j = m.e2t_ptr[e]; j < m.e2t_ptr[e + 1]; ++j)
+                for (int k = 0; k < 6; ++k) {
+                    const int32_t i = m.int_edge_of[m.te[6 * (int64_t)(m.e2t[j] >> 3) + k]];
+                    if (i >= 0) col[l].push_back(pos[i]);
+                }
+            std::sort(col[l].begin(), col[l].end());
+            col[l].erase(std::unique(col[l].begin(), col[l].end()), col[l].end());
+            w = std::max(w, col[l].size());
+            entries += (int64_t)col[l].size();
+        }
+        for (size_t k = 0; k < w; ++k) {
+            at.clear();
+            for (int l = 0; l < kSlice; ++l) at.push_back(col[l][std::min(k, col[l].size() - 1)] / 16);
+            std::sort(at.begin(), at.end());
+            lines += std::unique(at.begin(), at.end()) - at.begin();
+        }
+    }
+    return entries > 0 ? (double)lines / (double)entries : 0.0;
+}
+
+// By rank, unless the mesh's numbering makes that a bad order: on the repository's boxes and cylinders it
+// touches 0.10 to 0.29 lines per entry; on boxes numbered at random 0.86 to 1.09 against 0.26 along the curve,
+// on Delaunay meshes of points in random order or in slabs 1.0 to 1.7 against 0.44 to 0.50. A learned
+// mixed-precision solve to 1e-8 on a 48^3 box numbered at random took 11.2 ms by rank, 4.4 along the curve (the
+// tiled products before the slices: 6.3); FP64 Jacobi on 100,000 points in random order 27.1 -> 11.1 (16.7).
+// Up to 2048 unknowns a solve keeps its vectors in LDS, whatever their order.
+void number_unknowns(HostMesh &m) {
+    constexpr double kLinesByRank = 0.4;
+    m.order = order_by_rank(m);
+    m.pos_of = inverse(m.order);
+    if (m.order.size() > 2048) {
+        const double by_rank = lines_per_entry(m, m.order, m.pos_of);
+        if (by_rank > kLinesByRank) {
+            std::vector<int32_t> order = order_in_space(m), pos = inverse(order);
+            if (lines_per_entry(m, order, pos) < by_rank) {
+                m.order.swap(order);
+                m.pos_of.swap(pos);
+                m.in_space = true;
+            }
+        }
+    }
+    m.dev_edges.resize(m.order.size());
+    for (size_t p = 0; p < m.order.size(); ++p) m.dev_edges[p] = m.int_edges[m.order[p]];
+}
+
 }  // namespace
 
 std::string qh_build_mesh(HostMesh &m, int64_t Nn, const double *xyz, int64_t Nt,
@@ -206,29 +339,7 @@ std::string qh_build_mesh(HostMesh &m, int64_t Nn, const double *xyz, int64_t Nt
             m.n2e[cur[m.edges[2 * e + 1]]++] = (int32_t)(e + 1);
         }
     }
-    // Device numbering of the edge unknowns: in groups of 256 nodes, by their rank among the edges
-    // whose lower node is theirs, then by that node. On meshes numbered line by line those of one
-    // rank are edges of one direction at consecutive nodes.
-    {
-        constexpr int32_t kGroup = 256;
-        const size_t n = m.int_edges.size();
-        std::vector<int32_t> rank(m.Ne, 0);
-        for (int64_t e = 1; e < m.Ne; ++e) rank[e] = m.edges[2 * e] == m.edges[2 * e - 2] ? rank[e - 1] + 1 : 0;
-        auto group = [&](size_t i) { return m.edges[2 * (int64_t)m.int_edges[i]] / kGroup; };
-        m.order.resize(n);
-        std::iota(m.order.begin(), m.order.end(), 0);
-        for (size_t i0 = 0, i1; i0 < n; i0 = i1) {
-            for (i1 = i0 + 1; i1 < n && group(i1) == group(i0);) ++i1;
-            std::stable_sort(m.order.begin() + i0, m.order.begin() + i1,
-                             [&](int32_t a, int32_t b) { return rank[m.int_edges[a]] < rank[m.int_edges[b]]; });
-        }
-        m.pos_of.resize(n);
-        m.dev_edges.resize(n);
-        for (size_t p = 0; p < n; ++p) {
-            m.pos_of[m.order[p]] = (int32_t)p;
-            m.dev_edges[p] = m.int_edges[m.order[p]];
-        }
-    }
+    number_unknowns(m);
     return "";
 }
 
@@ -444,7 +555,7 @@ namespace {
 // mesh boundary lacks some of its neighbours' entries; beside theirs, the others of its entries keep
 // the columns of a slot close together.
 template <typename D, typename T>
-void place_row(int32_t cnt, int32_t fw, D &&d, T &&t, std::vector<int32_t> &slots) {
+void place_row(int32_t cnt, int32_t fw, D &&d, T &&t, std::vector<int32_t> &slots, std::vector<int64_t> &cost) {
     slots.resize(cnt);
     if (cnt == fw || cnt == 0) {
         for (int32_t k = 0; k < cnt; ++k) slots[k] = k;
@@ -452,7 +563,7 @@ void place_row(int32_t cnt, int32_t fw, D &&d, T &&t, std::vector<int32_t> &slot
     }
     // cost[k][i]: entries 0..k placed, entry k in slot k + i (i <= gap) at the latest
     const int32_t gap = fw - cnt;
-    std::vector<int64_t> cost((size_t)cnt * (gap + 1));
+    cost.resize((size_t)cnt * (gap + 1));
     for (int32_t k = 0; k < cnt; ++k)
         for (int32_t i = 0; i <= gap; ++i) {
             const int64_t here = std::abs((int64_t)d(k) - t(k + i)) + (k > 0 ? cost[(size_t)(k - 1) * (gap + 1) + i] : 0);
@@ -469,7 +580,7 @@ void place_row(int32_t cnt, int32_t fw, D &&d, T &&t, std::vector<int32_t> &slot
 }  // namespace
 
 void qh_build_sell(int32_t n, const int32_t *ptr, const int32_t *col, const int32_t *rows, const int32_t *cpos,
-                   SellHost &o) {
+                   SellHost &o, bool wide) {
     constexpr int32_t kSpan = 1 << 16;
     o = SellHost();
     o.n = n;
@@ -498,6 +609,7 @@ void qh_build_sell(int32_t n, const int32_t *ptr, const int32_t *col, const int3
     o.c16.assign(len, 0);
     o.base.assign((size_t)std::max(o.off[o.ns], 1), -1);
     std::vector<int32_t> slots, lo, hi;
+    std::vector<int64_t> cost;
     for (int32_t s = 0; s < o.ns; ++s) {
         const size_t e0 = (size_t)o.off[s] * kSlice;
         const int32_t w = o.off[s + 1] - o.off[s];
@@ -521,7 +633,7 @@ void qh_build_sell(int32_t n, const int32_t *ptr, const int32_t *col, const int3
             const int32_t j0 = r < 0 ? 0 : ptr[r], cnt = r < 0 ? 0 : ptr[r + 1] - ptr[r];
             place_row(
                 cnt, fw, [&](int32_t k) { return column(j0 + k) - l; },
-                [&](int32_t k) { return column(f0 + k) - full; }, slots);
+                [&](int32_t k) { return column(f0 + k) - full; }, slots, cost);
             for (int32_t k = 0; k < cnt; ++k) {
                 const size_t e = e0 + (size_t)slots[k] * kSlice + l;
                 o.src[e] = j0 + k;
@@ -554,7 +666,7 @@ void qh_build_sell(int32_t n, const int32_t *ptr, const int32_t *col, const int3
                 hi[k] = std::max(hi[k], best);
             }
         }
-        bool fits = true;
+        bool fits = !wide;
         for (int32_t k = 0; k < w; ++k) fits = fits && (int64_t)hi[k] - lo[k] < kSpan;
         if (!fits) {
             o.wide = true;

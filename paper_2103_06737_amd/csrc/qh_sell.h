@@ -6,7 +6,8 @@
 // side by side (shorter rows padded with zero values on columns of their own), so a wave reads a
 // slice's values and columns coalesced, sums each row in its lane's registers and needs neither LDS
 // nor a block barrier. The edge unknowns are numbered on the device so that the 64 rows of a slice
-// are edges of one kind at consecutive nodes (HostMesh::order): the k-th entries of a slice then
+// are edges of one kind at consecutive nodes, or neighbours in space on meshes whose nodes are not numbered
+// line by line (HostMesh::order): the k-th entries of a slice then
 // gather from a few runs of neighbouring vector entries. What bounds the products is the gathers'
 // misses in the first-level cache; the entries of a tile of rows in storage order (products in LDS,
 // then one thread per row) touched about 25 cache lines per 64 gathers, these slices about 4 on
@@ -32,9 +33,9 @@ constexpr int kSellOneWidth = 2048;            // matrices of at most this many 
 constexpr int kSellMaxBlocks = 1024;           // 8192 waves: what the 256 CUs hold at eight waves per SIMD
 
 // Slices of a CSR matrix. rows: matrix row of each position (null: the same), cpos: gather index
-// of each column (null: the same). Row entries keep their order.
+// of each column (null: the same), wide: 32-bit columns throughout. Row entries keep their order.
 void qh_build_sell(int32_t n, const int32_t *ptr, const int32_t *col, const int32_t *rows, const int32_t *cpos,
-                   SellHost &out);
+                   SellHost &out, bool wide = false);
 
 // Sum over the wave's 64 lanes, the same in every lane: shifts within rows of 16, then across rows, as
 // data-parallel moves (a shuffle through LDS costs several times a move's latency, six in a chain:

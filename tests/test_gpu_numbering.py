@@ -1,0 +1,116 @@
+"""Meshes whose nodes are not numbered line by line: boxes numbered at random and Delaunay meshes of random
+points. Their edge unknowns follow a space-filling curve on the device; slices hold rows of many lengths, with
+16-bit and 32-bit columns side by side."""
+import numpy as np
+import pytest
+import scipy.sparse as sp
+
+import qh_inputs as qi
+
+from .gpu_setup import gpu_context
+
+pytestmark = pytest.mark.gpu
+
+
+def _scattered(n):
+    mesh = qi.BoxMesh(n, 1.0)
+    perm = np.random.default_rng(3).permutation(mesh.xyz.shape[0])
+    inv = np.empty_like(perm)
+    inv[perm] = np.arange(perm.size)
+    mesh.xyz, mesh.tets = mesh.xyz[perm], inv[mesh.tets].astype(np.int32)
+    return mesh
+
+
+class _Points:
+    def __init__(self, count):
+        from scipy.spatial import Delaunay
+        self.xyz = np.random.default_rng(1).random((count, 3))
+        self.tets = Delaunay(self.xyz).simplices.astype(np.int32)
+
+
+def test_a_random_numbering_is_replaced():
+    """146,692 unknowns of a 28^3 box: by the nodes' numbers the columns of a slice's entry scatter over all of
+    them, so hardly any slice has 16-bit columns; along the curve most have."""
+    ctx = gpu_context(_scattered(28), 1e-10)
+    mi = ctx.mesh_info()
+    assert mi.nnz_edge_c16 > mi.nnz_edge // 2
+    ctx.close()
+
+
+# 476 and 1273 unknowns (one launch: a slice per wave with rows of 28, more than the 20 kept in registers; two
+# slices per wave), 14,818 (232 slices), 146,692 (2293 slices of their own width, both column kinds)
+@pytest.mark.parametrize("kind,size,dt", [("points", 90, 2e-10), ("points", 200, 2e-10), ("points", 2000, 1e-10),
+                                          ("scattered", 28, 1e-10)])
+def test_solves_and_application(kind, size, dt):
+    import paper_2103_06737_amd as qh
+    ctx = gpu_context(_scattered(size) if kind == "scattered" else _Points(size), dt)
+    for system, which in ((qh.SYS_EDGE, 0), (qh.SYS_NODE, 5)):
+        A = ctx.matrix(which)
+        rhs = A @ np.random.default_rng(size).standard_normal(A.shape[0])
+        if system == qh.SYS_EDGE:
+            ctx.precond_train(steps=40, lr=3e-3, seed=1, validate_every=0)
+        for pc in (qh.PC_JACOBI, qh.PC_LEARNED) if system == qh.SYS_EDGE else (qh.PC_JACOBI,):
+            for solver in (qh.SOLVER_FP64, qh.SOLVER_MIXED):
+                x, st = ctx.field_solve(system, rhs, tol=1e-10, precond=pc, solver=solver)
+                # the matrix as downloaded: 1e-13 of the terms for its products' rounding
+                assert np.linalg.norm(A @ x - rhs) <= 1e-10 * np.linalg.norm(rhs) + 1e-13 * np.linalg.norm(abs(A) @ abs(x))
+    # z = G^T (G r) against the factor as returned, rounded to BF16: FP64 sums of at most 64 terms per row
+    gr, gc, gv = ctx.precond_factor()
+    u = gv.view(np.uint32).astype(np.uint64)
+    h = ((u + 0x7fff + ((u >> 16) & 1)) & 0xffff0000).astype(np.uint32).view(np.float32)
+    n = ctx.mesh_info().n_int_edges
+    G = sp.csr_matrix((h.astype(np.float64), (gr, gc)), shape=(n, n))
+    assert np.diff(G.indptr).max() <= 64 and np.diff(G.tocsc().indptr).max() <= 64
+    r = np.random.default_rng(size + 1).standard_normal(n)
+    z = ctx.precond_apply(r)
+    assert (abs(z - G.T @ (G @ r)) <= 128 * 2.0 ** -53 * (abs(G).T @ (abs(G) @ abs(r)))).all()
+    ctx.close()
+
+
+def test_cycle_against_the_oracle():
+    """Two full cycles on a 9^3 box numbered at random (4401 unknowns), then a saved state continued in the
+    wave update: fields against the oracle's update of the same deposits."""
+    import paper_2103_06737_amd as qh
+    from oracle.complex_ import Complex
+    from oracle.field import FieldOracle, init_fields
+    from oracle.whitney import Operators
+    mesh, u_b, dt = _scattered(9), 2.0 ** -56, 5 * 7.68e-10 / 9
+    u_q = qi.QE * 2.0 ** -40
+    cx = Complex(mesh.xyz, mesh.tets)
+    op = Operators(cx, qi.EPS0, qi.MU0)
+    fo = FieldOracle(cx, op, dt)
+    e, b = init_fields(cx, qi.white(cx.Ne, 0, 3), qi.white(cx.Ne, 0, 5), 1e2, 0.1, 0.0, u_b)
+    ctx = gpu_context(mesh, dt)
+    ctx.fields_upload(e, b)
+    rng = np.random.default_rng(2)
+    x = rng.uniform(0.05, 0.95, (2000, 3)).astype(np.float32)
+    sid = ctx.species_add(-qi.QE / qi.ME, -1)
+    ctx.particles_upload(sid, x, (1e6 * rng.standard_normal((2000, 3))).astype(np.float32))
+    zero = np.zeros(cx.Nn, np.int64)
+    for solver in (qh.SOLVER_FP64, qh.SOLVER_MIXED):
+        st = ctx.pic_step(ctx.step_params(field_mode=qh.FIELDS_SOLVE, verify=1, tol_edge=1e-10, tol_node=1e-10,
+                                          solver=solver))[0]
+        assert st["continuity_bad"] == 0 and st["divb_bad"] == 0
+        g, Q = ctx.deposits_download()
+        eo, bo, _ = fo.step(e, b, u_b, g, u_q, Q, zero, tol=1e-13, tol_n=1e-13)
+        e, b = ctx.fields_download()
+        assert np.linalg.norm(e - eo) <= 1e-8 * np.linalg.norm(eo)
+        rhs, sol = ctx.edge_system_download()
+        A = ctx.matrix(0)
+        assert np.linalg.norm(A @ sol - rhs) <= 1.01e-10 * np.linalg.norm(rhs)
+    w_e, _ = ctx.fields_energy()
+    M = ctx.matrix(1)
+    ei = e[cx.int_edges]
+    assert abs(w_e - 0.5 * ei @ (M @ ei)) <= 1e-12 * w_e
+    # the wave update's history goes through a saved state in interior-edge order
+    wave = ctx.step_params(field_mode=qh.FIELDS_WAVE, tol_edge=1e-10, tol_node=1e-10)
+    ctx.pic_step(wave)
+    blob = ctx.state_save()
+    ctx.pic_step(wave)
+    other = gpu_context(mesh, dt)
+    other.species_add(-qi.QE / qi.ME, -1)
+    other.state_load(blob)
+    other.pic_step(wave)
+    assert all(np.array_equal(p, q) for p, q in zip(ctx.fields_download(), other.fields_download()))
+    ctx.close()
+    other.close()
