@@ -71,6 +71,30 @@ int upload_sell_values(qh_ctx *c, DevSell &d, const HostCsr &h, const int32_t *r
     return QH_OK;
 }
 
+// Whether 64 consecutive rows have columns 2^16 apart beside each other, in most of a sample of slices.
+bool columns_far_apart(const HostCsr &h) {
+    const int64_t ns = h.nrow / kSlice, sample = std::min<int64_t>(ns, 32);
+    int64_t far = 0;
+    for (int64_t q = 0; q < sample; ++q) {
+        const int64_t r0 = q * ns / sample * kSlice;
+        std::vector<int32_t> lo, hi;
+        for (int64_t r = r0; r < r0 + kSlice; ++r)
+            for (int32_t j = h.ptr[r]; j < h.ptr[r + 1]; ++j) {
+                const size_t k = j - h.ptr[r];
+                if (k >= lo.size()) {
+                    lo.push_back(h.col[j]);
+                    hi.push_back(h.col[j]);
+                }
+                lo[k] = std::min(lo[k], h.col[j]);
+                hi[k] = std::max(hi[k], h.col[j]);
+            }
+        bool f = false;
+        for (size_t k = 0; k < lo.size(); ++k) f = f || hi[k] - lo[k] >= 1 << 16;
+        far += f;
+    }
+    return 2 * far > sample;
+}
+
 void free_all(qh_ctx *c) {
     for (void *p : c->allocations) (void)hipFree(p);
     c->allocations.clear();
@@ -131,7 +155,10 @@ int ensure_assembled(qh_ctx *c) {
             QH_HIP(c, hipStreamSynchronize(c->stream));
             qh_release(c, c->As.src);  // the map has done its work
         }
-        if ((rc = upload_sell_values(c, c->CMb, c->hCMb, nullptr, nullptr)) ||
+        // rows of C^T [*mu^-1] in interior-edge order, or in the device numbering (k_edge_rhs_b)
+        const bool by_device = m.in_space || columns_far_apart(c->hCMb);
+        c->CMb_pos = by_device ? nullptr : c->pos_of;
+        if ((rc = upload_sell_values(c, c->CMb, c->hCMb, by_device ? m.order.data() : nullptr, nullptr)) ||
             (rc = upload_sell_values(c, c->GtM, c->hGtM, nullptr, m.pos_of.data())) ||
             (rc = upload_sell_values(c, c->K, c->hK, nullptr, nullptr)))
             return rc;

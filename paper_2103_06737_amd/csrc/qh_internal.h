@@ -238,6 +238,7 @@ struct qh_ctx {
     // the products of the field update on slices, edge unknowns in device numbering
     DevCsr A;
     DevSell As, CMb, GtM, K;
+    const int32_t *CMb_pos = nullptr;  // position of the unknown that a row of CMb belongs to (null: the row's own)
     int64_t nnz_edge_c16 = 0;  // entries of A with 16-bit columns (without padding)
     double *A_S = nullptr;  // S values on the pattern of A
     double *As_eps = nullptr, *As_S = nullptr;  // [*eps] and S on the slices of A

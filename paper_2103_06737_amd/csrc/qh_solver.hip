@@ -833,8 +833,9 @@ __global__ void k_renumber(int64_t n, const int32_t *__restrict__ idx, const dou
 //   rhs_i += dt u_b sum_f (C^T [*mu^-1])_if b_f                          (k_edge_rhs_b)
 // The second takes its rows in interior-edge order (pos: their place in rhs): face fluxes are kept
 // by face number, a dozen per node, and the edges of one node share most of them. Rows in device
-// numbering would gather 96 bytes apart (48^3: 93 us for both passes in one kernel, 86 us so; 83
-// with the present rounds of loads).
+// numbering gather 96 bytes apart (both passes, us: 48^3 75.9 against 74.4, 64^3 195 against 187), but they are
+// taken (pos null) where interior-edge order has no 16-bit columns, as of 74^3 (96^3: 601 against 630),
+// and where the device numbering follows a curve in space (48^3 numbered at random: 87.5 against 129).
 template <int U>
 __global__ void __launch_bounds__(kThreads) k_edge_rhs_e(int32_t n, int32_t ns, const SellCols S,
                                                          const double *__restrict__ mval,
@@ -860,7 +861,7 @@ __global__ void __launch_bounds__(kThreads) k_edge_rhs_b(int32_t n, int32_t ns, 
         const int32_t row = s * kSlice + (int32_t)(threadIdx.x & 63);
         const double t = sell_dot<U>(S, cval, b, s);
         if (row < n) {
-            double *d = rhs + pos[row];
+            double *d = rhs + (pos ? pos[row] : row);
             *d += dtub * t;
         }
     }
@@ -1531,7 +1532,7 @@ hipError_t launch_edge_rhs(qh_ctx *c) {
     hipLaunchKernelGGL((A.width > 0 ? k_edge_rhs_e<kUAll> : k_edge_rhs_e<kU64>), dim3(sell_grid(A.ns)), dim3(kThreads), 0,
                        c->stream, A.n, A.ns, A.cols(), c->A_rhs, c->cge.x, c->g, c->int_edges, c->phys.u_q, c->cge.b);
     hipLaunchKernelGGL((C.width > 0 ? k_edge_rhs_b<kUAll> : k_edge_rhs_b<kU64>), dim3(sell_grid(C.ns)), dim3(kThreads), 0,
-                       c->stream, C.n, C.ns, C.cols(), C.val, c->b, c->phys.dt * c->phys.u_b, c->pos_of, c->cge.b);
+                       c->stream, C.n, C.ns, C.cols(), C.val, c->b, c->phys.dt * c->phys.u_b, c->CMb_pos, c->cge.b);
     return hipGetLastError();
 }
 

@@ -114,3 +114,31 @@ def test_cycle_against_the_oracle():
     assert all(np.array_equal(p, q) for p, q in zip(ctx.fields_download(), other.fields_download()))
     ctx.close()
     other.close()
+
+
+@pytest.mark.parametrize("kind", ["slab", "box", "scattered"])
+def test_edge_right_hand_side(kind):
+    """rhs = ([*eps] - tau S) e + dt C^T [*mu^-1] b - u_q g where the rows of C^T [*mu^-1] are in interior-edge
+    order (box) and in the device numbering (a slab of 76 x 76 x 2 cells, whose planes are 2^16 faces apart; a
+    numbering at random)."""
+    import paper_2103_06737_amd as qh
+    if kind == "slab":
+        mesh = qi.BoxMesh(76)
+        mesh.xyz, mesh.tets = mesh.xyz[:3 * 77 * 77], mesh.tets[:12 * 76 * 76]
+    else:
+        mesh = qi.BoxMesh(12) if kind == "box" else _scattered(12)
+    u_b, dt = 2.0 ** -56, 1e-11
+    ctx = gpu_context(mesh, dt)
+    mi = ctx.mesh_info()
+    ctx.fields_init_synthetic(qi.white(mi.n_edges, 0, 3), qi.white(mi.n_edges, 0, 5), 1e2, 0.1, 1e-3)
+    e0, b0 = ctx.fields_download()
+    ctx.pic_step(ctx.step_params(field_mode=qh.FIELDS_SOLVE), 1)
+    rhs, _ = ctx.edge_system_download()
+    M, S, C = ctx.matrix(1), ctx.matrix(2), ctx.matrix(3)
+    x = e0[~ctx.topology()["wall_edge"].astype(bool)]
+    tau = dt * dt / 4
+    ref = M @ x - tau * (S @ x) + dt * u_b * (C @ b0.astype(np.float64))
+    size = abs(M) @ abs(x) + tau * (abs(S) @ abs(x)) + dt * u_b * (abs(C) @ abs(b0.astype(np.float64)))
+    # sums of at most 64 terms and the rounding of b and of the combined entries
+    assert (abs(rhs - ref) <= 80 * 2.0 ** -53 * size).all()
+    ctx.close()
