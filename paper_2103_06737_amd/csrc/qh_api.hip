@@ -531,8 +531,13 @@ int qh_mesh_upload(qh_ctx *c, int64_t n_nodes, const double *xyz, int64_t n_tets
     if ((rc = upload(c, &c->order, m.order.data(), std::max<size_t>(1, m.order.size())))) return rc;
     if ((rc = upload(c, &c->pos_of, m.pos_of.data(), std::max<size_t>(1, m.pos_of.size())))) return rc;
     if ((rc = upload(c, &c->int_nodes, m.int_nodes.data(), std::max<size_t>(1, m.int_nodes.size())))) return rc;
-    if ((rc = upload(c, &c->int_node_of, m.int_node_of.data(), m.int_node_of.size()))) return rc;
-    if ((rc = upload(c, &c->edge_nodes, m.edges.data(), m.edges.size()))) return rc;
+    if ((rc = upload(c, &c->edge_of, m.int_edges.data(), std::max<size_t>(1, m.int_edges.size())))) return rc;
+    std::vector<int2> ends(std::max<size_t>(1, m.dev_edges.size()));  // until the synchronisation below
+    for (size_t p = 0; p < m.dev_edges.size(); ++p) {
+        const int64_t e = m.dev_edges[p];
+        ends[p] = make_int2(m.int_node_of[m.edges[2 * e]], m.int_node_of[m.edges[2 * e + 1]]);
+    }
+    if ((rc = upload(c, &c->edge_ends, ends.data(), ends.size()))) return rc;
     if ((rc = upload(c, &c->n2e_ptr, m.n2e_ptr.data(), m.n2e_ptr.size()))) return rc;
     if ((rc = upload(c, &c->n2e, m.n2e.data(), m.n2e.size()))) return rc;
     if ((rc = upload(c, &c->e2t_ptr, m.e2t_ptr.data(), m.e2t_ptr.size()))) return rc;

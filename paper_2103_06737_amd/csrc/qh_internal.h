@@ -224,8 +224,8 @@ struct qh_ctx {
     int32_t *order = nullptr;       // position of an edge unknown -> interior index
     int32_t *pos_of = nullptr;      // interior index of an edge unknown (as in the C ABI) -> position
     int32_t *int_nodes = nullptr;   // interior -> global node
-    int32_t *int_node_of = nullptr; // global node -> interior or -1
-    int32_t *edge_nodes = nullptr;  // 2*Ne
+    int32_t *edge_of = nullptr;     // interior index of an edge unknown -> global edge
+    int2 *edge_ends = nullptr;      // position of an edge unknown -> unknowns of its tail and head, -1: wall
     int32_t *n2e_ptr = nullptr, *n2e = nullptr;
     int32_t *e2t_ptr = nullptr, *e2t = nullptr;  // edge -> tet*8 + local edge
     int32_t *n2t_ptr = nullptr, *n2t = nullptr;  // node -> tet*8 + local vertex

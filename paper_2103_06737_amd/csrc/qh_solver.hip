@@ -938,41 +938,44 @@ __global__ void __launch_bounds__(kThreads) k_gauss_finish(const double *__restr
     }
 }
 
-// Item of this thread in kernels between the device numbering and arrays by edge: the blocks of an
-// XCD (which gets every eighth) take one contiguous span. The edges at 256 nodes are seven runs of
-// 256 by kind in the one order and interleaved in the other, so neighbouring blocks touch the same
-// lines of the other side: one L2 gathers or completes them (blocks in launch order and so: k_faraday_u
-// 43.0 and 21.1 us at 64^3, 19.6 and 11.5 at 48^3; k_gauss_apply 27.5 and 18.8, 13.5 and 9.8). Grids
-// (xcd_grid) are multiples of 8, or blocks share items.
+// Item of this thread in kernels that gather from another numbering than the one they run over: the
+// blocks of an XCD (which gets every eighth) take one contiguous span, since the edges at 256 nodes are
+// seven runs of 256 by kind in the device numbering and interleaved by edge number, so neighbouring blocks
+// gather the same lines and one L2 serves them. Grids (xcd_grid) are multiples of 8, or blocks share items.
 inline unsigned xcd_grid(int64_t n) { return (unsigned)(((n + 255) / 256 + 7) / 8 * 8); }
 __device__ __forceinline__ int32_t xcd_item() {
     const int32_t block = ((int32_t)blockIdx.x & 7) * ((int32_t)gridDim.x >> 3) + ((int32_t)blockIdx.x >> 3);
     return block * 256 + (int32_t)threadIdx.x;
 }
 
-// e_i += delta[head] - delta[tail] (wall nodes carry 0); keep: the uncorrected e (or null)
-__global__ void k_gauss_apply(int32_t n, const int32_t *__restrict__ int_edges,
-                              const int32_t *__restrict__ edge_nodes, const int32_t *__restrict__ int_node_of,
-                              const double *__restrict__ delta, double *__restrict__ e, double *__restrict__ keep) {
+// e_i += delta[head] - delta[tail] (wall nodes carry 0); keep: the uncorrected e (or null). ends: the edge's
+// tail and head among the unknown nodes, -1: wall (through the edge's number and its nodes' numbers, three
+// dependent gathers, 19.3 us at 64^3 and 60 at 96^3; now 12.8 and 39).
+__global__ void k_gauss_apply(int32_t n, const int2 *__restrict__ ends, const double *__restrict__ delta,
+                              double *__restrict__ e, double *__restrict__ keep) {
     const int32_t i = xcd_item();
     if (i >= n) return;
-    int32_t ge = int_edges[i];
-    int32_t a = int_node_of[edge_nodes[2 * ge]], b = int_node_of[edge_nodes[2 * ge + 1]];
-    double d = (b >= 0 ? delta[b] : 0.0) - (a >= 0 ? delta[a] : 0.0);
+    const int2 v = ends[i];
+    const double d = (v.y >= 0 ? delta[v.y] : 0.0) - (v.x >= 0 ? delta[v.x] : 0.0);
     const double ei = e[i];
     if (keep) keep[i] = ei;
     e[i] = ei + d;
 }
 
-// u = round((dt/2)(e_new + e_old)/u_b) per interior edge; e (global) <- e_new
-__global__ void k_faraday_u(int32_t n, const int32_t *__restrict__ int_edges, const double *__restrict__ enew,
-                            const double *__restrict__ eold, double half_dt_over_ub, int64_t *__restrict__ u,
-                            double *__restrict__ eglob) {
+// u = round((dt/2)(e_new + e_old)/u_b) per interior edge; e (global) <- e_new. edge_of: the edge of item i,
+// pos_of: its position (null: i). In edge order it gathers e and writes u in order (over the device numbering,
+// with scattered writes, 21.3 us at 64^3 and 61 at 96^3; so 14.5 and 39.5); where the device numbering follows
+// a curve in space the gathers are the worse (48^3 numbered at random, with k_faraday_b: 33.4 against 26.5),
+// and the items are the positions.
+__global__ void k_faraday_u(int32_t n, const int32_t *__restrict__ edge_of, const int32_t *__restrict__ pos_of,
+                            const double *__restrict__ enew, const double *__restrict__ eold, double half_dt_over_ub,
+                            int64_t *__restrict__ u, double *__restrict__ eglob) {
     const int32_t i = xcd_item();
     if (i >= n) return;
-    int32_t ge = int_edges[i];
-    u[ge] = (int64_t)llrint(half_dt_over_ub * (enew[i] + eold[i]));
-    eglob[ge] = enew[i];
+    const int32_t ge = edge_of[i], p = pos_of ? pos_of[i] : i;
+    const double en = enew[p];
+    u[ge] = (int64_t)llrint(half_dt_over_ub * (en + eold[p]));
+    eglob[ge] = en;
 }
 
 // b_f -= u_bc - u_ac + u_ab
@@ -1587,8 +1590,8 @@ hipError_t launch_div_e(qh_ctx *c, double *out3, double tol_n) {
 // e_int += G delta (interior edge values; delta on the unknown nodes)
 hipError_t launch_grad_add(qh_ctx *c, const double *delta, double *e_int) {
     int32_t n = c->A.n;
-    hipLaunchKernelGGL(k_gauss_apply, dim3(xcd_grid(n)), dim3(256), 0, c->stream, n, c->int_edges, c->edge_nodes,
-                       c->int_node_of, delta, e_int, (double *)nullptr);
+    hipLaunchKernelGGL(k_gauss_apply, dim3(xcd_grid(n)), dim3(256), 0, c->stream, n, c->edge_ends, delta, e_int,
+                       (double *)nullptr);
     return hipGetLastError();
 }
 
@@ -1597,15 +1600,16 @@ hipError_t launch_gauss_apply(qh_ctx *c, bool delta) {
     if (n == 0) return hipSuccess;
     if (!delta)
         return hipMemcpyAsync(c->e_star, c->cge.x, sizeof(double) * n, hipMemcpyDeviceToDevice, c->stream);
-    hipLaunchKernelGGL(k_gauss_apply, dim3(xcd_grid(n)), dim3(256), 0, c->stream, n, c->int_edges, c->edge_nodes,
-                       c->int_node_of, c->cgn.x, c->cge.x, c->e_star);
+    hipLaunchKernelGGL(k_gauss_apply, dim3(xcd_grid(n)), dim3(256), 0, c->stream, n, c->edge_ends, c->cgn.x,
+                       c->cge.x, c->e_star);
     return hipGetLastError();
 }
 
 hipError_t launch_faraday(qh_ctx *c) {
     int32_t n = c->A.n;
-    hipLaunchKernelGGL(k_faraday_u, dim3(xcd_grid(n)), dim3(256), 0, c->stream, n, c->int_edges, c->cge.x,
-                       c->e_old, 0.5 * c->phys.dt / c->phys.u_b, c->u_int, c->e);
+    const bool by_pos = c->hm.in_space;
+    hipLaunchKernelGGL(k_faraday_u, dim3(xcd_grid(n)), dim3(256), 0, c->stream, n, by_pos ? c->int_edges : c->edge_of,
+                       by_pos ? (const int32_t *)nullptr : c->pos_of, c->cge.x, c->e_old, 0.5 * c->phys.dt / c->phys.u_b, c->u_int, c->e);
     int64_t nf = c->hm.Nf;
     hipLaunchKernelGGL(k_faraday_b, dim3((unsigned)((nf + 255) / 256)), dim3(256), 0, c->stream, nf, c->face_edges,
                        c->u_int, c->b);
