@@ -561,15 +561,40 @@ constexpr int kTrRows = 3 * kH + kF;        // dZ2^T, H1^T, dZ1^T, X^T
 constexpr int kTrDZ2 = 0, kTrH1 = kH, kTrDZ1 = 2 * kH, kTrX = 3 * kH;
 // What bounds it: the chain of a wave's step (products, masks, LDS and back) more than any unit, so two
 // waves per SIMD: with the fragments of W2 and W2^T in 64 registers it was one. A block fills a CU (150
-// KB of LDS). 0.77 M entries (24^3): 73.2 -> 58.2 us, and 4.9 instead of 7.1 for the blocks' gradients
-// after it, summed over a block's waves here.
+// KB of LDS): 0.77 M entries (24^3) 73.2 -> 57.0 us, and 4.9 instead of 7.1 for the blocks' gradients after
+// it, summed over a block's waves here. That was 2048 waves after 8192, each summing four times as many steps
+// in FP32, which rounds 1.8 times as much; so a wave's sums go to FP64 after as many steps as those 8192 took
+// (backward_chain), 6 us each time: 75.0 us at 24^3, 41.9 at 16^3 (24.3 in one go), 237 at 40^3 (221).
 constexpr int kBwWaves = 8;
-static_assert((kBwWaves / 2) * 5313 * sizeof(float) <= sizeof(unsigned short) * kBwWaves * kTrRows * kTrStride,
+// A wave's FP32 gradient in the staging area: rows of W1 and W2 padded so that the four groups of lanes that
+// hold four rows apart write to different banks; the vectors behind their matrices as in the weights.
+constexpr int kSumRow1 = kF + 4, kSumRow2 = kH + 4, kSumB1 = kH * kSumRow1, kSumW2 = kSumB1 + kH;
+constexpr int kSumB2 = kSumW2 + kH * kSumRow2, kSumW3 = kSumB2 + kH, kSumB3 = kSumW3 + kH, kSumAll = kSumB3 + 4;
+static_assert((kBwWaves / 2) * kSumAll * sizeof(float) <= sizeof(unsigned short) * kBwWaves * kTrRows * kTrStride,
               "half the waves' gradients fit the staging area");
+constexpr int kGradRow = 5316;  // doubles per block in gpart: 16-byte aligned rows
+// where four weights from e on (a multiple of 4) stand there
+__device__ __forceinline__ int sum_at(int e) {
+    if (e < kOffB1) return e / kF * kSumRow1 + e % kF;
+    if (e < kOffW2) return kSumB1 + (e - kOffB1);
+    if (e < kOffB2) return kSumW2 + (e - kOffW2) / kH * kSumRow2 + (e - kOffW2) % kH;
+    return kSumB2 + (e - kOffB2);
+}
+// Sum over 16 lanes, the same in each: rotations within the row as data-parallel moves.
+template <int CTRL>
+__device__ __forceinline__ float row_move(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float row_sum(float v) {
+    v += row_move<0x128>(v);  // row_ror:8, 4, 2, 1
+    v += row_move<0x124>(v);
+    v += row_move<0x122>(v);
+    return v + row_move<0x121>(v);
+}
 __global__ void __launch_bounds__(64 * kBwWaves, 2) k_mlp_backward(const float *__restrict__ w,
                                                                    const unsigned short *__restrict__ feats,
                                                                    const float *__restrict__ d_o, int64_t nnz,
-                                                                   double *__restrict__ gpart) {
+                                                                   int64_t chain, double *__restrict__ gpart) {
     __shared__ __align__(16) unsigned short tr[kBwWaves][kTrRows][kTrStride];
     __shared__ __align__(16) float vec[196];
     __shared__ W2Frags w2, w2t;
@@ -580,165 +605,176 @@ __global__ void __launch_bounds__(64 * kBwWaves, 2) k_mlp_backward(const float *
     load_w1(w, w1);
     __syncthreads();
     const int l = threadIdx.x & 63, r = l & 15, g = l >> 4;
-    const int wv = threadIdx.x >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     unsigned short(*T)[kTrStride] = tr[wv];
     const int64_t wave = (int64_t)wv * gridDim.x + blockIdx.x;  // few entries: a wave or two per block
-    f32x4 gW2[4][4], gW1[4];
-    float gb1[4][4], gb2[4][4], gw3[4][4], gb3 = 0.f;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        gW1[a] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            gW2[a][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
-            gb1[a][b] = gb2[a][b] = gw3[a][b] = 0.f;
-        }
-    }
     const int64_t nwaves = (int64_t)gridDim.x * kBwWaves;
-    // the next step's features and output gradients are always in flight
     auto load_d = [&](int64_t e) { return e < nnz ? d_o[e] : 0.f; };
-    bf16x4 xn[2] = {load_x(feats, wave * 32, nnz), load_x(feats, wave * 32 + 16, nnz)};
-    float dn[2] = {load_d(wave * 32 + r), load_d(wave * 32 + 16 + r)};
-    for (int64_t e0 = wave * 32; e0 < nnz; e0 += nwaves * 32) {
-        const bf16x4 xt[2] = {xn[0], xn[1]};
-        const float dt[2] = {dn[0], dn[1]};
-        xn[0] = load_x(feats, e0 + nwaves * 32, nnz);
-        xn[1] = load_x(feats, e0 + nwaves * 32 + 16, nnz);
-        dn[0] = load_d(e0 + nwaves * 32 + r);
-        dn[1] = load_d(e0 + nwaves * 32 + 16 + r);
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            f32x4 z1[4], z2[4];
-            bf16x4 h1b[4];
-            wave_lds_sync();  // or the first tile's fragments are kept for the second: 35 registers spilled
-            tile_forward(w1, w2, vec, xt[s], z1, z2, h1b);
-            const float dout = dt[s];
-            bf16x4 dz2b[4];
-#pragma unroll
-            for (int mb = 0; mb < 4; ++mb) {
-                const f32x4 w3 = vec4(vec, kVecW3, mb);
-                float dz[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    dz[j] = z2[mb][j] > 0.f ? w3[j] * dout : 0.f;
-                    gb2[mb][j] += dz[j];
-                    gw3[mb][j] += relu(z2[mb][j]) * dout;
-                }
-                dz2b[mb] = bf16x4_of(dz[0], dz[1], dz[2], dz[3]);
-            }
-            if (g == 0) gb3 += dout;
-            bf16x4 dz1b[4];
-#pragma unroll
-            for (int mb = 0; mb < 4; ++mb) {
-                f32x4 c = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int q = 0; q < 2; ++q) c = mfma32(w2t[mb][q][l], cat8(dz2b[2 * q], dz2b[2 * q + 1]), c);
-                float dz[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    dz[j] = z1[mb][j] > 0.f ? c[j] : 0.f;
-                    gb1[mb][j] += dz[j];
-                }
-                dz1b[mb] = bf16x4_of(dz[0], dz[1], dz[2], dz[3]);
-            }
-            // stage this tile's columns (entry 16s + l%16)
-#pragma unroll
-            for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int row = 16 * mb + 4 * g + j;
-                    T[kTrDZ2 + row][16 * s + r] = (unsigned short)dz2b[mb][j];
-                    T[kTrH1 + row][16 * s + r] = (unsigned short)h1b[mb][j];
-                    T[kTrDZ1 + row][16 * s + r] = (unsigned short)dz1b[mb][j];
-                }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) T[kTrX + 4 * g + j][16 * s + r] = (unsigned short)xt[s][j];
-        }
-        wave_lds_sync();
-        // dW2[o][i] += sum_e dZ2^T[o][e] H1^T[i][e]: A = dZ2^T (o x e), B = H1 (e x i), k = 8(l/16)+j
-#pragma unroll
-        for (int ob = 0; ob < 4; ++ob) {
-            const bf16x8s a = *(const bf16x8s *)&T[kTrDZ2 + 16 * ob + r][8 * g];
-#pragma unroll
-            for (int ib = 0; ib < 4; ++ib) {
-                const bf16x8s b = *(const bf16x8s *)&T[kTrH1 + 16 * ib + r][8 * g];
-                gW2[ob][ib] = mfma32(a, b, gW2[ob][ib]);
-            }
-        }
-        // dW1[o][f] += sum_e dZ1^T[o][e] X[e][f]
-        const bf16x8s xb = *(const bf16x8s *)&T[kTrX + r][8 * g];
-#pragma unroll
-        for (int ob = 0; ob < 4; ++ob) {
-            const bf16x8s a = *(const bf16x8s *)&T[kTrDZ1 + 16 * ob + r][8 * g];
-            gW1[ob] = mfma32(a, xb, gW1[ob]);
-        }
-        wave_lds_sync();
-    }
-    // the vector terms' sums over the 16 entry lanes
-    float vb1[4][4], vb2[4][4], vw3[4][4];
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            float a = gb1[mb][j], b = gb2[mb][j], c = gw3[mb][j];
-#pragma unroll
-            for (int off = 8; off > 0; off >>= 1) {
-                a += __shfl_xor(a, off, 16);
-                b += __shfl_xor(b, off, 16);
-                c += __shfl_xor(c, off, 16);
-            }
-            vb1[mb][j] = a;
-            vb2[mb][j] = b;
-            vw3[mb][j] = c;
-        }
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) gb3 += __shfl_xor(gb3, off, 16);
-    // the block's gradient: half the waves' at a time through LDS, FP64 sums in wave order
-    float *part = reinterpret_cast<float *>(&tr[0][0][0]);
-    constexpr int kPer = (5313 + 64 * kBwWaves - 1) / (64 * kBwWaves);
-    double sum[kPer];
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) sum[k] = 0.0;
+    // FP32 sums over at most `chain` steps of a wave, then FP64: a segment. Every block takes as many as the
+    // wave with the most steps needs.
+    int64_t e0 = wave * 32;
+    const int64_t most = (nnz + nwaves * 32 - 1) / (nwaves * 32);
+    // the next step's features and output gradients are always in flight
+    bf16x4 xn[2] = {load_x(feats, e0, nnz), load_x(feats, e0 + 16, nnz)};
+    float dn[2] = {load_d(e0 + r), load_d(e0 + 16 + r)};
 #pragma unroll 1
-    for (int half = 0; half < 2; ++half) {
-        __syncthreads();
-        if (wv / (kBwWaves / 2) == half) {
-            float *out = part + (wv % (kBwWaves / 2)) * 5313;
+    for (int64_t done = 0; done < most; done += chain) {
+        f32x4 gW2[4][4], gW1[4];
+        float gb1[4][4], gb2[4][4], gw3[4][4], gb3 = 0.f;
 #pragma unroll
-            for (int ob = 0; ob < 4; ++ob) {
+        for (int a = 0; a < 4; ++a) {
+            gW1[a] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    out[kOffW1 + (16 * ob + 4 * g + j) * kF + r] = gW1[ob][j];
-#pragma unroll
-                    for (int ib = 0; ib < 4; ++ib)
-                        out[kOffW2 + (16 * ob + 4 * g + j) * kH + 16 * ib + r] = gW2[ob][ib][j];
-                }
+            for (int b = 0; b < 4; ++b) {
+                gW2[a][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                gb1[a][b] = gb2[a][b] = gw3[a][b] = 0.f;
             }
-            if (r == 0) {
+        }
+        for (const int64_t end = e0 + chain * nwaves * 32; e0 < nnz && e0 < end; e0 += nwaves * 32) {
+            const bf16x4 xt[2] = {xn[0], xn[1]};
+            const float dt[2] = {dn[0], dn[1]};
+            xn[0] = load_x(feats, e0 + nwaves * 32, nnz);
+            xn[1] = load_x(feats, e0 + nwaves * 32 + 16, nnz);
+            dn[0] = load_d(e0 + nwaves * 32 + r);
+            dn[1] = load_d(e0 + nwaves * 32 + 16 + r);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                f32x4 z1[4], z2[4];
+                bf16x4 h1b[4];
+                wave_lds_sync();  // or the first tile's fragments are kept for the second: 35 registers spilled
+                tile_forward(w1, w2, vec, xt[s], z1, z2, h1b);
+                const float dout = dt[s];
+                bf16x4 dz2b[4];
+#pragma unroll
+                for (int mb = 0; mb < 4; ++mb) {
+                    const f32x4 w3 = vec4(vec, kVecW3, mb);
+                    float dz[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        dz[j] = z2[mb][j] > 0.f ? w3[j] * dout : 0.f;
+                        gb2[mb][j] += dz[j];
+                        gw3[mb][j] += relu(z2[mb][j]) * dout;
+                    }
+                    dz2b[mb] = bf16x4_of(dz[0], dz[1], dz[2], dz[3]);
+                }
+                if (g == 0) gb3 += dout;
+                bf16x4 dz1b[4];
+#pragma unroll
+                for (int mb = 0; mb < 4; ++mb) {
+                    f32x4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) c = mfma32(w2t[mb][q][l], cat8(dz2b[2 * q], dz2b[2 * q + 1]), c);
+                    float dz[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        dz[j] = z1[mb][j] > 0.f ? c[j] : 0.f;
+                        gb1[mb][j] += dz[j];
+                    }
+                    dz1b[mb] = bf16x4_of(dz[0], dz[1], dz[2], dz[3]);
+                }
+                // stage this tile's columns (entry 16s + l%16)
 #pragma unroll
                 for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        out[kOffB1 + 16 * mb + 4 * g + j] = vb1[mb][j];
-                        out[kOffB2 + 16 * mb + 4 * g + j] = vb2[mb][j];
-                        out[kOffW3 + 16 * mb + 4 * g + j] = vw3[mb][j];
+                        const int row = 16 * mb + 4 * g + j;
+                        T[kTrDZ2 + row][16 * s + r] = (unsigned short)dz2b[mb][j];
+                        T[kTrH1 + row][16 * s + r] = (unsigned short)h1b[mb][j];
+                        T[kTrDZ1 + row][16 * s + r] = (unsigned short)dz1b[mb][j];
                     }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) T[kTrX + 4 * g + j][16 * s + r] = (unsigned short)xt[s][j];
             }
-            if (l == 0) out[kOffB3] = gb3;
+            wave_lds_sync();
+            // dW2[o][i] += sum_e dZ2^T[o][e] H1^T[i][e]: A = dZ2^T (o x e), B = H1 (e x i), k = 8(l/16)+j
+#pragma unroll
+            for (int ob = 0; ob < 4; ++ob) {
+                const bf16x8s a = *(const bf16x8s *)&T[kTrDZ2 + 16 * ob + r][8 * g];
+#pragma unroll
+                for (int ib = 0; ib < 4; ++ib) {
+                    const bf16x8s b = *(const bf16x8s *)&T[kTrH1 + 16 * ib + r][8 * g];
+                    gW2[ob][ib] = mfma32(a, b, gW2[ob][ib]);
+                }
+            }
+            // dW1[o][f] += sum_e dZ1^T[o][e] X[e][f]
+            const bf16x8s xb = *(const bf16x8s *)&T[kTrX + r][8 * g];
+#pragma unroll
+            for (int ob = 0; ob < 4; ++ob) {
+                const bf16x8s a = *(const bf16x8s *)&T[kTrDZ1 + 16 * ob + r][8 * g];
+                gW1[ob] = mfma32(a, xb, gW1[ob]);
+            }
+            wave_lds_sync();
         }
-        __syncthreads();
+        // the vector terms' sums over the 16 entry lanes
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                gb1[mb][j] = row_sum(gb1[mb][j]);
+                gb2[mb][j] = row_sum(gb2[mb][j]);
+                gw3[mb][j] = row_sum(gw3[mb][j]);
+            }
+        gb3 = row_sum(gb3);
+        // the block's gradient: half the waves' at a time through LDS, FP64 sums in wave order
+        float *part = reinterpret_cast<float *>(&tr[0][0][0]);
+        int tid = (int)threadIdx.x;
+        asm volatile("" : "+v"(tid));  // or the sums' addresses are held through the segment
+        const int lr = tid & 15, lg = (tid >> 4) & 3;
+        constexpr int kPer = (kGradRow / 4 + 64 * kBwWaves - 1) / (64 * kBwWaves);
+        double sum[kPer][4];
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) sum[k][0] = sum[k][1] = sum[k][2] = sum[k][3] = 0.0;
+#pragma unroll 1
+        for (int half = 0; half < 2; ++half) {
+            __syncthreads();
+            if (wv / (kBwWaves / 2) == half) {
+                float *out = part + (wv % (kBwWaves / 2)) * kSumAll;
+#pragma unroll
+                for (int ob = 0; ob < 4; ++ob) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int row = 16 * ob + 4 * lg + j;
+                        out[row * kSumRow1 + lr] = gW1[ob][j];
+#pragma unroll
+                        for (int ib = 0; ib < 4; ++ib) out[kSumW2 + row * kSumRow2 + 16 * ib + lr] = gW2[ob][ib][j];
+                    }
+                }
+                if (lr == 0) {
+#pragma unroll
+                    for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            out[kSumB1 + 16 * mb + 4 * lg + j] = gb1[mb][j];
+                            out[kSumB2 + 16 * mb + 4 * lg + j] = gb2[mb][j];
+                            out[kSumW3 + 16 * mb + 4 * lg + j] = gw3[mb][j];
+                        }
+                }
+                if ((tid & 63) < 4) out[kSumB3 + (tid & 63)] = (tid & 63) == 0 ? gb3 : 0.f;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                const int e = 4 * (k * 64 * kBwWaves + tid);
+                if (e >= kGradRow) continue;
+                const float *from = part + sum_at(e);
+#pragma unroll
+                for (int v = 0; v < kBwWaves / 2; ++v) {
+                    const f32x4 q = *reinterpret_cast<const f32x4 *>(from + v * kSumAll);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) sum[k][j] += (double)q[j];
+                }
+            }
+        }
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
-            const int e = k * 64 * kBwWaves + (int)threadIdx.x;
-            if (e < 5313)
-#pragma unroll
-                for (int v = 0; v < kBwWaves / 2; ++v) sum[k] += (double)part[v * 5313 + e];
+            const int e = 4 * (k * 64 * kBwWaves + tid);
+            if (e >= kGradRow) continue;
+            double2 *to = reinterpret_cast<double2 *>(gpart + (int64_t)blockIdx.x * kGradRow + e);  // this thread's own
+            const double2 p = done > 0 ? to[0] : double2{0.0, 0.0}, q = done > 0 ? to[1] : double2{0.0, 0.0};
+            to[0] = double2{p.x + sum[k][0], p.y + sum[k][1]};
+            to[1] = double2{q.x + sum[k][2], q.y + sum[k][3]};
         }
-    }
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const int e = k * 64 * kBwWaves + (int)threadIdx.x;
-        if (e < 5313) gpart[(int64_t)blockIdx.x * 5313 + e] = sum[k];
+        __syncthreads();  // the staging area is the next segment's
     }
 }
 
@@ -751,7 +787,7 @@ __global__ void k_grad_reduce(const double *__restrict__ gpart, int64_t nblocks,
     const int64_t per = (nblocks + kGradChunks - 1) / kGradChunks;
     const int64_t b0 = (int64_t)blockIdx.y * per, b1 = b0 + per < nblocks ? b0 + per : nblocks;
     double s = 0.0;
-    for (int64_t b = b0; b < b1; ++b) s += gpart[b * 5313 + k];
+    for (int64_t b = b0; b < b1; ++b) s += gpart[b * kGradRow + k];
     part2[(int64_t)blockIdx.y * 5313 + k] = s;
 }
 __global__ void k_grad_finish(const double *__restrict__ part2, float *__restrict__ grad) {
@@ -941,6 +977,8 @@ static unsigned mlp_grid(int64_t nnz, int64_t resident) {
     return (unsigned)std::min<int64_t>((steps + kWaves - 1) / kWaves, resident);
 }
 constexpr int64_t kForwardBlocks = 1024, kBackwardBlocks = 256;
+// Steps of 32 entries that the backward pass sums in FP32: those of one of 8192 waves.
+static int64_t backward_chain(int64_t nnz) { return std::max<int64_t>(1, ((nnz + 31) / 32 + 8191) / 8192); }
 
 int qh_learned_factor(qh_ctx *c) {
     LearnedPrec &L = c->lp;
@@ -1040,7 +1078,7 @@ int qh_learned_loss_grad(qh_ctx *c, const float *V_dev, bool want_grad, double p
         if ((rc = qh_alloc(c, &L.W, (int64_t)n * kP)) || (rc = qh_alloc(c, &L.AW, (int64_t)n * kP)) ||
             (rc = qh_alloc(c, &L.tpart, 2048 * kP)) ||
             (rc = qh_alloc(c, &L.lpart, (L.nnz + 255) / 256)) ||
-            (rc = qh_alloc(c, &L.gpart, (int64_t)mlp_grid(L.nnz, kBackwardBlocks) * 5313)) ||
+            (rc = qh_alloc(c, &L.gpart, (int64_t)mlp_grid(L.nnz, kBackwardBlocks) * kGradRow)) ||
             (rc = qh_alloc(c, &L.gpart2, (int64_t)kGradChunks * 5313)))
             return rc;
     }
@@ -1090,7 +1128,8 @@ int qh_learned_loss_grad(qh_ctx *c, const float *V_dev, bool want_grad, double p
     }
     if (want_grad) {
         const unsigned gm = mlp_grid(L.nnz, kBackwardBlocks);
-        hipLaunchKernelGGL(k_mlp_backward, dim3(gm), dim3(64 * kBwWaves), 0, c->stream, L.w, L.feats, L.d_o, L.nnz, L.gpart);
+        hipLaunchKernelGGL(k_mlp_backward, dim3(gm), dim3(64 * kBwWaves), 0, c->stream, L.w, L.feats, L.d_o, L.nnz,
+                           backward_chain(L.nnz), L.gpart);
         hipLaunchKernelGGL(k_grad_reduce, dim3((5313 + 255) / 256, kGradChunks), dim3(256), 0, c->stream, L.gpart,
                            (int64_t)gm, L.gpart2);
         hipLaunchKernelGGL(k_grad_finish, dim3((5313 + 255) / 256), dim3(256), 0, c->stream, L.gpart2, L.grad);
