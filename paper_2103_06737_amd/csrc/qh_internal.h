@@ -399,7 +399,6 @@ struct SolveResult {
     bool true_ok = false;   // the recomputed residual meets the target
     int flag = 0;           // why the iteration stopped: 0 iteration cap, 1 target met, 2 stall rule
                             // (learned preconditioner), 3 non-finite values
-    int restarts = 0;       // restarts from the iterate after the recomputed residual missed the target
     int refinements = 0;    // mixed precision: reliable updates (FP64 residuals after the start)
 };
 int qh_cg_alloc(qh_ctx *c, CgWork &w, int32_t n);

@@ -1,4 +1,4 @@
-// Implicit field update on gfx950 (Sec. IV.B): FP64 CSR products, preconditioned conjugate
+// Implicit field update on gfx950 (Sec. IV.B): FP64 products on slices of 64 rows, preconditioned conjugate
 // gradients with FP64 dot products reduced in a fixed order (deterministic iteration counts),
 // the Gauss-law solve for the non-solenoidal part and the integer Faraday update.
 //
@@ -454,7 +454,7 @@ __global__ void __launch_bounds__(kThreads) k_residual(int32_t n, int32_t ns, co
 
 // Mixed-precision solve. Start: the FP32 system A d = r0 / s, s = ||r0|| (a unit right-hand
 // side), from d = 0: r32 = r0 / s, d = p = 0, with Jacobi z = D^-1 r32; partials of r.z (Jacobi),
-// r.r and b.b (= r.r here). rr: ||r0||^2 on the device; s is kept in scal[S_SCALE] for the solve.
+// r.r. rr: ||r0||^2 on the device; s is kept in scal[S_SCALE] for the solve.
 template <bool JAC>
 __global__ void __launch_bounds__(kThreads) k_inner_init(int32_t n, const double *__restrict__ r, const double *rr,
                                                          double *scal, float *__restrict__ r32,
@@ -463,7 +463,7 @@ __global__ void __launch_bounds__(kThreads) k_inner_init(int32_t n, const double
                                                          float *__restrict__ dinv32, double *__restrict__ part) {
     const double s = sqrt(*rr), inv = 1.0 / s;
     if (blockIdx.x == 0 && threadIdx.x == 0) scal[S_SCALE] = s;
-    double acc[3] = {0.0, 0.0, 0.0};
+    double acc[2] = {0.0, 0.0};
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
         const float ri = (float)(r[i] * inv);
         r32[i] = ri;
@@ -478,8 +478,7 @@ __global__ void __launch_bounds__(kThreads) k_inner_init(int32_t n, const double
         }
         acc[1] += (double)ri * (double)ri;
     }
-    acc[2] = acc[1];
-    write_partials<3>(acc, part);
+    write_partials<2>(acc, part);
 }
 
 // Reliable update, first half: x += s d in FP64 and d = 0. A batch that met non-finite values is not
@@ -590,11 +589,10 @@ __global__ void __launch_bounds__(kSmallThreads) k_solve_small(
         int32_t c[kResA];
         const int32_t o0 = wid * S.width;
         const int64_t e0 = (int64_t)o0 * kSlice + lane;
-        const bool wide = *sell_bases(S, o0) < 0;
 #pragma unroll
-        for (int u = 0; u < kResA; ++u) {
+        for (int u = 0; u < kResA; ++u) {  // at most 1024 unknowns: 16-bit columns
             av[u] = u < S.width ? val[e0 + u * kSlice] : 0.0;
-            c[u] = u >= S.width ? 0 : wide ? S.c32[e0 + u * kSlice] : S.base[o0 + u] + (int32_t)S.c16[e0 + u * kSlice];
+            c[u] = u < S.width ? S.base[o0 + u] + (int32_t)S.c16[e0 + u * kSlice] : 0;
         }
 #pragma unroll
         for (int u = 0; u < kResA / 2; ++u) ac[u] = (uint32_t)c[2 * u] | (uint32_t)c[2 * u + 1] << 16;
@@ -1310,7 +1308,6 @@ int qh_cg_solve(qh_ctx *c, const DevSell &M, CgWork &w, double tol, int max_it, 
         }
         out.converged = out.flag == CG_CONVERGED && out.true_ok;
         if (out.converged || out.flag != CG_CONVERGED || it >= max_it || restart == kRestarts) break;
-        out.restarts = restart + 1;
     }
     if (out.converged) w.last_iters[learned ? 1 : 0] = out.iters;
     return QH_OK;
