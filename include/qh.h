@@ -102,17 +102,22 @@ typedef struct {
     double tol_edge;     /* relative residual of the edge solve (e.g. 1e-8) */
     double tol_node;     /* Gauss-law residual target, relative to ||rho|| + || |G^T[*eps]| |e| || */
     int32_t max_it_edge, max_it_node;
-    int32_t check_every; /* iterations between host reads of the convergence flag; the first read
-                            of a solve comes after as many iterations as the previous solve of
-                            the same system and preconditioner took (QH_SOLVER_MIXED: a read and
+    int32_t check_every; /* least number of iterations between host reads of the convergence flag; the first
+                            read of a solve comes after as many iterations as the previous solve of
+                            the same system and preconditioner took, or after check_every without one, a
+                            later one after most of those that the solve's rate leaves to do, at most
+                            twice those done (QH_SOLVER_MIXED: a read and
                             reliable update each time the previous solve had reduced its residual
-                            by another 1e-4, the last at its iteration count) */
+                            by another 1e-4, the last at its iteration count, and wherever the present
+                            one has by 3e-5). Systems solved in one launch (see solver) are read once */
     int32_t verify;      /* 1: check continuity and D b on the device every step */
     int32_t solver;      /* edge solve: QH_SOLVER_FP64 (0), or QH_SOLVER_MIXED (1): PCG in FP32 (FP32
                             copy of A's values and FP32 vectors, FP64 products and dot products, the
                             same preconditioner) with reliable updates in FP64 (x accumulated and
                             b - A x recomputed in FP64 between batches, replacing the FP32
-                            residual), stopping on the same FP64 residual tol_edge */
+                            residual), stopping on the same FP64 residual tol_edge. Systems of at most
+                            2048 unknowns (1536 with the learned preconditioner) are solved in one
+                            launch and in FP64 whichever is asked for */
 } qh_step_params_t;
 
 #define QH_SOLVER_FP64 0
@@ -131,7 +136,9 @@ typedef struct {
     double gauss_res_rho;           /* ||rho - G^T[*eps] e|| / ||rho|| (0 when rho = 0): the same residual
                                        against the charge alone, for comparison with gauss_res */
     int32_t edge_refinements;       /* QH_SOLVER_MIXED: reliable updates of the edge solve (FP64
-                                       residuals recomputed after the start); 0 otherwise */
+                                       residuals recomputed after the start; 1 for a system solved in
+                                       one launch, its final residual; 0 where the start met the target or
+                                       was not finite); 0 otherwise */
 } qh_step_stats_t;
 
 typedef struct {
@@ -343,8 +350,9 @@ int qh_fields_energy(qh_ctx *ctx, double *w_e, double *w_m);
 /* Solve system (QH_SYS_EDGE or QH_SYS_NODE) A x = rhs on its interior unknowns
  * (n_int_edges or n_int_nodes values), to ||rhs - A x|| <= tol ||rhs|| in FP64: FP64 PCG with
  * FP64 dot products (solver = QH_SOLVER_FP64), or FP32 PCG with FP64 reliable updates
- * (QH_SOLVER_MIXED). x holds the initial guess on entry. A learned or mixed solve that does not
- * converge is restarted as FP64 Jacobi-PCG (stats->fallback = 1). */
+ * (QH_SOLVER_MIXED; small systems as in qh_step_params_t). x holds the initial guess on entry. A
+ * learned or mixed solve that does not converge is restarted as FP64 Jacobi-PCG
+ * (stats->fallback = 1). */
 int qh_field_solve(qh_ctx *ctx, int32_t system, const double *rhs, double *x, double tol,
                    int32_t max_it, int32_t precond, int32_t solver, qh_solve_stats_t *stats);
 

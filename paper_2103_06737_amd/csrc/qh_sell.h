@@ -15,7 +15,8 @@
 // round of loads has exactly as many entries as it needs: with four column windows per slice to select
 // from and a test per entry, the products at 64^3 (FP32, learned; us) took 54.4 for A, 28.9 for the
 // update with G, 23.0 for G^T, now 50.6, 24.9, 19.9; at 48^3 19.4, 12.9, 10.3, now 16.3, 10.9, 8.3.
-// At 64^3 the three read about 350 MB, more than the last-level cache holds, at 3.7 TB/s.
+// At 64^3 the three read and write about 406 MB with their vectors, more than the last-level cache holds, at
+// 4.3 TB/s (counted in HBM: 222 + 123 + 82 MB).
 #pragma once
 
 #include <type_traits>
@@ -82,8 +83,8 @@ __device__ __forceinline__ SellRange sell_range(int32_t ns) {
     return r;
 }
 
-// Every wave gets the same number of slices, as few waves as that needs: at 64^3 (28,100 slices)
-// 879 blocks of eight waves with four slices each.
+// Every wave gets the same number of slices, as few waves as that needs: at 64^3 (28,099 slices)
+// 880 blocks of eight waves with four slices each.
 inline unsigned sell_grid(int32_t ns) {
     const int64_t most = (int64_t)kSellMaxBlocks * kSellWaves;
     const int64_t per = ns > most ? (ns + most - 1) / most : 1;
