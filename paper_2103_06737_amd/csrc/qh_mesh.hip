@@ -61,7 +61,8 @@ std::vector<int32_t> order_in_space(const HostMesh &m) {
     for (int64_t v = 0; v < m.Nn; ++v) {
         uint64_t k = 0;
         for (int d = 0; d < 3; ++d) {  // 21 bits of each coordinate, every third bit of the key
-            uint64_t q = std::min<uint64_t>((uint64_t)((m.xyz[3 * v + d] - lo[d]) * inv[d]), 2097151);
+            const double t = (m.xyz[3 * v + d] - lo[d]) * inv[d];  // anything in a node of no tet
+            uint64_t q = t > 0.0 ? (t < 2097151.0 ? (uint64_t)t : 2097151) : 0;
             q = (q | q << 32) & 0x1f00000000ffffull;
             q = (q | q << 16) & 0x1f0000ff0000ffull;
             q = (q | q << 8) & 0x100f00f00f00f00full;
