@@ -985,9 +985,11 @@ int qh_edge_system_download(const qh_ctx *cc, double *rhs, double *sol) {
     if (!c) return QH_EINVAL;
     if (c->host_only) return qh_fail(c, QH_ESTATE, "host-only context has no device");
     if (!c->assembled) return qh_fail(c, QH_ESTATE, "mesh and physics first");
-    int rc;
-    if (rhs && (rc = edge_to_host(c, c->cge.b, c->cge.z, rhs))) return rc;
-    if (sol && (rc = edge_to_host(c, c->e_star, c->cge.q, sol))) return rc;
+    // both renumbered before the first copy waits
+    if (rhs) QH_HIP(c, launch_renumber(c, c->A.n, c->pos_of, c->cge.b, c->cge.z));
+    if (sol) QH_HIP(c, launch_renumber(c, c->A.n, c->pos_of, c->e_star, c->cge.q));
+    if (rhs) QH_HIP(c, hipMemcpyAsync(rhs, c->cge.z, sizeof(double) * c->A.n, hipMemcpyDeviceToHost, c->stream));
+    if (sol) QH_HIP(c, hipMemcpyAsync(sol, c->cge.q, sizeof(double) * c->A.n, hipMemcpyDeviceToHost, c->stream));
     return sync(c);
 }
 

@@ -232,22 +232,29 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_mlp_factor(const float *__re
     }
 }
 
-// G^T values out[k] = in[src[k]]
+// G^T values out[k] = in[src[k]] (training)
 __global__ void k_gather_f32(int64_t n, const int32_t *__restrict__ src, const float *__restrict__ in,
                              float *__restrict__ out) {
     int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k < n) out[k] = in[src[k]];
 }
 
-// BF16 copy of G or G^T for the application, packed with the 16-bit columns (value bits high,
-// column low) in the order of the slices (src: entry of in, -1: padding)
-__global__ void k_pack_slices(int64_t len, const int32_t *__restrict__ src, const float *__restrict__ in,
-                              const uint16_t *__restrict__ c16, uint32_t *__restrict__ pk) {
+// BF16 copies of G and G^T for the application, packed with the 16-bit columns (value bits high, column
+// low) in the order of the slices (src: entry of in, -1: padding), both in one launch.
+struct PackPart {
+    int64_t len;
+    const int32_t *src;
+    const uint16_t *c16;
+    uint32_t *pk;
+};
+__global__ void k_pack_slices(const PackPart G, const PackPart T, const float *__restrict__ in) {
     int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= len) return;
-    const int32_t e = src[k];
+    const bool first = k < G.len;
+    if (!first) k -= G.len;
+    if (k >= (first ? G.len : T.len)) return;
+    const int32_t e = first ? G.src[k] : T.src[k];
     const uint32_t h = e >= 0 ? (uint16_t)f2bf(in[e]) : 0u;
-    pk[k] = h << 16 | c16[k];
+    (first ? G.pk : T.pk)[k] = h << 16 | (first ? G.c16[k] : T.c16[k]);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -984,8 +991,6 @@ int qh_learned_factor(qh_ctx *c) {
     LearnedPrec &L = c->lp;
     hipLaunchKernelGGL(k_mlp_factor, dim3(mlp_grid(L.nnz, kForwardBlocks)), dim3(64 * kWaves), 0, c->stream, L.w, L.feats, L.grow,
                        L.gcol, L.gscale, L.nnz, L.o, L.gval);
-    hipLaunchKernelGGL(k_gather_f32, dim3((unsigned)((L.nnz + 255) / 256)), dim3(256), 0, c->stream, L.nnz, L.tsrc,
-                       L.gval, L.tval);
     QH_HIP(c, hipGetLastError());
     L.factor_valid = true;
     L.pk_valid = false;
@@ -999,10 +1004,10 @@ unsigned qh_prec_grid(qh_ctx *c) { return sell_grid(c->lp.gs.ns); }
 static void pack_factor(qh_ctx *c) {
     LearnedPrec &L = c->lp;
     if (L.pk_valid) return;
-    hipLaunchKernelGGL(k_pack_slices, dim3((unsigned)((L.gs.len + 255) / 256)), dim3(256), 0, c->stream, L.gs.len,
-                       L.gs.src, L.gval, L.gs.c16, L.gpk);
-    hipLaunchKernelGGL(k_pack_slices, dim3((unsigned)((L.ts.len + 255) / 256)), dim3(256), 0, c->stream, L.ts.len,
-                       L.ts.src, L.gval, L.ts.c16, L.tpk);
+    const int64_t len = L.gs.len + L.ts.len;
+    hipLaunchKernelGGL(k_pack_slices, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, c->stream,
+                       PackPart{L.gs.len, L.gs.src, L.gs.c16, L.gpk}, PackPart{L.ts.len, L.ts.src, L.ts.c16, L.tpk},
+                       (const float *)L.gval);
     L.pk_valid = true;
 }
 
@@ -1073,6 +1078,8 @@ int qh_learned_loss_grad(qh_ctx *c, const float *V_dev, bool want_grad, double p
     LearnedPrec &L = c->lp;
     int rc;
     if ((rc = qh_learned_factor(c))) return rc;
+    hipLaunchKernelGGL(k_gather_f32, dim3((unsigned)((L.nnz + 255) / 256)), dim3(256), 0, c->stream, L.nnz, L.tsrc,
+                       L.gval, L.tval);
     const int32_t n = L.n;
     if (!L.W) {
         if ((rc = qh_alloc(c, &L.W, (int64_t)n * kP)) || (rc = qh_alloc(c, &L.AW, (int64_t)n * kP)) ||
