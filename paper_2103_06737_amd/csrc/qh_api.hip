@@ -57,10 +57,11 @@ int upload(qh_ctx *c, T **dst, const T *src, size_t n) {
     return QH_OK;
 }
 
-// A host matrix on slices with its values (rows, cpos: as qh_build_sell).
-int upload_sell_values(qh_ctx *c, DevSell &d, const HostCsr &h, const int32_t *rows, const int32_t *cpos) {
+// A host matrix on slices with its values (rows, cpos, packed: as qh_build_sell).
+int upload_sell_values(qh_ctx *c, DevSell &d, const HostCsr &h, const int32_t *rows, const int32_t *cpos,
+                       bool packed = false) {
     SellHost sh;
-    qh_build_sell((int32_t)h.nrow, h.ptr.data(), h.col.data(), rows, cpos, sh);
+    qh_build_sell((int32_t)h.nrow, h.ptr.data(), h.col.data(), rows, cpos, sh, false, packed);
     std::vector<double> v(sh.src.size(), 0.0);
     for (size_t i = 0; i < sh.src.size(); ++i)
         if (sh.src[i] >= 0) v[i] = h.val[sh.src[i]];
@@ -145,7 +146,8 @@ int ensure_assembled(qh_ctx *c) {
             // random, Jacobi, FP64 and mixed: 1553 and 1497 us, 32-bit 1544 and 1485; 48^3: 5182 and 4239, 5484
             // and 4477): those systems read 32-bit ones throughout.
             const bool wide = m.in_space && c->A.n <= 1 << 17;
-            qh_build_sell(c->A.n, c->hA.ptr.data(), c->hA.col.data(), m.order.data(), m.pos_of.data(), sh, wide);
+            qh_build_sell(c->A.n, c->hA.ptr.data(), c->hA.col.data(), m.order.data(), m.pos_of.data(), sh, wide,
+                          m.in_space);
             c->nnz_edge_c16 = sh.nnz_c16;
             if ((rc = qh_upload_sell(c, c->As, sh)) || (rc = qh_alloc(c, &c->As.val, (size_t)c->As.len)) ||
                 (rc = qh_alloc(c, &c->A_rhs, (size_t)c->As.len)) || (rc = qh_alloc(c, &c->As_eps, (size_t)c->As.len)) ||
@@ -158,8 +160,9 @@ int ensure_assembled(qh_ctx *c) {
         // rows of C^T [*mu^-1] in interior-edge order, or in the device numbering (k_edge_rhs_b)
         const bool by_device = m.in_space || columns_far_apart(c->hCMb);
         c->CMb_pos = by_device ? nullptr : c->pos_of;
-        if ((rc = upload_sell_values(c, c->CMb, c->hCMb, by_device ? m.order.data() : nullptr, nullptr)) ||
-            (rc = upload_sell_values(c, c->GtM, c->hGtM, nullptr, m.pos_of.data())) ||
+        if ((rc = upload_sell_values(c, c->CMb, c->hCMb, by_device ? m.order.data() : nullptr, nullptr,
+                                     m.in_space)) ||
+            (rc = upload_sell_values(c, c->GtM, c->hGtM, nullptr, m.pos_of.data(), m.in_space)) ||
             (rc = upload_sell_values(c, c->K, c->hK, nullptr, nullptr)))
             return rc;
         if ((rc = qh_cg_alloc(c, c->cge, c->A.n))) return rc;

@@ -884,8 +884,8 @@ int qh_learned_setup(qh_ctx *c) {
         QH_HIP(c, hipMemcpyAsync(L.tsrc, tsrc.data(), 4 * nnz, hipMemcpyHostToDevice, c->stream));
         // G and G^T on slices, unknowns in device numbering; G^T's entries refer to G's
         SellHost gh, th;
-        qh_build_sell(n, gptr.data(), gcol.data(), m.order.data(), m.pos_of.data(), gh);
-        qh_build_sell(n, tptr.data(), tcol.data(), m.order.data(), m.pos_of.data(), th);
+        qh_build_sell(n, gptr.data(), gcol.data(), m.order.data(), m.pos_of.data(), gh, false, m.in_space);
+        qh_build_sell(n, tptr.data(), tcol.data(), m.order.data(), m.pos_of.data(), th, false, m.in_space);
         for (int32_t &q : th.src)
             if (q >= 0) q = tsrc[q];
         L.nnz_c16 = gh.nnz_c16 + th.nnz_c16;

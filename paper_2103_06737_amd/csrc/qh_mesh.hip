@@ -581,7 +581,7 @@ void place_row(int32_t cnt, int32_t fw, D &&d, T &&t, std::vector<int32_t> &slot
 }  // namespace
 
 void qh_build_sell(int32_t n, const int32_t *ptr, const int32_t *col, const int32_t *rows, const int32_t *cpos,
-                   SellHost &o, bool wide) {
+                   SellHost &o, bool wide, bool packed) {
     constexpr int32_t kSpan = 1 << 16;
     o = SellHost();
     o.n = n;
@@ -633,7 +633,7 @@ void qh_build_sell(int32_t n, const int32_t *ptr, const int32_t *col, const int3
             const int32_t r = row_of(l);
             const int32_t j0 = r < 0 ? 0 : ptr[r], cnt = r < 0 ? 0 : ptr[r + 1] - ptr[r];
             place_row(
-                cnt, fw, [&](int32_t k) { return column(j0 + k) - l; },
+                cnt, packed ? cnt : fw, [&](int32_t k) { return column(j0 + k) - l; },
                 [&](int32_t k) { return column(f0 + k) - full; }, slots, cost);
             for (int32_t k = 0; k < cnt; ++k) {
                 const size_t e = e0 + (size_t)slots[k] * kSlice + l;
