@@ -104,7 +104,7 @@ std::vector<int32_t> inverse(const std::vector<int32_t> &order) {
 // per matrix entry, over a sample of slices (k-th entries of 64 rows side by side; a row shorter than the
 // longest gathers its last column again).
 double lines_per_entry(const HostMesh &m, const std::vector<int32_t> &order, const std::vector<int32_t> &pos) {
-    constexpr int32_t kSample = 128;
+    constexpr int32_t kSample = 16;  // 0.3 ms
     const int32_t n = (int32_t)order.size(), ns = n / kSlice;
     int64_t lines = 0, entries = 0;
     std::vector<int32_t> col[kSlice], at;
@@ -134,9 +134,9 @@ double lines_per_entry(const HostMesh &m, const std::vector<int32_t> &order, con
     return entries > 0 ? (double)lines / (double)entries : 0.0;
 }
 
-// By rank, unless the mesh's numbering makes that a bad order: on the repository's boxes and cylinders it
-// touches 0.10 to 0.29 lines per entry; on boxes numbered at random 0.86 to 1.09 against 0.26 along the curve,
-// on Delaunay meshes of points in random order or in slabs 1.0 to 1.7 against 0.44 to 0.50. A learned
+// By rank, unless the mesh's numbering makes that a bad order: on boxes and cylinders numbered line by line it
+// touches 0.10 to 0.28 lines per entry; on boxes numbered at random 0.87 to 1.08 against 0.25 to 0.27 along the
+// curve, on Delaunay meshes of points in random order or in slabs 0.94 to 1.7 against 0.46 to 0.52. A learned
 // mixed-precision solve to 1e-8 on a 48^3 box numbered at random took 11.2 ms by rank, 4.4 along the curve (the
 // tiled products before the slices: 6.3); FP64 Jacobi on 100,000 points in random order 27.1 -> 11.1 (16.7).
 // Up to 2048 unknowns a solve keeps its vectors in LDS, whatever their order.
